@@ -1,0 +1,756 @@
+"""Workloads of the stitching framework, by size: what a program that uses it calls per frame,
+per batch of jobs, per registration and per refinement step.
+
+A case is a dict of plain values.  `prepare` makes what such a program holds before the call
+(frames on the GPU, or pinned on the host for the pipe; the bound plan, batch, workspace or
+feature set it keeps), `run` is one pass through the public entry points and returns what they
+compute, `work` the bytes and operations that pass cannot do without, `exact` the floating
+outputs in 64 bits by plain torch and numpy.
+
+Rigs are rings of equal cameras side by side on one canvas (neighbours share `overlap` of a
+frame's width, small residual yaws and rolls), seams at the middle of the overlaps, cut hard
+or feathered over `feather` columns.  Frames see one multi-octave texture through their maps.
+"""
+from __future__ import annotations
+
+import math
+
+import numpy as np
+import torch
+
+import paper_1810_03988_amd as P
+
+DEV = "cuda"
+
+
+# ----------------------------------------------------------------------------- the cases
+def listed() -> list:
+    return [
+        # the smallest planned rig in use: two VGA cameras, one frame set at a time, where
+        # launches and latency count
+        dict(name="frame_pair_vga_f32", kind="frame", n=2, w=640, h=480, overlap=0.375, yaw=0.0, roll=2.0,
+             levels=5, storage="f32", feather=0),
+        # four 1080p cameras, the ordinary live rig, default storage
+        dict(name="frame_rig_1080p_f32", kind="frame", n=4, w=1920, h=1080, overlap=0.15, yaw=3.0, roll=0.0,
+             levels=6, storage="f32", feather=0),
+        # four 4K cameras at half-precision storage, the largest single rig
+        dict(name="frame_rig_4k_f16", kind="frame", n=4, w=3840, h=2160, overlap=0.15, yaw=3.0, roll=0.0,
+             levels=7, storage="f16", feather=64),
+        # offline stitching of many jobs of mixed resolutions in one captured launch sequence
+        dict(name="batch_mixed_f16", kind="batch", jobs=8, wmin=640, wmax=3840, levels=0, storage="f16",
+             feather=0, geom=3),
+        # the same form on odd frame sizes at default storage
+        dict(name="batch_ragged_f32", kind="batch", jobs=5, wmin=321, wmax=1283, levels=4, storage="f32",
+             feather=33, geom=8),
+        # live video from host memory to host memory: uploads, stitching, downloads in flight
+        dict(name="pipe_1080p_f32", kind="pipe", n=2, w=1920, h=1080, overlap=0.2, yaw=2.0, roll=0.0, levels=5,
+             storage="f32", feather=0, sets=4, depth=2),
+        # a program that calls the stages itself: warp, band and weight pyramids, blend
+        dict(name="stages_vga_f32", kind="stages", n=2, w=641, h=479, overlap=0.3, yaw=1.0, roll=1.0, levels=4,
+             storage="f32", feather=17),
+        dict(name="stages_1080p_f16", kind="stages", n=3, w=1920, h=1080, overlap=0.15, yaw=2.0, roll=0.0, levels=5,
+             storage="f16", feather=0),
+        # registration front end: features of every camera of a rig in its overlap areas
+        dict(name="lorb_rig_1080p", kind="lorb", n=4, w=1920, h=1080, overlap=0.15, yaw=3.0, roll=0.0, n_max=500,
+             nd=256, fast=20),
+        # registration back end: matching and PROSAC of the neighbouring pairs of that rig
+        dict(name="register_3_pairs", kind="register", pairs=3, points=500, nd=256, tables=6, kbits=14, nhyp=1024),
+        # the differentiable form: stitched float panorama and its vector-Jacobian product
+        dict(name="vjp_pair_720p", kind="vjp", n=2, w=1280, h=720, overlap=0.2, yaw=1.0, roll=0.0, levels=3,
+             feather=0),
+        # refinement of a pair's map on the stitched result: freeze, loss and gradient, twice
+        dict(name="refine_pair_720p", kind="refine", w=1280, h=720, overlap=0.2, yaw=1.0, levels=3, steps=2),
+    ]
+
+
+def _log(rng, lo, hi) -> int:
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def _levels(rng, w, h, n=4) -> int:
+    """A level count that leaves the top level at least eight samples a side."""
+    return rng.randint(2, max(2, min(7, int(math.log2(min(w, h))) - 3)))
+
+
+def draw(rng) -> dict:
+    kind = rng.choice(["frame", "frame", "batch", "pipe", "stages", "stages", "lorb", "register", "vjp", "refine"])
+    ring = dict(overlap=round(rng.uniform(0.10, 0.30), 3), yaw=round(rng.uniform(0.0, 3.0), 2),
+                roll=round(rng.uniform(-1.5, 1.5), 2))
+    feather = rng.choice([0, 0, rng.randint(2, 80)])
+    if kind == "frame":
+        w = _log(rng, 160, 3840)
+        h = max(96, int(w * rng.uniform(0.5, 0.8)))
+        return dict(kind=kind, n=rng.randint(2, 4), w=w, h=h, levels=_levels(rng, w, h),
+                    storage=rng.choice(["f32", "f16"]), feather=feather, **ring)
+    if kind == "batch":
+        lo = _log(rng, 160, 640)
+        return dict(kind=kind, jobs=rng.randint(2, 8), wmin=lo, wmax=min(3840, lo * rng.randint(1, 5)),
+                    levels=rng.choice([0, 3, 4]), storage=rng.choice(["f32", "f16"]), feather=feather,
+                    geom=rng.randint(100, 10 ** 6))
+    if kind == "pipe":
+        w = _log(rng, 320, 1920)
+        h = max(180, int(w * rng.uniform(0.5, 0.8)))
+        return dict(kind=kind, n=rng.randint(2, 3), w=w, h=h, levels=min(5, _levels(rng, w, h)),
+                    storage=rng.choice(["f32", "f16"]), feather=feather, sets=rng.randint(2, 5),
+                    depth=rng.randint(1, 3), **ring)
+    if kind == "stages":
+        w = _log(rng, 200, 1920)
+        h = max(120, int(w * rng.uniform(0.5, 0.8)))
+        return dict(kind=kind, n=rng.randint(2, 3), w=w, h=h, levels=min(5, _levels(rng, w, h)),
+                    storage=rng.choice(["f32", "f16"]), feather=feather, **ring)
+    if kind == "lorb":
+        w = _log(rng, 320, 2304)
+        return dict(kind=kind, n=rng.randint(2, 6), w=w, h=max(240, int(w * rng.uniform(0.5, 0.8))),
+                    n_max=_log(rng, 60, 1000), nd=rng.choice([96, 128, 256, 512]), fast=rng.randint(8, 30), **ring)
+    if kind == "register":
+        return dict(kind=kind, pairs=rng.randint(1, 8), points=_log(rng, 60, 2000), nd=rng.choice([128, 256, 512]),
+                    tables=rng.randint(2, 8), kbits=rng.randint(8, 16), nhyp=_log(rng, 128, 2048))
+    if kind == "vjp":
+        w = _log(rng, 160, 1280)
+        h = max(96, int(w * rng.uniform(0.5, 0.6)))
+        return dict(kind=kind, n=rng.randint(2, 3), w=w, h=h, levels=min(4, _levels(rng, w, h)), feather=feather,
+                    **ring)
+    w = _log(rng, 200, 1280)
+    h = max(120, int(w * rng.uniform(0.5, 0.6)))
+    return dict(kind="refine", w=w, h=h, overlap=ring["overlap"], yaw=ring["yaw"], levels=min(4, _levels(rng, w, h)),
+                steps=2)
+
+
+# ----------------------------------------------------------------------------- rigs and frames
+def _T(x, y):
+    return np.array([[1.0, 0.0, x], [0.0, 1.0, y], [0.0, 0.0, 1.0]])
+
+
+def _rig(n, w, h, overlap, yaw, roll, feather=0):
+    """Maps (source -> canvas), seam weights (callable: host uint8 maps) and canvas size."""
+    step = w - int(round(overlap * w))
+    W, H = w + (n - 1) * step, h
+    f = 1100.0 * w / 1920.0
+    cx, cy = (w - 1) / 2.0, (h - 1) / 2.0
+    K = np.array([[f, 0.0, cx], [0.0, f, cy], [0.0, 0.0, 1.0]])
+    Hs = []
+    for i in range(n):
+        a = math.radians(yaw * (2.0 * i / (n - 1) - 1.0))
+        R = np.array([[math.cos(a), 0.0, math.sin(a)], [0.0, 1.0, 0.0], [-math.sin(a), 0.0, math.cos(a)]])
+        r = math.radians(roll if i % 2 else 0.0)
+        Z = np.array([[math.cos(r), -math.sin(r), 0.0], [math.sin(r), math.cos(r), 0.0], [0.0, 0.0, 1.0]])
+        Hi = _T(i * step - f * math.tan(a), 0.0) @ K @ R @ np.linalg.inv(K) @ _T(cx, cy) @ Z @ _T(-cx, -cy)
+        Hs.append(Hi / Hi[2, 2])
+    seams = [i * step + (w - step) // 2 for i in range(n)]      # camera i's left edge
+
+    def masks():
+        x = np.arange(W)
+        left = np.zeros(W, dtype=np.int64)          # weight already given to cameras before i
+        rows = []
+        for i in range(n):
+            if i == n - 1:
+                upto = np.full(W, 255, dtype=np.int64)
+            elif feather > 1:
+                k = min(feather, max(2, w - step))
+                upto = np.rint(255.0 * np.clip((seams[i + 1] + k / 2.0 - x) / k, 0.0, 1.0)).astype(np.int64)
+            else:
+                upto = np.where(x < seams[i + 1], 255, 0)
+            upto = np.maximum(upto, left)
+            rows.append((upto - left).astype(np.uint8))
+            left = upto
+        return [np.ascontiguousarray(np.broadcast_to(r, (H, W))) for r in rows]
+
+    return Hs, masks, W, H
+
+
+def _texture(gen, W, H):
+    """(3, H, W) float32 in [0, 1]: four octaves of smooth noise and scattered hard blocks, so
+    that there are gradients, corners and flat parts."""
+    out = torch.zeros(1, 3, H, W, device=DEV)
+    for cell, amp in ((96, 0.5), (32, 0.25), (12, 0.15), (5, 0.1)):
+        g = torch.rand(1, 3, H // cell + 3, W // cell + 3, device=DEV, generator=gen)
+        out += amp * torch.nn.functional.interpolate(g, size=(H, W), mode="bilinear", align_corners=True)
+    blocks = torch.rand(1, 1, H // 11 + 2, W // 11 + 2, device=DEV, generator=gen)
+    blocks = torch.nn.functional.interpolate((blocks > 0.93).float(), size=(H, W), mode="nearest")
+    return (out * (1.0 - 0.6 * blocks) + 0.3 * blocks)[0].clamp(0.0, 1.0)
+
+
+def _see(tex, Hm, w, h):
+    """(3, h, w) of the texture under a camera's pixels."""
+    _, TH, TW = tex.shape
+    t = torch.as_tensor(Hm, dtype=torch.float32, device=DEV)
+    y, x = torch.meshgrid(torch.arange(h, device=DEV, dtype=torch.float32),
+                          torch.arange(w, device=DEV, dtype=torch.float32), indexing="ij")
+    z = t[2, 0] * x + t[2, 1] * y + t[2, 2]
+    X = (t[0, 0] * x + t[0, 1] * y + t[0, 2]) / z
+    Y = (t[1, 0] * x + t[1, 1] * y + t[1, 2]) / z
+    grid = torch.stack([2.0 * X / (TW - 1) - 1.0, 2.0 * Y / (TH - 1) - 1.0], dim=-1)[None]
+    return torch.nn.functional.grid_sample(tex[None], grid, mode="bilinear", padding_mode="reflection",
+                                           align_corners=True)[0]
+
+
+def _frames(gen, Hs, w, h, W, H, floats=False):
+    tex = _texture(gen, W, H)
+    out = []
+    for Hm in Hs:
+        f = _see(tex, Hm, w, h)
+        f = (f + 0.05 * (torch.rand(f.shape, device=DEV, generator=gen) - 0.5)).clamp(0.0, 1.0)
+        out.append(f.contiguous() if floats else torch.round(255.0 * f).to(torch.uint8).permute(1, 2, 0).contiguous())
+    return out
+
+
+def _gen(seed):
+    return torch.Generator(device=DEV).manual_seed(int(seed))
+
+
+def _ring_of(case):
+    return _rig(case["n"], case["w"], case["h"], case["overlap"], case["yaw"], case["roll"], case.get("feather", 0))
+
+
+def _batch_rigs(case):
+    """Geometry of the batch's jobs: fixed by the case, as a program's jobs are."""
+    rng = np.random.default_rng(case["geom"])
+    out = []
+    for j in range(case["jobs"]):
+        t = j / max(1, case["jobs"] - 1)
+        w = int(round(case["wmin"] * (case["wmax"] / case["wmin"]) ** t))
+        h = int(round(w * (0.75 if j % 2 else 0.5625)))
+        n = int(rng.integers(2, 5)) if w <= 2000 else 2
+        L = case["levels"] or max(2, int(math.floor(math.log2(min(w, h)))) - 4)
+        out.append((n, w, h, L, float(rng.uniform(0.10, 0.25)), 3.0 * float(rng.uniform(0.2, 1.0))))
+    return out
+
+
+_STREAM = []
+
+
+def _stream():
+    """The one side stream the program runs its batches on."""
+    if not _STREAM:
+        _STREAM.append(torch.cuda.Stream())
+    return _STREAM[0]
+
+
+# ----------------------------------------------------------------------------- prepare
+def prepare(case, seed):
+    gen = _gen(seed)
+    k = case["kind"]
+    if k == "frame":
+        Hs, masks, W, H = _ring_of(case)
+        plan = P.Plan([(case["w"], case["h"])] * case["n"], Hs, masks(), W, H, case["levels"], storage=case["storage"])
+        return dict(kind=k, plan=plan, frames=_frames(gen, Hs, case["w"], case["h"], W, H),
+                    pano=torch.empty((H, W, 3), dtype=torch.uint8, device=DEV))
+    if k == "batch":
+        plans, frames, panos = [], [], []
+        for n, w, h, L, ov, yaw in _batch_rigs(case):
+            Hs, masks, W, H = _rig(n, w, h, ov, yaw, 0.0, case["feather"])
+            plans.append(P.Plan([(w, h)] * n, Hs, masks(), W, H, L, storage=case["storage"]))
+            frames.append(_frames(gen, Hs, w, h, W, H))
+            panos.append(torch.empty((H, W, 3), dtype=torch.uint8, device=DEV))
+        batch = P.Batch(plans)
+        return dict(kind=k, batch=batch, frames=frames, panos=panos, args=batch.args(frames, panos), stream=_stream())
+    if k == "pipe":
+        Hs, masks, W, H = _ring_of(case)
+        plan = P.Plan([(case["w"], case["h"])] * case["n"], Hs, masks(), W, H, case["levels"], storage=case["storage"])
+        sets = []
+        for _ in range(case["sets"]):
+            pinned = []
+            for f in _frames(gen, Hs, case["w"], case["h"], W, H):
+                p = torch.empty(f.shape, dtype=torch.uint8, pin_memory=True)
+                p.copy_(f)
+                pinned.append(p)
+            sets.append(pinned)
+        panos = [torch.empty((H, W, 3), dtype=torch.uint8, pin_memory=True) for _ in range(case["sets"])]
+        return dict(kind=k, pipe=P.Pipe(plan, case["depth"]), sets=sets, panos=panos)
+    if k == "stages":
+        Hs, masks, W, H = _ring_of(case)
+        rois = _stage_rois(case, Hs, W, H)
+        weights = [torch.from_numpy(np.ascontiguousarray(m[y:y + rh, x:x + rw])).to(DEV)
+                   for m, (x, y, rw, rh) in zip(masks(), rois)]
+        return dict(kind=k, Hs=Hs, rois=rois, weights=weights, W=W, H=H, L=case["levels"],
+                    dtype=torch.float16 if case["storage"] == "f16" else torch.float32,
+                    frames=_frames(gen, Hs, case["w"], case["h"], W, H))
+    if k == "lorb":
+        Hs, _, W, H = _ring_of(case)
+        sizes = [(case["w"], case["h"])] * case["n"]
+        areas = P.detection_areas(sizes, Hs, W, H)
+        rng = np.random.default_rng(11)
+        pattern = np.clip(np.rint(rng.normal(0.0, 31.0 / 5.0, size=(case["nd"], 4))), -15, 15).astype(np.int32)
+        return dict(kind=k, set=P.LorbSet(sizes, areas, n_max=case["n_max"], nd=case["nd"], fast_threshold=case["fast"]),
+                    frames=_frames(gen, Hs, case["w"], case["h"], W, H), pattern=torch.from_numpy(pattern).to(DEV))
+    if k == "register":
+        pairs, positions = _features(case, seed)
+        dev = [{q: torch.from_numpy(v).to(DEV) for q, v in p.items()} for p in pairs]
+        caps = [(case["points"], case["points"])] * case["pairs"]
+        m = P.MatcherSet(caps, case["nd"], positions, max_dist=case["nd"] // 4)
+        pr = P.ProsacSet(caps, case["nhyp"])
+        return dict(kind=k, matcher=m, prosac=pr,
+                    match_in=[(p["desc_a"], p["count"], p["desc_b"], p["count"]) for p in dev],
+                    prosac_in=[(p["pts_a"], p["pts_b"], m.match[i], m.dist[i], p["count"], p["uniforms"])
+                               for i, p in enumerate(dev)])
+    if k == "vjp":
+        Hs, masks, W, H = _ring_of(case)
+        plan = P.Plan([(case["w"], case["h"])] * case["n"], Hs, masks(), W, H, case["levels"], bind=False)
+        return dict(kind=k, plan=plan, frames=_frames(gen, Hs, case["w"], case["h"], W, H, floats=True),
+                    d_pano=torch.randn(3, H, W, device=DEV, generator=gen) / (3.0 * W * H))
+    fa, fb, Ha, qs, masks, W, H = _refine_inputs(case, seed)
+    grad = P.Grad([(case["w"], case["h"])] * 2, masks, W, H, case["levels"])
+    return dict(kind="refine", grad=grad, fa=fa, fb=fb, Ha=Ha, qs=qs)
+
+
+def _stage_rois(case, Hs, W, H):
+    """Canvas rectangles that hold every level's support, on multiples of 2^(levels - 1)."""
+    A, margin = 1 << (case["levels"] - 1), 4 << case["levels"]
+    w, h = case["w"], case["h"]
+    out = []
+    for Hm in Hs:
+        c = Hm @ np.array([[-1.0, w, w, -1.0], [-1.0, -1.0, h, h], [1.0, 1.0, 1.0, 1.0]])
+        X, Y = c[0] / c[2], c[1] / c[2]
+        x0 = max(0, int(math.floor((X.min() - margin) / A)) * A)
+        y0 = max(0, int(math.floor((Y.min() - margin) / A)) * A)
+        x1 = min(W, int(math.ceil((X.max() + margin) / A)) * A)
+        y1 = min(H, int(math.ceil((Y.max() + margin) / A)) * A)
+        out.append((x0, y0, x1 - x0, y1 - y0))
+    return out
+
+
+def _features(case, seed):
+    """Descriptors and points of `pairs` area pairs as an extractor leaves them: 60 % of the
+    points of A are seen in B (a few tests flipped, one pixel of noise), a fifth of the rest
+    look like a wrong point of B, the others are unlike any."""
+    n, nd = case["points"], case["nd"]
+    prng = np.random.default_rng(5)
+    positions = np.stack([prng.choice(nd, case["kbits"], replace=False) for _ in range(case["tables"])]).astype(np.int32)
+    pairs = []
+    for p in range(case["pairs"]):
+        rng = np.random.default_rng([int(seed), p])
+        def bits():
+            t = rng.integers(0, 40, (n, nd))
+            return (t < 20).astype(np.uint8), (t > 20).astype(np.uint8)
+        gt_b, lt_b = bits()
+        gt_a, lt_a = bits()
+        perm = rng.permutation(n)
+        seen = rng.random(n) < 0.6
+        like = seen | (rng.random(n) < 0.2)
+        flip = rng.random((n, nd)) < 0.03
+        g, l = gt_b[perm], lt_b[perm]
+        g2, l2 = np.where(flip, l, g), np.where(flip, g, l)
+        gt_a[like], lt_a[like] = g2[like], l2[like]
+        a = np.stack([rng.integers(20, 1900, n), rng.integers(20, 1060, n)], 1)
+        th = math.radians(float(rng.uniform(-3, 3)))
+        Hm = np.array([[math.cos(th), -math.sin(th), rng.uniform(-200, 200)],
+                       [math.sin(th), math.cos(th), rng.uniform(-20, 20)],
+                       [rng.uniform(-1e-5, 1e-5), rng.uniform(-1e-5, 1e-5), 1.0]])
+        v = Hm @ np.vstack([a.T, np.ones(n)])
+        to = np.rint((v[:2] / v[2]).T + rng.uniform(-1.0, 1.0, (n, 2))).astype(np.int64)
+        b = np.stack([rng.integers(20, 1900, n), rng.integers(20, 1060, n)], 1)
+        b[perm[seen]] = to[seen]
+
+        def pack(gt, lt):
+            both = np.concatenate([gt, lt], 1).reshape(n, 2 * nd // 32, 32)
+            w = np.packbits(both, axis=2, bitorder="little")
+            return np.ascontiguousarray(w).view(np.int32).reshape(n, 2 * nd // 32)
+
+        pairs.append(dict(desc_a=pack(gt_a, lt_a), desc_b=pack(gt_b, lt_b), count=np.array([n], np.int32),
+                          pts_a=a.astype(np.int32), pts_b=b.astype(np.int32), uniforms=rng.random((case["nhyp"], 4))))
+    return pairs, positions
+
+
+def _refine_inputs(case, seed):
+    w, h = case["w"], case["h"]
+    Hs, masks, W, H = _rig(2, w, h, case["overlap"], case["yaw"], 0.0)
+    Hs = [_T(0.0, 0.0), np.linalg.inv(Hs[0]) @ Hs[1]]
+    Hs[1] = Hs[1] / Hs[1][2, 2]
+    gen = _gen(seed)
+    fa, fb = _frames(gen, Hs, w, h, W, H, floats=True)
+    c = Hs[1] @ np.array([[0.0, w - 1.0, w - 1.0, 0.0], [0.0, 0.0, h - 1.0, h - 1.0], [1.0, 1.0, 1.0, 1.0]])
+    q = (c[:2] / c[2]).T.reshape(8)
+    rng = np.random.default_rng(int(seed))
+    q0 = q + rng.uniform(-3.0, 3.0, 8)
+    qs = [q0 + (q - q0) * 0.2 * s for s in range(case["steps"])]
+    return fa, fb, Hs[0], qs, masks(), W, H
+
+
+# ----------------------------------------------------------------------------- run
+def run(state):
+    k = state["kind"]
+    if k == "frame":
+        return state["plan"].frame(state["frames"], state["pano"])
+    if k == "batch":
+        s = state["stream"]
+        state["batch"].run(state["frames"], state["panos"], stream=s, args=state["args"])
+        return state["panos"]
+    if k == "pipe":
+        state["pipe"].run(state["sets"], state["panos"])
+        return state["panos"]
+    if k == "stages":
+        L, W, H = state["L"], state["W"], state["H"]
+        laps, gms, orig = [], [], []
+        for f, Hm, m, (x, y, w, h) in zip(state["frames"], state["Hs"], state["weights"], state["rois"]):
+            g0 = P.warp(f, Hm, x, y, w, h, dtype=state["dtype"])
+            laps.append(P.pyramid(g0, L, "laplacian", canvas=(W, H), origin=(x, y)))
+            gms.append(P.pyramid(m, L, "gaussian", canvas=(W, H), origin=(x, y), dtype=state["dtype"]))
+            orig.append([(x >> j, y >> j) for j in range(L)])
+        pano, rs = P.blend(laps, gms, W, H, band_origins=orig, weight_origins=orig)
+        return [pano, rs, laps, gms]
+    if k == "lorb":
+        s = state["set"]
+        s.run_raw(state["frames"], state["pattern"], torch.cuda.current_stream().cuda_stream)
+        return [s.counts, s.points, s.responses, s.descriptors]
+    if k == "register":
+        stream = torch.cuda.current_stream().cuda_stream
+        m, p = state["matcher"], state["prosac"]
+        m.run_raw(state["match_in"], stream)
+        p.run_raw(state["prosac_in"], stream)
+        return [m.match, m.dist, p.inliers, p.mask, p.hyp_counts, p.H]
+    if k == "vjp":
+        r0 = state["plan"].forward_f32(state["frames"])
+        d_frames, d_maps = state["plan"].backward(state["frames"], state["d_pano"])
+        return [r0, d_frames, d_maps]
+    out = []
+    w, h = state["grad"].frame_sizes[1]
+    for q in state["qs"]:
+        fa = state["fa"].detach().requires_grad_(True)
+        fb = state["fb"].detach().requires_grad_(True)
+        qt = torch.tensor(q, dtype=torch.float64, requires_grad=True)
+        state["grad"].freeze([state["Ha"], P.corners_to_h(q, w, h)])
+        loss = P.StitchPairLoss.apply(fa, fb, qt, state["grad"], state["Ha"])
+        loss.backward()
+        out.append([loss, fa.grad, fb.grad, qt.grad])
+    return out
+
+
+# ----------------------------------------------------------------------------- work
+def work(case) -> dict:
+    """Inputs read once, outputs written once; operations of the warp (about 20 a sample and
+    channel), the pyramids (4/3 of 10 for REDUCE and 10 for EXPAND) and the blend."""
+    k = case["kind"]
+
+    def ring(n, w, h, ov):
+        return n * w * h, (w + (n - 1) * (w - int(round(ov * w)))) * h
+
+    if k in ("frame", "pipe", "stages"):
+        fpx, cpx = ring(case["n"], case["w"], case["h"], case["overlap"])
+        es = 2 if case.get("storage") == "f16" else 4
+        b, f = 3 * fpx + 3 * cpx, 3 * 50 * fpx + 3 * 20 * cpx
+        if k == "pipe":
+            return dict(bytes=case["sets"] * b, flops=case["sets"] * f)
+        if k == "stages":   # the stages return their pyramids: every level of bands, weights and R
+            b += int((4.0 / 3.0) * es * (4 * fpx + 3 * cpx)) + fpx
+        return dict(bytes=b, flops=f)
+    if k == "batch":
+        b = f = 0
+        for n, w, h, _, ov, _ in _batch_rigs(case):
+            fpx, cpx = ring(n, w, h, ov)
+            b += 3 * fpx + 3 * cpx
+            f += 3 * 50 * fpx + 3 * 20 * cpx
+        return dict(bytes=b, flops=f)
+    if k == "lorb":
+        px = 2 * (case["n"] - 1) * case["h"] * int(case["w"] * case["overlap"] + 48)
+        kept = 2 * (case["n"] - 1) * case["n_max"]
+        return dict(bytes=3 * px + kept * (16 + case["nd"] // 4), flops=120 * px + kept * 35 * 35 * 20)
+    if k == "register":
+        n, p = case["points"], case["pairs"]
+        return dict(bytes=p * (n * (case["nd"] // 2 + 16 + 17) + case["nhyp"] * 36),
+                    flops=p * (n * n * 2 * case["tables"] + case["nhyp"] * (700 + n * 25)))
+    fpx, cpx = ring(case.get("n", 2), case["w"], case["h"], case["overlap"])
+    one = dict(bytes=2 * 12 * fpx + 12 * fpx + 2 * 12 * cpx, flops=3 * 150 * fpx + 3 * 60 * cpx)
+    if k == "vjp":
+        return one
+    return {q: case["steps"] * v for q, v in one.items()}
+
+
+# ----------------------------------------------------------------------------- the same in 64 bits
+def _map32(Hm):
+    a = np.asarray(Hm, dtype=np.float64).reshape(9)
+    adj = np.array([a[4] * a[8] - a[5] * a[7], a[2] * a[7] - a[1] * a[8], a[1] * a[5] - a[2] * a[4],
+                    a[5] * a[6] - a[3] * a[8], a[0] * a[8] - a[2] * a[6], a[2] * a[3] - a[0] * a[5],
+                    a[3] * a[7] - a[4] * a[6], a[1] * a[6] - a[0] * a[7], a[0] * a[4] - a[1] * a[3]])
+    return (adj / adj[8]).astype(np.float32)
+
+
+def _fold(i, n):
+    i = i.abs()
+    return torch.where(i > n - 1, 2 * (n - 1) - i, i)
+
+
+_W5 = (1.0 / 16, 4.0 / 16, 6.0 / 16, 4.0 / 16, 1.0 / 16)
+
+
+def _reduce(g):
+    for d in (1, 2):
+        n = g.shape[d]
+        base = torch.arange((n + 1) // 2, device=g.device) * 2
+        g = sum(wt * g.index_select(d, _fold(base + a - 2, n)) for a, wt in enumerate(_W5))
+    return g
+
+
+def _expand(c, h, w):
+    z = torch.zeros(c.shape[0], h, c.shape[2], dtype=c.dtype, device=c.device)
+    z = z.index_add(1, torch.arange(0, h, 2, device=c.device), c)
+    u = torch.zeros(c.shape[0], h, w, dtype=c.dtype, device=c.device)
+    u = u.index_add(2, torch.arange(0, w, 2, device=c.device), z)
+    for d in (1, 2):
+        n = u.shape[d]
+        base = torch.arange(n, device=c.device)
+        u = 2.0 * sum(wt * u.index_select(d, _fold(base + a - 2, n)) for a, wt in enumerate(_W5))
+    return u
+
+
+def _gauss(g, L):
+    out = [g]
+    for _ in range(L - 1):
+        out.append(_reduce(out[-1]))
+    return out
+
+
+def _laplace(g, L):
+    gs = _gauss(g, L)
+    return [gs[k] - _expand(gs[k + 1], gs[k].shape[1], gs[k].shape[2]) for k in range(L - 1)] + [gs[-1]]
+
+
+def _collapse(laps, gms):
+    L = len(laps[0])
+    r, out = None, [None] * L
+    for k in range(L - 1, -1, -1):
+        b = sum(l[k] * g[k] for l, g in zip(laps, gms))
+        r = b if r is None else b + _expand(r, b.shape[1], b.shape[2])
+        out[k] = r
+    return out
+
+
+def _coords(m32, W, H):
+    """Source coordinates of the canvas, each operation rounded to FP32, and z > 0."""
+    m = torch.as_tensor(m32, device=DEV)
+    X = torch.arange(W, device=DEV, dtype=torch.float32)[None, :]
+    Y = torch.arange(H, device=DEV, dtype=torch.float32)[:, None]
+    u, v, z = [((m[3 * i] * X) + (m[3 * i + 1] * Y)) + m[3 * i + 2] for i in range(3)]
+    div = lambda a: (a.double() / z.double()).float()   # noqa: E731  (the rounding of an IEEE divide)
+    return div(u), div(v), z > 0
+
+
+def _bilinear(f, x, y, ok, dx=0.0, dy=0.0):
+    """(3, H, W) float64 of frame f (3, h, w); cells from the FP32 coordinates x, y; dx, dy
+    carry the coordinates' derivative (their value is 0)."""
+    h, w = f.shape[1:]
+    big = ok & (x.abs() < 1e7) & (y.abs() < 1e7)
+    xs, ys = torch.where(big, x, torch.full_like(x, -9.0)), torch.where(big, y, torch.full_like(y, -9.0))
+    x0, y0 = xs.floor(), ys.floor()
+    fx, fy = (xs - x0).double() + dx, (ys - y0).double() + dy
+    x0, y0 = x0.long(), y0.long()
+    out = 0.0
+    flat = f.reshape(3, -1)
+    for j in (0, 1):
+        for i in (0, 1):
+            xi, yi = x0 + i, y0 + j
+            inside = big & (xi >= 0) & (xi < w) & (yi >= 0) & (yi < h)
+            at = torch.where(inside, yi * w + xi, torch.zeros_like(xi))
+            tap = flat.index_select(1, at.reshape(-1)).reshape(3, *x.shape)
+            wt = (fx if i else 1.0 - fx) * (fy if j else 1.0 - fy)
+            out = out + torch.where(inside, wt, torch.zeros_like(wt)) * tap
+    return out
+
+
+def _moving(M, m32, x, y, ok, W, H):
+    """Zero-valued tensors whose gradients with respect to M are the coordinates'."""
+    X = torch.arange(W, device=DEV, dtype=torch.float64)[None, :]
+    Y = torch.arange(H, device=DEV, dtype=torch.float64)[:, None]
+    u, v, z = [M[3 * i] * X + M[3 * i + 1] * Y + M[3 * i + 2] for i in range(3)]
+    zs = torch.where(ok, z, torch.ones_like(z))
+    xd, yd = u / zs, v / zs
+    return xd - xd.detach(), yd - yd.detach()
+
+
+def exact(case, seed):
+    k = case["kind"]
+    if k == "stages":
+        return _exact_stages(case, seed)
+    if k == "register":
+        return _exact_register(case, seed)
+    if k == "vjp":
+        return _exact_vjp(case, seed)
+    if k == "refine":
+        return _exact_refine(case, seed)
+    return None                                   # whole numbers and bytes only
+
+
+def _exact_stages(case, seed):
+    Hs, masks, W, H = _ring_of(case)
+    rois = _stage_rois(case, Hs, W, H)
+    frames = _frames(_gen(seed), Hs, case["w"], case["h"], W, H)
+    L = case["levels"]
+    laps, gms, lap_out, gm_out = [], [], [], []
+    for f, Hm, m, (x, y, w, h) in zip(frames, Hs, masks(), rois):
+        g0 = _bilinear(f.permute(2, 0, 1).double() / 255.0, *_coords(_map32(Hm), W, H))
+        lap = _laplace(g0, L)
+        gm = _gauss(torch.from_numpy(m).to(DEV)[None].double() / 255.0, L)
+        laps.append(lap)
+        gms.append(gm)
+
+        def crop(levels):
+            out = []
+            for j, t in enumerate(levels):
+                x1, y1 = min(-(-(x + w) // (1 << j)), t.shape[2]), min(-(-(y + h) // (1 << j)), t.shape[1])
+                out.append(t[:, y >> j:y1, x >> j:x1].contiguous())
+            return out
+
+        lap_out.append(crop(lap))
+        gm_out.append(crop(gm))
+    return [None, _collapse(laps, gms), lap_out, gm_out]
+
+
+def _exact_vjp(case, seed):
+    Hs, masks, W, H = _ring_of(case)
+    gen = _gen(seed)
+    frames = [f.double().requires_grad_(True) for f in _frames(gen, Hs, case["w"], case["h"], W, H, floats=True)]
+    d_pano = torch.randn(3, H, W, device=DEV, generator=gen) / (3.0 * W * H)
+    L = case["levels"]
+    laps, gms, maps = [], [], []
+    for f, Hm, m in zip(frames, Hs, masks()):
+        m32 = _map32(Hm)
+        M = torch.tensor(m32.astype(np.float64), device=DEV, requires_grad=True)
+        x, y, ok = _coords(m32, W, H)
+        dx, dy = _moving(M, m32, x, y, ok, W, H)
+        laps.append(_laplace(_bilinear(f, x, y, ok, dx, dy), L))
+        gms.append(_gauss(torch.from_numpy(m).to(DEV)[None].double() / 255.0, L))
+        maps.append(M)
+    r0 = _collapse(laps, gms)[0]
+    g = torch.autograd.grad((r0 * d_pano.double()).sum(), frames + maps)
+    n = case["n"]
+    return [r0.detach(), list(g[:n]), torch.stack(g[n:]).reshape(n, 3, 3).cpu().numpy()]
+
+
+def _exact_refine(case, seed):
+    fa, fb, Ha, qs, masks, W, H = _refine_inputs(case, seed)
+    w, h, L = case["w"], case["h"], case["levels"]
+    gms = [_gauss(torch.from_numpy(m).to(DEV)[None].double() / 255.0, L) for m in masks]
+    cx, cy = [0.0, w - 1.0, w - 1.0, 0.0], [0.0, 0.0, h - 1.0, h - 1.0]
+    out = []
+    for q in qs:
+        A = fa.double().requires_grad_(True)
+        B = fb.double().requires_grad_(True)
+        qt = torch.tensor(q, dtype=torch.float64, requires_grad=True)
+        rows, rhs = [], []
+        one, zero = torch.ones((), dtype=torch.float64), torch.zeros((), dtype=torch.float64)
+        for c in range(4):
+            X, Y = qt[2 * c], qt[2 * c + 1]
+            rows.append(torch.stack([cx[c] * one, cy[c] * one, one, zero, zero, zero, -X * cx[c], -X * cy[c]]))
+            rows.append(torch.stack([zero, zero, zero, cx[c] * one, cy[c] * one, one, -Y * cx[c], -Y * cy[c]]))
+            rhs += [X, Y]
+        hv = torch.linalg.solve(torch.stack(rows), torch.stack(rhs))
+        Hb = torch.cat([hv, one[None]]).reshape(3, 3)
+        N = torch.linalg.inv(Hb)
+        Mq = (N / N[2, 2]).reshape(9)
+        frames, laps, warped, inside = [A, B], [], [], []
+        for f, Hm, live in zip(frames, [Ha, Hb.detach().numpy()], [False, True]):
+            m32 = _map32(Hm)
+            x, y, ok = _coords(m32, W, H)
+            dx = dy = 0.0
+            if live:
+                M = torch.tensor(m32.astype(np.float64), device=DEV) + (Mq - Mq.detach()).to(DEV)
+                dx, dy = _moving(M, m32, x, y, ok, W, H)
+            g0 = _bilinear(f, x, y, ok, dx, dy)
+            x0, y0 = x.floor(), y.floor()
+            inside.append(ok & (x0 >= 0) & (x0 + 1 <= w - 1) & (y0 >= 0) & (y0 + 1 <= h - 1))
+            warped.append(g0)
+            laps.append(_laplace(g0, L))
+        p = _collapse(laps, gms)[0]
+        om = (inside[0] & inside[1]).double()
+        loss = (om * ((p - warped[0]) ** 2 + (p - warped[1]) ** 2)).sum() / (6.0 * om.sum())
+        ga, gb, gq = torch.autograd.grad(loss, [A, B, qt])
+        out.append([loss.detach().cpu(), ga, gb, gq])
+    return out
+
+
+def _exact_register(case, seed):
+    pairs, positions = _features(case, seed)
+    Hs = [_prosac64(*_match64(p, positions, case), p, case["nhyp"]) for p in pairs]
+    return [None, None, None, None, None, torch.from_numpy(np.stack(Hs))]
+
+
+def _match64(p, positions, case):
+    """Nearest candidate (some table's keys within one bit) by (distance, index)."""
+    n, nd = case["points"], case["nd"]
+
+    def bits(d):
+        return np.unpackbits(np.ascontiguousarray(d).view(np.uint8).reshape(n, -1), axis=1, bitorder="little")
+
+    a, b = bits(p["desc_a"]), bits(p["desc_b"])
+    cand = np.zeros((n, n), dtype=bool)
+    for pos in positions:
+        ka, kb = a[:, pos].astype(np.float32), b[:, pos].astype(np.float32)
+        cand |= ka.sum(1)[:, None] + kb.sum(1)[None] - 2.0 * (ka @ kb.T) <= 1.5
+    af, bf = a.astype(np.float32), b.astype(np.float32)
+    d = np.rint(af.sum(1)[:, None] + bf.sum(1)[None] - 2.0 * (af @ bf.T)).astype(np.int64)
+    d = np.where(cand, d, 10 ** 6)
+    j = d.argmin(1)
+    best = d[np.arange(n), j]
+    ok = best <= nd // 4
+    return np.where(ok, j, -1), np.where(ok, best, -1)
+
+
+def _prosac64(match, dist, p, nhyp, T_N=200000.0, eps=3.0):
+    idx = np.nonzero(match >= 0)[0]
+    order = idx[np.argsort(dist[idx], kind="stable")]
+    a, b = p["pts_a"][order].astype(np.float64), p["pts_b"][match[order]].astype(np.float64)
+    M = len(order)
+    if M < 4:
+        return np.zeros(9)
+    T = T_N
+    for i in range(4):
+        T = T * float(4 - i) / float(M - i)
+    tp = [0] * (M + 1)
+    tp[4] = 1
+    for n in range(4, M):
+        Tn = T * float(n + 1) / float(n + 1 - 4)
+        tp[n + 1] = tp[n] + int(math.ceil(Tn - T))
+        T = Tn
+    tp = np.array(tp)
+    samples = np.empty((nhyp, 4), dtype=np.int64)
+    for t in range(nhyp):
+        n = 4 + int(np.searchsorted(tp[4:M], t + 1, side="right"))
+        nth = not tp[n] < t + 1
+        R, draws = (n - 1, 3) if nth else (n, 4)
+        got = []
+        for c in range(draws):
+            r = min(int(math.floor(p["uniforms"][t, c] * (R - c))), R - c - 1)
+            for s in sorted(got):
+                if s <= r:
+                    r += 1
+            got.append(r)
+        samples[t] = got + [n - 1] if nth else got
+
+    def system(x, y, u, v):
+        one, zero = np.ones_like(x), np.zeros_like(x)
+        r0 = np.stack([x, y, one, zero, zero, zero, -u * x, -u * y], -1)
+        r1 = np.stack([zero, zero, zero, x, y, one, -v * x, -v * y], -1)
+        return np.concatenate([r0, r1], -2), np.concatenate([u, v], -1)
+
+    pa, pb = a[samples], b[samples]
+    bad = np.zeros(nhyp, dtype=bool)
+    for i, j, l in ((0, 1, 2), (0, 1, 3), (0, 2, 3), (1, 2, 3)):
+        for q in (pa, pb):
+            e, f = q[:, j] - q[:, i], q[:, l] - q[:, i]
+            bad |= e[:, 0] * f[:, 1] - e[:, 1] * f[:, 0] == 0
+    A, r = system(pa[..., 0], pa[..., 1], pb[..., 0], pb[..., 1])
+    A[bad] = np.eye(8)
+    h = np.concatenate([np.linalg.solve(A, r[..., None])[..., 0], np.ones((nhyp, 1))], 1)
+    ones = np.concatenate([a, np.ones((M, 1))], 1)
+    inl = np.zeros((nhyp, M), dtype=bool)
+    for t in range(nhyp):
+        v = h[t].reshape(3, 3) @ ones.T
+        with np.errstate(divide="ignore", invalid="ignore"):
+            e = (v[0] / v[2] - b[:, 0]) ** 2 + (v[1] / v[2] - b[:, 1]) ** 2
+            inl[t] = (v[2] > 0) & (e <= eps * eps)
+    count = np.where(bad, -1, inl.sum(1))
+    t = int(count.argmax())
+    if count[t] < 0:
+        return np.zeros(9)
+    if count[t] < 5:
+        return h[t] / h[t, 8]
+    ia, ib = a[inl[t]], b[inl[t]]
+    ca, cb = ia.mean(0), ib.mean(0)
+    sa = math.sqrt(2.0) / np.hypot(*(ia - ca).T).mean()
+    sb = math.sqrt(2.0) / np.hypot(*(ib - cb).T).mean()
+    na, nb = sa * (ia - ca), sb * (ib - cb)
+    A, r = system(na[:, 0], na[:, 1], nb[:, 0], nb[:, 1])
+    hn = np.append(np.linalg.lstsq(A, r, rcond=None)[0], 1.0).reshape(3, 3)
+    Ta = np.array([[sa, 0, -sa * ca[0]], [0, sa, -sa * ca[1]], [0, 0, 1]])
+    Tb = np.array([[1 / sb, 0, cb[0]], [0, 1 / sb, cb[1]], [0, 0, 1]])
+    Hm = Tb @ hn @ Ta
+    return (Hm / Hm[2, 2]).reshape(9)
