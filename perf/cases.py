@@ -167,7 +167,7 @@ def _texture(gen, W, H):
         out += amp * torch.nn.functional.interpolate(g, size=(H, W), mode="bilinear", align_corners=True)
     blocks = torch.rand(1, 1, H // 11 + 2, W // 11 + 2, device=DEV, generator=gen)
     blocks = torch.nn.functional.interpolate((blocks > 0.93).float(), size=(H, W), mode="nearest")
-    return (out * (1.0 - 0.6 * blocks) + 0.3 * blocks)[0].clamp(0.0, 1.0)
+    return (out * (1.0 - 0.8 * blocks))[0].clamp(0.0, 1.0)
 
 
 def _see(tex, Hm, w, h):
