@@ -213,8 +213,10 @@ struct CamPlan {
   Rect lwin[kMaxLevels];
   std::vector<uint8_t> mask0;     // seam weights on roi[0], rows of mask_row bytes
   // the seam weights on their own support box (for the float-frame forward and its
-  // vector-Jacobian product, which define every array on the whole canvas)
-  std::vector<uint8_t> wsup;
+  // vector-Jacobian product): one uint32 row number per row of the box, then the rows, a row
+  // equal to the one above it stored once (every row of a vertical cut is the same, so a call
+  // uploads kilobytes instead of the box)
+  std::vector<uint8_t> wdict;
   int wsx = 0, wsy = 0, wsw = 0, wsh = 0;
   int64_t mask_row = 0;
   size_t off_mask0 = 0;
@@ -258,7 +260,13 @@ void stitch::plan_camera(const stitch_plan* p, int i, PlanCamera* out) {
   out->fh = c.fh;
   for (int j = 0; j < 9; ++j) out->hinv[j] = c.hinv[j];
   out->wx = c.wsx; out->wy = c.wsy; out->ww = c.wsw; out->wh = c.wsh;
-  out->weights = c.wsup.empty() ? nullptr : c.wsup.data();
+  out->wdict = c.wdict.empty() ? nullptr : c.wdict.data();
+  out->wdict_bytes = c.wdict.size();
+  for (int k = 0; k < p->L; ++k) {
+    const Rect r = c.roi[k], b = c.band[k];
+    out->roi[k][0] = r.x; out->roi[k][1] = r.y; out->roi[k][2] = r.w; out->roi[k][3] = r.h;
+    out->band[k][0] = b.x; out->band[k][1] = b.y; out->band[k][2] = b.w; out->band[k][3] = b.h;
+  }
 }
 
 void stitch::plan_geometry(const stitch_plan* p, int* n, int* frame_w, int* frame_h, int* canvas_w, int* canvas_h,
@@ -882,9 +890,17 @@ stitch_status stitch_plan_create(int32_t n, const int32_t* frame_w, const int32_
     }
     if (mx1 >= mx0) {
       c.wsx = (int)mx0; c.wsy = (int)my0; c.wsw = (int)(mx1 - mx0 + 1); c.wsh = (int)(my1 - my0 + 1);
-      c.wsup.resize((size_t)c.wsw * c.wsh);
-      for (int y = 0; y < c.wsh; ++y)
-        std::memcpy(&c.wsup[(size_t)y * c.wsw], m + (size_t)(c.wsy + y) * canvas_w + c.wsx, c.wsw);
+      c.wdict.resize((size_t)4 * c.wsh);
+      uint32_t rows = 0;
+      for (int y = 0; y < c.wsh; ++y) {
+        const uint8_t* row = m + (size_t)(c.wsy + y) * canvas_w + c.wsx;
+        if (y == 0 || std::memcmp(row, row - canvas_w, c.wsw) != 0) {
+          c.wdict.insert(c.wdict.end(), row, row + c.wsw);
+          ++rows;
+        }
+        const uint32_t id = rows - 1;
+        std::memcpy(&c.wdict[(size_t)4 * y], &id, sizeof id);
+      }
     }
     Interval nx{mx0, mx1}, ny{my0, my1};
     for (int k = 0; k < L; ++k) {

@@ -117,13 +117,16 @@ void plan_geometry(const stitch_plan* p, int* n, int* frame_w, int* frame_h, int
                    bool* bound);
 
 // One camera of a plan for the float-frame forward and its vector-Jacobian product: frame
-// size, the FP32 canvas -> source map and the seam weights on their support box (weights
-// holds ww x wh bytes row-major, or is NULL when the camera has no weight anywhere).
+// size, the FP32 canvas -> source map, the seam weights on their support box (wdict: wh
+// uint32 row numbers, then rows of ww bytes; empty when the camera has no weight anywhere),
+// and per level the region its pyramid needs and the band the blend reads ({x, y, w, h}).
 struct PlanCamera {
   int fw, fh;
   float hinv[9];
   int wx, wy, ww, wh;
-  const uint8_t* weights;
+  const uint8_t* wdict;
+  size_t wdict_bytes;
+  int roi[kMaxLevels][4], band[kMaxLevels][4];
 };
 int plan_levels(const stitch_plan* p);
 void plan_camera(const stitch_plan* p, int i, PlanCamera* out);
