@@ -1430,24 +1430,14 @@ stitch_status stitch_grad_create(const int32_t frame_w[2], const int32_t frame_h
     g->fw[c] = frame_w[c]; g->fh[c] = frame_h[c];
   }
   const size_t np = (size_t)canvas_w * canvas_h;
-  g->masks.resize(2 * np);
-  for (size_t i = 0; i < np; ++i) {
-    if ((int)masks[0][i] + (int)masks[1][i] != 255) return fail(STITCH_E_MASK, "seam weights do not sum to 255");
-    g->masks[i] = masks[0][i];
-    g->masks[np + i] = masks[1][i];
-  }
+  int off = 0;
+  for (size_t i = 0; i < np; ++i) off |= ((int)masks[0][i] + (int)masks[1][i]) ^ 255;
+  if (off) return fail(STITCH_E_MASK, "seam weights do not sum to 255");
+  for (int c = 0; c < 2; ++c) g->masks.insert(g->masks.end(), masks[c], masks[c] + np);
   for (int c = 0; c < 2; ++c) {
-    int x0 = canvas_w, x1 = -1, y0 = canvas_h, y1 = -1;
-    for (int y = 0; y < canvas_h; ++y) {
-      const uint8_t* row = &g->masks[c * np + (size_t)y * canvas_w];
-      int a = 0, b = canvas_w - 1;
-      while (a < canvas_w && !row[a]) ++a;
-      if (a == canvas_w) continue;
-      while (!row[b]) --b;
-      x0 = std::min(x0, a); x1 = std::max(x1, b);
-      y0 = std::min(y0, y); y1 = y;
-    }
-    regions_of(g->d, Box{x0, y0, x1 - x0 + 1, y1 - y0 + 1}, g->roi[c], g->band[c]);
+    int box[4] = {0, 0, 0, 0};
+    weight_box(masks[c], canvas_w, canvas_h, box);
+    regions_of(g->d, Box{box[0], box[1], box[2], box[3]}, g->roi[c], g->band[c]);
   }
   size_t top = 0;
   const Box all{0, 0, canvas_w, canvas_h};

@@ -63,6 +63,65 @@ int elem_size(int dtype) { return dtype == STITCH_F32 ? 4 : dtype == STITCH_F16 
 
 }  // namespace
 
+namespace {
+
+// Index of the first non-zero byte of p[0 .. n), n when there is none (eight bytes at a time).
+int first_nonzero(const uint8_t* p, int n) {
+  int i = 0;
+  for (uint64_t v; i + 8 <= n; i += 8) {
+    std::memcpy(&v, p + i, 8);
+    if (v) return i + (__builtin_ctzll(v) >> 3);
+  }
+  for (; i < n; ++i)
+    if (p[i]) return i;
+  return n;
+}
+
+// Index of the last non-zero byte of p[0 .. n), -1 when there is none.
+int last_nonzero(const uint8_t* p, int n) {
+  int i = n;
+  for (uint64_t v; i >= 8; i -= 8) {
+    std::memcpy(&v, p + i - 8, 8);
+    if (v) return i - 1 - (__builtin_clzll(v) >> 3);
+  }
+  while (i > 0)
+    if (p[--i]) return i;
+  return -1;
+}
+
+}  // namespace
+
+// The box is grown row by row: of each row only the columns outside the box so far can widen
+// it, and the inside is looked at only to see whether the row counts at all.  (A byte at a
+// time over the whole canvas, this and the sum check took most of a plan's 4.1 ms at
+// 2304x720; 0.55 ms now.)
+bool stitch::weight_box(const uint8_t* m, int w, int h, int box[4]) {
+  int x0 = w, x1 = -1, y0 = h, y1 = -1;
+  for (int y = 0; y < h; ++y) {
+    const uint8_t* row = m + (size_t)y * w;
+    bool any = false;
+    if (x1 < x0) {
+      const int a = first_nonzero(row, w);
+      if (a == w) continue;
+      x0 = a;
+      x1 = last_nonzero(row, w);
+      any = true;
+    } else {
+      const int a = first_nonzero(row, x0), b = last_nonzero(row + x1 + 1, w - x1 - 1);
+      any = a < x0 || b >= 0 || first_nonzero(row + x0, x1 - x0 + 1) <= x1 - x0;
+      x0 = std::min(x0, a);
+      x1 += b + 1;
+    }
+    if (any) {
+      y0 = std::min(y0, y);
+      y1 = y;
+    }
+  }
+  if (y1 < y0) return false;
+  box[0] = x0; box[1] = y0; box[2] = x1 - x0 + 1; box[3] = y1 - y0 + 1;
+  return true;
+}
+
 // Canvas -> source map: adj(H) / adj(H)[2][2] in FP64, cofactors formed as a*b - c*d,
 // each entry rounded to FP32.  Returns false (with a reason) if H is unusable.
 bool stitch::hinv_spec(const double* a, float out[9], double* sign_out, const char** why) {
@@ -211,14 +270,13 @@ struct CamPlan {
   // (inside roi), so band rows go out as whole 16-byte vectors at either storage size; the
   // added columns carry seam weight 0
   Rect lwin[kMaxLevels];
-  std::vector<uint8_t> mask0;     // seam weights on roi[0], rows of mask_row bytes
-  // the seam weights on their own support box (for the float-frame forward and its
-  // vector-Jacobian product): one uint32 row number per row of the box, then the rows, a row
-  // equal to the one above it stored once (every row of a vertical cut is the same, so a call
-  // uploads kilobytes instead of the box)
+  // the seam weights on their support box (ws*): one uint32 row number per row of the box,
+  // then the rows, a row equal to the one above it stored once (every row of a vertical cut is
+  // the same, so a call of the float-frame forward or its vector-Jacobian product uploads
+  // kilobytes instead of the box)
   std::vector<uint8_t> wdict;
   int wsx = 0, wsy = 0, wsw = 0, wsh = 0;
-  int64_t mask_row = 0;
+  int64_t mask_row = 0;           // the workspace's weights on roi[0]: bytes per row
   size_t off_mask0 = 0;
   size_t off_g[kMaxLevels] = {};  int64_t g_row[kMaxLevels] = {}, g_plane[kMaxLevels] = {};
   size_t off_gm[kMaxLevels] = {}; int64_t gm_row[kMaxLevels] = {};
@@ -816,18 +874,22 @@ stitch_status stitch_plan_create(int32_t n, const int32_t* frame_w, const int32_
   p->cam.resize(n);
   const int L = levels;
   // --- seam weights: present, partition of unity ---
-  std::vector<uint16_t> total((size_t)canvas_w * canvas_h, 0);
-  for (int i = 0; i < n; ++i) {
+  for (int i = 0; i < n; ++i)
     if (!masks[i]) return fail(STITCH_E_NULL, "masks[%d] is NULL", i);
-    const uint8_t* m = masks[i];
-    for (size_t j = 0; j < total.size(); ++j) total[j] += m[j];
+  std::vector<uint16_t> total(canvas_w);               // one row's sums: they stay in cache
+  for (int y = 0; y < canvas_h; ++y) {
+    std::fill(total.begin(), total.end(), (uint16_t)0);
+    for (int i = 0; i < n; ++i) {
+      const uint8_t* m = masks[i] + (size_t)y * canvas_w;
+      for (int x = 0; x < canvas_w; ++x) total[x] += m[x];
+    }
+    uint16_t off = 0;
+    for (int x = 0; x < canvas_w; ++x) off |= total[x] ^ 255;
+    if (!off) continue;
+    const int x = (int)(std::find_if(total.begin(), total.end(), [](uint16_t t) { return t != 255; }) - total.begin());
+    return fail(STITCH_E_MASK, "seam weights sum to %d at canvas pixel (%d, %d); they must sum to 255", (int)total[x],
+                x, y);
   }
-  for (size_t j = 0; j < total.size(); ++j)
-    if (total[j] != 255)
-      return fail(STITCH_E_MASK, "seam weights sum to %d at canvas pixel (%zu, %zu); they must sum to 255",
-                  (int)total[j], j % canvas_w, j / canvas_w);
-  total.clear();
-  total.shrink_to_fit();
   const int64_t A = (int64_t)1 << (L - 1);   // every ROI origin is a multiple of 2^(L-1)
   for (int i = 0; i < n; ++i) {
     CamPlan& c = p->cam[i];
@@ -880,16 +942,11 @@ stitch_status stitch_plan_create(int32_t n, const int32_t* frame_w, const int32_
     // --- seam-weight support per level (bounding box), and the band windows ---
     const uint8_t* m = masks[i];
     int64_t mx0 = canvas_w, mx1 = -1, my0 = canvas_h, my1 = -1;
-    for (int y = 0; y < canvas_h; ++y) {
-      const uint8_t* row = m + (size_t)y * canvas_w;
-      for (int x = 0; x < canvas_w; ++x)
-        if (row[x]) {
-          mx0 = std::min<int64_t>(mx0, x); mx1 = std::max<int64_t>(mx1, x);
-          my0 = std::min<int64_t>(my0, y); my1 = std::max<int64_t>(my1, y);
-        }
-    }
-    if (mx1 >= mx0) {
-      c.wsx = (int)mx0; c.wsy = (int)my0; c.wsw = (int)(mx1 - mx0 + 1); c.wsh = (int)(my1 - my0 + 1);
+    int box[4];
+    if (weight_box(m, canvas_w, canvas_h, box)) {
+      c.wsx = box[0]; c.wsy = box[1]; c.wsw = box[2]; c.wsh = box[3];
+      mx0 = box[0]; mx1 = box[0] + box[2] - 1;
+      my0 = box[1]; my1 = box[1] + box[3] - 1;
       c.wdict.resize((size_t)4 * c.wsh);
       uint32_t rows = 0;
       for (int y = 0; y < c.wsh; ++y) {
@@ -978,14 +1035,8 @@ stitch_status stitch_plan_create(int32_t n, const int32_t* frame_w, const int32_
       const int x1 = std::min<int>(r.x + r.w, r.x + (int)ceil_div(b.x + b.w - r.x, q) * q);
       c.lwin[k] = Rect{x0, b.y, x1 - x0, b.h};
     }
-    // --- keep the seam weights on roi[0] ---
-    const Rect r0 = c.roi[0];
-    if (!r0.empty()) {
-      c.mask_row = align_up(r0.w, 256);
-      c.mask0.assign((size_t)c.mask_row * r0.h, 0);
-      for (int y = 0; y < r0.h; ++y)
-        std::memcpy(&c.mask0[(size_t)y * c.mask_row], m + (size_t)(r0.y + y) * canvas_w + r0.x, r0.w);
-    }
+    // the workspace holds the seam weights on roi[0] (laid out from wdict at bind)
+    if (!c.roi[0].empty()) c.mask_row = align_up(c.roi[0].w, 256);
   }
   // --- workspace layout ---
   Layout lay;
@@ -1048,9 +1099,20 @@ stitch_status stitch_plan_bind(stitch_plan* p, void* workspace, size_t bytes, vo
   build_tables(p);
   const hipStream_t s = (hipStream_t)stream;
   stitch_status st = STITCH_OK;
+  std::vector<std::vector<uint8_t>> masks(p->n);       // alive until the stream has drained
   for (int i = 0; i < p->n && !st; ++i) {
     const CamPlan& c = p->cam[i];
-    if (!c.mask0.empty()) st = upload(p->ws + c.off_mask0, c.mask0.data(), c.mask0.size(), s, "seam weight upload");
+    const Rect r = c.roi[0];
+    if (r.empty()) continue;
+    masks[i].assign((size_t)c.mask_row * r.h, 0);
+    const int x0 = std::max(r.x, c.wsx), x1 = std::min(r.x + r.w, c.wsx + c.wsw);
+    for (int y = std::max(r.y, c.wsy); x0 < x1 && y < std::min(r.y + r.h, c.wsy + c.wsh); ++y) {
+      uint32_t id;
+      std::memcpy(&id, &c.wdict[(size_t)4 * (y - c.wsy)], sizeof id);
+      std::memcpy(&masks[i][(size_t)(y - r.y) * c.mask_row + (x0 - r.x)],
+                  &c.wdict[(size_t)4 * c.wsh + (size_t)id * c.wsw + (x0 - c.wsx)], x1 - x0);
+    }
+    st = upload(p->ws + c.off_mask0, masks[i].data(), masks[i].size(), s, "seam weight upload");
   }
   for (int k = 0; k + 1 < p->L && !st; ++k)
     st = upload(p->ws + p->off_items[k], p->items[k].data(), p->items[k].size() * sizeof(PyrItem), s, "table upload");

@@ -136,5 +136,7 @@ stitch_status fail(stitch_status s, const char* fmt, ...);
 stitch_status hip_fail(hipError_t e, const char* what);
 stitch_status check_image(const stitch_image* im, const char* name, int dtype, int layout, int channels);
 bool hinv_spec(const double* H, float out[9], double* sign_out, const char** why);
+// Bounding box {x, y, w, h} of the non-zero bytes of a w x h map; false when there is none.
+bool weight_box(const uint8_t* m, int w, int h, int box[4]);
 
 }  // namespace stitch
