@@ -83,6 +83,10 @@ KERNEL_KINDS = {
     "k_blend<float, false, false>": "blend_middle/top, batched (f32)",
     "k_blend<_Float16, true, false>": "blend_level0, batched (f16)",
     "k_blend<_Float16, false, false>": "blend_middle/top, batched (f16)",
+    "k_tail<float, false>": "level_pass (f32), small levels", "k_tail<_Float16, false>": "level_pass (f16), small levels",
+    "k_blend_tail<float, false>": "blend_middle/top (f32), small levels",
+    "k_blend_tail<_Float16, false>": "blend_middle/top (f16), small levels",
+    "k_blend_tail<float, true>": "blend of every level (f32)", "k_blend_tail<_Float16, true>": "blend of every level (f16)",
     "k_lorb_clear": "L-ORB clear", "k_lorb_detect": "L-ORB detect (FAST, R, suppression)",
     "k_lorb_select": "L-ORB select (histogram threshold)", "k_lorb_rank": "L-ORB rank",
     "k_lorb_brief": "L-ORB BRIEF",
@@ -408,12 +412,16 @@ def phase_bytes(plan, rig, s, keep_r0=False):
     return out
 
 
-# launch kinds of the plain form's event timing -> the phases each covers
-PLAIN_KINDS = {"warp_level0_pass": lambda L: ["pyr0"],
-               "level_pass": lambda L: [f"pyr{k}" for k in range(1, L - 1)],
-               "blend_level0": lambda L: ["blend0"],
-               "blend_middle": lambda L: [f"blend{k}" for k in range(L - 2, 0, -1)],
-               "blend_top": lambda L: [f"blend{L - 1}"]}
+def plain_kinds(L, per_step):
+    """Launch kinds of the plain form's event timing -> the phases each covers in a step
+    (per_step: launches of each kind): the small levels' single launches, which are timed as a
+    level pass and as the top blend (or level 0's), cover every level the others leave."""
+    m = per_step.get("blend_middle", 0)
+    own0 = "blend_top" in per_step
+    return {"warp_level0_pass": ["pyr0"], "level_pass": [f"pyr{k}" for k in range(1, L - 1)],
+            "blend_level0": [f"blend{k}" for k in range(1 if own0 else L)],
+            "blend_middle": [f"blend{k}" for k in range(1, m + 1)],
+            "blend_top": [f"blend{k}" for k in range(m + 1, L)]}
 
 
 def phase_name(key):
@@ -1121,14 +1129,16 @@ def _row(tot_ms, launches, steps, nbytes):
 
 def kernel_table(plan, rig, timing, steps, s):
     """Plain form: per launch kind, average launch time and bytes (the kind's phases of a
-    frame averaged the same way as its launches)."""
+    frame, over its launches)."""
     ph = phase_bytes(plan, rig, s)
     table = {}
+    per_step = {kind: launches // steps for kind, (_, launches) in timing.items()}
+    kinds = plain_kinds(rig.levels, per_step)
     for kind, (tot_ms, launches) in timing.items():
-        keys = PLAIN_KINDS.get(kind, lambda L: [])(rig.levels)
-        if not keys:
+        keys = kinds.get(kind, [])
+        if not keys or not per_step[kind]:
             continue
-        table[kind] = _row(tot_ms, launches, steps, float(np.mean([ph[k] for k in keys])))
+        table[kind] = _row(tot_ms, launches, steps, sum(ph[k] for k in keys) / per_step[kind])
     return table
 
 

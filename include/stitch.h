@@ -208,7 +208,9 @@ stitch_status stitch_plan_regions(const stitch_plan* plan, int32_t camera, int32
  * events is charged to the launch's kind:
  *   0 warp + level-0 pyramid pass, 1 pyramid passes of levels >= 1, 2 blend of level 0
  *   (with EXPAND of R_1), 3 blend of a middle level, 4 blend of the top level, 5 blend of
- *   a single-level plan, 6 warp of a single-level plan.
+ *   a single-level plan, 6 warp of a single-level plan.  Small levels share a launch: a
+ *   pyramid launch of several levels counts as kind 1, a blend launch of several levels as
+ *   kind 4, or kind 2 when level 0 is among them.
  * set_timing clears the totals; read_timing waits for the recorded events and returns
  * accumulated milliseconds and launch counts per kind.  Errors: NULL, DEVICE. */
 #define STITCH_TIMING_KINDS 8

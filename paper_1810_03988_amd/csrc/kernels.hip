@@ -112,6 +112,33 @@ __device__ __forceinline__ int fold(int i, int n) {
   return i < n ? i : p - i;
 }
 
+// EXPAND at even samples, 1/8 (a + c) + 3/4 b with s = a + c: along rows first (exp_h), then down
+// the columns (exp_v).  Every kernel that expands uses these two, whose roundings differ, so
+// that all of them give the same bits.  (At odd samples 1/2 (a + b) has one rounding however
+// it is formed; so do REDUCE's 1/16 and 1/4 terms.)
+__device__ __forceinline__ float exp_h(float s, float b) { return __builtin_fmaf(0.75f, b, 0.125f * s); }
+__device__ __forceinline__ float exp_v(float s, float b) { return __builtin_fmaf(0.125f, s, 0.75f * b); }
+
+// FP16 storage rounds a float to half; where that float is itself a multiply-add the compiler may
+// round the exact sum to half at once (v_fma_mixlo_f16) or to float first, and the two differ
+// about once in 10^7 samples.  Which of the two is part of a result that several kernels share,
+// so it is written down: fma_half rounds once, settled(v) keeps v the float it is.
+__device__ __forceinline__ float fma_half(float a, float b, float c) {
+  _Float16 r;
+  asm("v_fma_mixlo_f16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return (float)r;
+}
+__device__ __forceinline__ float settled(float v) {
+  asm("" : "+v"(v));
+  return v;
+}
+// Column `col` (0 .. 3 of an aligned four) of a band's odd row: g - s/2, s the sum of the two
+// rows it lies between.
+__device__ __forceinline__ float band_odd(float g, float s, int, float) { return __builtin_fmaf(-0.5f, s, g); }
+__device__ __forceinline__ float band_odd(float g, float s, int col, _Float16) {
+  return col < 2 ? fma_half(-0.5f, s, g) : settled(__builtin_fmaf(-0.5f, s, g));
+}
+
 // Workgroups are dispatched round-robin over the 8 XCDs; give each XCD a contiguous
 // run of logical tiles so neighbouring tiles (which share halos) share an L2.
 __device__ __forceinline__ int xcd_remap(int b, int g) {
@@ -879,9 +906,9 @@ __global__ void __launch_bounds__(kThreads, 4) k_pyr(const PyrItem* __restrict__
         for (int k = 0; k < 4; ++k) {
           const float* c = &sC[ch][2 * rq + k][CO + 2 * mm];
           const float2 lo = {c[0], c[1]}, hi = {c[2], c[3]};
-          eh[k].x = 0.125f * (lo.x + hi.x) + 0.75f * lo.y;
+          eh[k].x = exp_h(lo.x + hi.x, lo.y);
           eh[k].y = 0.5f * (lo.y + hi.x);
-          eh[k].z = 0.125f * (lo.y + hi.y) + 0.75f * hi.x;
+          eh[k].z = exp_h(lo.y + hi.y, hi.x);
           eh[k].w = 0.5f * (hi.x + hi.y);
         }
         const int X = X0 + x - it.lw_x;
@@ -890,18 +917,18 @@ __global__ void __launch_bounds__(kThreads, 4) k_pyr(const PyrItem* __restrict__
 #pragma unroll
         for (int yy = 0; yy < 4; ++yy) {
           const int y = 4 * rq + yy, k = yy >> 1;
-          float4 ev;
-          if (yy & 1) {
-            ev.x = 0.5f * (eh[k + 1].x + eh[k + 2].x); ev.y = 0.5f * (eh[k + 1].y + eh[k + 2].y);
-            ev.z = 0.5f * (eh[k + 1].z + eh[k + 2].z); ev.w = 0.5f * (eh[k + 1].w + eh[k + 2].w);
-          } else {
-            ev.x = 0.125f * (eh[k].x + eh[k + 2].x) + 0.75f * eh[k + 1].x;
-            ev.y = 0.125f * (eh[k].y + eh[k + 2].y) + 0.75f * eh[k + 1].y;
-            ev.z = 0.125f * (eh[k].z + eh[k + 2].z) + 0.75f * eh[k + 1].z;
-            ev.w = 0.125f * (eh[k].w + eh[k + 2].w) + 0.75f * eh[k + 1].w;
-          }
           const float4 gv = *reinterpret_cast<const float4*>(rowp(y + 4) + x + 4);
-          l[yy][0] = gv.x - ev.x; l[yy][1] = gv.y - ev.y; l[yy][2] = gv.z - ev.z; l[yy][3] = gv.w - ev.w;
+          if (yy & 1) {
+            l[yy][0] = band_odd(gv.x, eh[k + 1].x + eh[k + 2].x, 0, T());
+            l[yy][1] = band_odd(gv.y, eh[k + 1].y + eh[k + 2].y, 1, T());
+            l[yy][2] = band_odd(gv.z, eh[k + 1].z + eh[k + 2].z, 2, T());
+            l[yy][3] = band_odd(gv.w, eh[k + 1].w + eh[k + 2].w, 3, T());
+          } else {
+            l[yy][0] = gv.x - exp_v(eh[k].x + eh[k + 2].x, eh[k + 1].x);
+            l[yy][1] = gv.y - exp_v(eh[k].y + eh[k + 2].y, eh[k + 1].y);
+            l[yy][2] = gv.z - exp_v(eh[k].z + eh[k + 2].z, eh[k + 1].z);
+            l[yy][3] = gv.w - exp_v(eh[k].w + eh[k + 2].w, eh[k + 1].w);
+          }
         }
         // FP16: lanes 2m and 2m+1 hold eight adjacent columns of the same four rows; the
         // even lane stores rows 0-1 and the odd lane rows 2-3 as 16-byte vectors, each
@@ -976,6 +1003,30 @@ __device__ __forceinline__ int find_blend_item(const BlendItem* __restrict__ ite
     if (cst(items)[mid].tile_begin <= t) lo = mid; else hi = mid - 1;
   }
   return lo;
+}
+
+// Quantise one tile row (64 lanes, column X0 + x) of the panorama.  A full tile row in an
+// aligned panorama goes out as whole dwords: each group of four lanes (four adjacent pixels,
+// 12 bytes) packs its bytes into three dwords in its first lane; otherwise byte by byte.
+__device__ __forceinline__ void put_row(uint8_t* pano_ptr, int64_t pano_row, int X0, int x, int Y, int W, int H,
+                                        const float r[3]) {
+  const int X = X0 + x;
+  const bool words = X0 + kBlendTX <= W && (pano_row & 3) == 0 && ((uintptr_t)pano_ptr & 3) == 0;
+  // rint(255 R_0) clamped to [0, 255] by the byte conversion, packed byte by byte
+  uint32_t v = __builtin_amdgcn_cvt_pk_u8_f32(255.0f * r[0], 0u, 0u);
+  v = __builtin_amdgcn_cvt_pk_u8_f32(255.0f * r[1], 1u, v);
+  v = __builtin_amdgcn_cvt_pk_u8_f32(255.0f * r[2], 2u, v);
+  GLB uint8_t* prow = mg<uint8_t>(pano_ptr) + (int64_t)Y * pano_row + (int64_t)X * 3;
+  if (words) {
+    const uint32_t v1 = __shfl_down(v, 1), v2 = __shfl_down(v, 2), v3 = __shfl_down(v, 3);
+    if ((x & 3) == 0 && Y < H) {
+      typedef uint32_t vu3 __attribute__((ext_vector_type(3)));
+      *reinterpret_cast<GLB vu3*>(prow) = vu3{v | (v1 << 24), (v1 >> 8) | (v2 << 16), (v2 >> 16) | (v3 << 8)};
+    }
+  } else if (X < W && Y < H) {
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) prow[ch] = (uint8_t)(v >> (8 * ch));
+  }
 }
 
 template <typename T, bool FINAL, bool KARG>
@@ -1116,9 +1167,9 @@ __global__ void __launch_bounds__(kThreads) k_blend(const BlendItem* __restrict_
         const float2 lo = *reinterpret_cast<const float2*>(&sC[ch][i][2 * m]);
         const float2 hi = *reinterpret_cast<const float2*>(&sC[ch][i][2 * m + 2]);
         float4 o;
-        o.x = 0.125f * (lo.x + hi.x) + 0.75f * lo.y;
+        o.x = exp_h(lo.x + hi.x, lo.y);
         o.y = 0.5f * (lo.y + hi.x);
-        o.z = 0.125f * (lo.y + hi.y) + 0.75f * hi.x;
+        o.z = exp_h(lo.y + hi.y, hi.x);
         o.w = 0.5f * (hi.x + hi.y);
         *reinterpret_cast<float4*>(&sE[ch][i][4 * m]) = o;
       }
@@ -1145,7 +1196,7 @@ __global__ void __launch_bounds__(kThreads) k_blend(const BlendItem* __restrict_
 #pragma unroll
       for (int ch = 0; ch < 3; ++ch) {
         const float ev = (y & 1) ? 0.5f * (sE[ch][yh + 1][x] + sE[ch][yh + 2][x])
-                                 : 0.125f * (sE[ch][yh][x] + sE[ch][yh + 2][x]) + 0.75f * sE[ch][yh + 1][x];
+                                 : exp_v(sE[ch][yh][x] + sE[ch][yh + 2][x], sE[ch][yh + 1][x]);
         acc[j][ch] = acc[j][ch] + ev;
       }
     }
@@ -1156,32 +1207,521 @@ __global__ void __launch_bounds__(kThreads) k_blend(const BlendItem* __restrict_
     }
   }
   if (FINAL) {
-    // Quantise.  A full tile row in an aligned panorama goes out as whole dwords: each
-    // group of four lanes (four adjacent pixels, 12 bytes) packs its bytes into three
-    // dwords in its first lane; otherwise byte by byte.
     uint8_t* const pano_ptr = po.ptr ? po.ptr : a.pano;
     const int64_t pano_row = po.ptr ? po.row : a.pano_row;
-    const bool words = X0 + TX <= a.W && (pano_row & 3) == 0 && ((uintptr_t)pano_ptr & 3) == 0;
-    GLB uint8_t* pano = mg<uint8_t>(pano_ptr);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int Y = Y0 + ybase + j;
-      // rint(255 R_0) clamped to [0, 255] by the byte conversion, packed byte by byte
-      uint32_t v = __builtin_amdgcn_cvt_pk_u8_f32(255.0f * acc[j][0], 0u, 0u);
-      v = __builtin_amdgcn_cvt_pk_u8_f32(255.0f * acc[j][1], 1u, v);
-      v = __builtin_amdgcn_cvt_pk_u8_f32(255.0f * acc[j][2], 2u, v);
-      GLB uint8_t* prow = pano + (int64_t)Y * pano_row + (int64_t)X * 3;
-      if (words) {
-        const uint32_t v1 = __shfl_down(v, 1), v2 = __shfl_down(v, 2), v3 = __shfl_down(v, 3);
-        if ((x & 3) == 0 && Y < a.H) {
-          typedef uint32_t vu3 __attribute__((ext_vector_type(3)));
-          *reinterpret_cast<GLB vu3*>(prow) = vu3{v | (v1 << 24), (v1 >> 8) | (v2 << 16), (v2 >> 16) | (v3 << 8)};
+    for (int j = 0; j < 4; ++j) put_row(pano_ptr, pano_row, X0, x, Y0 + ybase + j, a.W, a.H, acc[j]);
+  }
+}
+
+// ------------------------------------------------------------------------------------
+// The tail of a pyramid: up to three consecutive REDUCEs (and the bands between them) of small
+// levels in one launch.  A level pass of a few hundred workgroups takes 7-10 us however small
+// it is -- launch, descriptor, window and store latencies one after another, with the chip
+// nearly empty -- so three levels cost 25-30 us.  Here a workgroup takes one channel of a
+// 64x32 tile with the halo all three levels need (104x69 samples: 3.5 times the tile's own,
+// which is why only levels below the host's size limit are done this way), and the coarser
+// levels never leave LDS between their uses.  VGA pair, levels 1 .. 4: 23.5 -> 12.3 us;
+// four 1080p cameras, levels 2 .. 5: 27.7 -> 23 us.
+//
+// The values are those of the level passes bit for bit: the same expressions, a level's
+// samples rounded to the storage type before they are reduced again, 0 outside its region,
+// reflect-101 at its canvas edges (each level's own for REDUCE; the reduced reflected fine
+// samples, as they come, for EXPAND).
+//
+// Windows in LDS, (0, 0) the tile's first sample of a level: level 0 columns -24 .. 79, rows
+// -22 .. 46; level 1 columns -12 .. 39, rows -10 .. 22; level 2 columns -8 .. 19, rows
+// -4 .. 10; level 3 columns -1 .. 10, rows -1 .. 4.
+constexpr int kT0S = 104, kT0R = 69;                      // the finest window (f below, d = 0)
+constexpr int kT1S = 52, kT1R = 33, kT2S = 28, kT2R = 15, kT3S = 12, kT3R = 6;
+
+__device__ __forceinline__ float as_stored(float v, float) { return v; }
+__device__ __forceinline__ float as_stored(float v, _Float16) { return (float)(_Float16)v; }
+__device__ __forceinline__ float byte_as_stored(uint32_t v, float) { return (float)v * kInv255; }
+__device__ __forceinline__ float byte_as_stored(uint32_t v, _Float16) { return fma_half((float)v, kInv255, 0.0f); }
+
+// Periodic reflect-101 by repeated reflection (a short loop; one turn where the overshoot is
+// below the side).
+__device__ __forceinline__ int fold_loop(int i, int n) {
+  for (;;) {
+    i = i < 0 ? -i : i;
+    if (i < n) return i;
+    i = 2 * (n - 1) - i;
+  }
+}
+
+// Read one dword of every 64-byte line of a descriptor at once, so that its fields, wanted one
+// level after another, come from the scalar cache (each line's first read is a trip to memory
+// otherwise: 4 x 1000 cycles of a tail's 20000).
+template <typename D>
+__device__ __forceinline__ void touch(const CST D* p) {
+  const CST int* w = (const CST int*)p;
+  int any = 0;
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(D) / 4); i += 16) any |= w[i];
+  asm volatile("" ::"s"(any));
+}
+
+// Four adjacent samples, columns X .. X+3 of a window w wide, to row pointer p (elements).
+template <typename T>
+__device__ __forceinline__ void store4(GLB T* p, int X, int w, const float v[4]) {
+  if (X >= 0 && X + 3 < w && ((uintptr_t)(p + X) & (4 * sizeof(T) - 1)) == 0) {
+    stg4nt(p + X, v);
+  } else {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (X + u >= 0 && X + u < w) stgnt(p, X + u, v[u]);
+  }
+}
+
+template <typename T, bool KARG>
+__global__ void __launch_bounds__(kThreads) k_tail(const TailItem* __restrict__ items, int nitems, const TailItem one,
+                                                   int nslot) {
+  // sm: the finest window, then levels 1 and 2 as the next REDUCE reads them; sc: levels 1 .. 3
+  // as reduced
+  __shared__ __attribute__((aligned(16))) float sm[kT0R * kT0S + kT1R * kT1S + kT2R * kT2S];
+  __shared__ __attribute__((aligned(16))) float sc[kT1R * kT1S + kT2R * kT2S + kT3R * kT3S];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t = (int)blockIdx.x / nslot, slot = (int)blockIdx.x - t * nslot;
+  const CST TailItem* itp;
+  if (KARG) {
+    itp = (const CST TailItem*)&one;
+  } else {
+    int lo = 0, hi = nitems - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (cst(items)[mid].tile_begin <= t) lo = mid; else hi = mid - 1;
+    }
+    itp = cst(items) + lo;
+  }
+  const CST TailItem& it = *itp;
+  touch(itp);
+  const int lt = t - it.tile_begin, tyi = lt / it.tiles_x, txi = lt - tyi * it.tiles_x;
+  const int X0 = it.tile_x0 + txi * kTailTX, Y0 = it.tile_y0 + tyi * kTailTY;
+  const int nch = it.nch;
+  const bool img = slot < nch;
+
+  // ---- the finest level's window ----
+  {
+    const TailLevel l0 = ld_cst(it.lev);
+    const int wx0 = X0 - 24, wy0 = Y0 - 22;
+    const int rx = l0.roi_x, ry = l0.roi_y, rw = l0.roi_w, rh = l0.roi_h, lw = l0.w, lh = l0.h;
+    const bool inx = wx0 >= 0 && wx0 + kT0S <= lw;
+    const int64_t row = img ? it.img_row : it.msk_row;
+    constexpr int C = 16 / (int)sizeof(T);
+    const bool u8 = KARG && img && it.src_u8 != 0;
+    const GLB T* src = img ? cg<T>(it.img) + slot * it.img_plane : cg<T>(it.msk);
+    if (!u8 && inx && rw > 0 && rh > 0 && (wx0 - rx) % C == 0 && ((uintptr_t)src & 15) == 0 && row % C == 0 &&
+        (!KARG || it.padded || rw % C == 0)) {
+      // columns inside the canvas: aligned 16-byte chunks from positions clamped into the
+      // plane (see k_pyr), rows folded; a wave reads RPW rows at a time
+      constexpr int NCK = kT0S / C, RPW = 64 / NCK, NQ = (kT0R + 4 * RPW - 1) / (4 * RPW);
+      const int rs = lane / NCK, k = lane - rs * NCK, c0 = wx0 - rx + C * k;
+      const int col = C * min(max(c0 / C, 0), (rw + C - 1) / C - 1);
+      const int keep = min(max(rw - c0, 0), c0 < 0 ? 0 : C);
+      uint32_t raw[NQ][4];
+      bool in[NQ];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const int y = fold_loop(wy0 + min((q * 4 + wv) * RPW + rs, kT0R - 1), lh) - ry;
+        in[q] = y >= 0 && y < rh;
+        typedef uint32_t vu4t __attribute__((ext_vector_type(4)));
+        const vu4t v = *reinterpret_cast<const GLB vu4t*>(src + (int64_t)min(max(y, 0), rh - 1) * row + col);
+        raw[q][0] = v.x; raw[q][1] = v.y; raw[q][2] = v.z; raw[q][3] = v.w;
+      }
+      float* out = sm + (wv * RPW + rs) * kT0S + C * k;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        if (rs >= RPW || (q * 4 + wv) * RPW + rs >= kT0R) continue;
+        float v[C];
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+          const float smp = sizeof(T) == 4 ? __builtin_bit_cast(float, raw[q][i & 3])
+                                           : from_raw((uint16_t)(raw[q][i >> 1] >> (16 * (i & 1))));
+          v[i] = in[q] && i < keep ? smp : 0.0f;
         }
-      } else if (X < a.W && Y < a.H) {
 #pragma unroll
-        for (int ch = 0; ch < 3; ++ch) prow[ch] = (uint8_t)(v >> (8 * ch));
+        for (int h = 0; h < C / 4; ++h)
+          *reinterpret_cast<float4*>(out + q * 4 * RPW * kT0S + 4 * h) =
+              float4{v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]};
+      }
+    } else {
+      // sample by sample: a wave takes a row at a time, a lane two columns
+      constexpr int NB = 6;
+      int xc[2];
+      bool xin[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        xc[h] = fold_loop(wx0 + min(lane + 64 * h, kT0S - 1), lw) - rx;
+        xin[h] = xc[h] >= 0 && xc[h] < rw;
+        xc[h] = xin[h] ? xc[h] : 0;
+      }
+#pragma unroll 1
+      for (int g = wv; g < kT0R; g += 4 * NB) {
+        uint32_t raw[NB][2];
+        bool yin[NB];
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+          const int y = fold_loop(wy0 + min(g + 4 * q, kT0R - 1), lh) - ry;
+          yin[q] = y >= 0 && y < rh;
+          const int64_t base = yin[q] ? (int64_t)y * row : 0;
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            raw[q][h] = u8 ? (uint32_t)cg<uint8_t>(it.img)[base + xc[h]] : (uint32_t)ld_raw(src, base + xc[h]);
+        }
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+          const int r = g + 4 * q;
+          if (r >= kT0R) break;
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const float v = u8 ? byte_as_stored(raw[q][h], T()) : from_raw((typename RawOf<T>::type)raw[q][h]);
+            if (lane + 64 * h < kT0S) sm[r * kT0S + lane + 64 * h] = yin[q] && xin[h] ? v : 0.0f;
+          }
+        }
       }
     }
+  }
+  __syncthreads();
+  if (KARG && it.copy_out && img) {
+    // the finest level itself, on its region
+    const CST TailLevel& l0 = it.lev[0];
+    GLB T* out = mg<T>(it.copy_out) + slot * it.copy_plane;
+#pragma unroll 1
+    for (int e = tid; e < (kTailTX / 4) * kTailTY; e += kThreads) {
+      const int r = e / (kTailTX / 4), m = e - r * (kTailTX / 4), y = Y0 + r - l0.roi_y;
+      if (y < 0 || y >= l0.roi_h) continue;
+      const float4 v4 = *reinterpret_cast<const float4*>(&sm[(22 + r) * kT0S + 24 + 4 * m]);
+      const float v[4] = {v4.x, v4.y, v4.z, v4.w};
+      store4(out + y * it.copy_row, X0 + 4 * m - l0.roi_x, l0.roi_w, v);
+    }
+  }
+
+  // ---- level by level: f the fine window, c the coarse one as reduced, g as the next level
+  //      reads it (one body for all three: the code is fetched once, and fetching it is much
+  //      of what a launch this small waits for; above the finest level a stage's few items
+  //      are spread over the waves, since every stage is then one thread's latency) ----
+  int fs = kT0S, fr = kT0R, fx = 24, fy = 22;       // stride, rows, column and row of (0, 0)
+  float* f = sm;
+  float* c = sc;
+  const int depth = it.depth;
+#pragma unroll 1
+  for (int d = 0; d < depth; ++d) {
+    const TailLevel lv = ld_cst(it.lev + d);    // every field at once, none behind a test
+    const int cs = d == 0 ? kT1S : d == 1 ? kT2S : kT3S, cr = d == 0 ? kT1R : d == 1 ? kT2R : kT3R;
+    const int cx = d == 0 ? 12 : d == 1 ? 8 : 1, cy = d == 0 ? 10 : d == 1 ? 4 : 1;
+    float* g = f + fr * fs;
+    // REDUCE: pair p of coarse columns reads fine columns fo + 4p .. fo + 4p + 7, coarse row i
+    // fine rows 2i .. 2i + 4; a thread takes a pair and four rows (one above the finest level)
+    {
+      const int np = d == 0 ? 25 : d == 1 ? 12 : 5, fo = d == 2 ? 4 : 0, co = d == 0 ? 1 : d == 1 ? 3 : 0;
+      const int i = (tid * (d == 0 ? 2622 : d == 1 ? 5462 : 13108)) >> 16, p = tid - i * np;   // tid / np
+      const int step = d == 0 ? 4 : 1, i0 = step * i, i1 = min(i0 + step, cr);
+      auto hrow = [&](int r) -> float2 {
+        const float* rowp = f + r * fs + fo + 4 * p;
+        const float4 u = *reinterpret_cast<const float4*>(rowp);
+        const float4 v = *reinterpret_cast<const float4*>(rowp + 4);
+        return float2{kW0 * (u.x + v.x) + kW1 * (u.y + u.w) + kW2 * u.z,
+                      kW0 * (u.z + v.z) + kW1 * (u.w + v.y) + kW2 * v.x};
+      };
+      if (i0 < cr) {
+        float2 h0 = hrow(2 * i0), h1 = hrow(2 * i0 + 1), h2 = hrow(2 * i0 + 2);
+#pragma unroll 1
+        for (int m = i0; m < i1; ++m) {
+          const float2 h3 = hrow(2 * m + 3), h4 = hrow(2 * m + 4);
+          float* o = c + m * cs + co + 2 * p;
+          o[0] = kW0 * (h0.x + h4.x) + kW1 * (h1.x + h3.x) + kW2 * h2.x;
+          o[1] = kW0 * (h0.y + h4.y) + kW1 * (h1.y + h3.y) + kW2 * h2.y;
+          h0 = h2; h1 = h3; h2 = h4;
+        }
+      }
+    }
+    __syncthreads();
+    // L = G - EXPAND(coarse), four columns and two rows a thread
+    const int rq = tid >> (4 - d), mm = tid & ((16 >> d) - 1);
+    if (img & (lv.lw_w > 0) & (rq < (16 >> d))) {
+      float4 eh[3];
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        const float* r = c + (cy - 1 + rq + u) * cs + cx - 1 + 2 * mm;
+        const float2 lo = {r[0], r[1]}, hi = {r[2], r[3]};
+        eh[u].x = exp_h(lo.x + hi.x, lo.y);
+        eh[u].y = 0.5f * (lo.y + hi.x);
+        eh[u].z = exp_h(lo.y + hi.y, hi.x);
+        eh[u].w = 0.5f * (hi.x + hi.y);
+      }
+#pragma unroll 1
+      for (int yy = 0; yy < 2; ++yy) {
+        const int y = (Y0 >> d) + 2 * rq + yy - lv.lw_y;
+        if ((y < 0) | (y >= lv.lw_h)) continue;
+        const float4 gv = *reinterpret_cast<const float4*>(f + (fy + 2 * rq + yy) * fs + fx + 4 * mm);
+        float l[4];
+        l[0] = yy ? band_odd(gv.x, eh[1].x + eh[2].x, 0, T()) : gv.x - exp_v(eh[0].x + eh[2].x, eh[1].x);
+        l[1] = yy ? band_odd(gv.y, eh[1].y + eh[2].y, 1, T()) : gv.y - exp_v(eh[0].y + eh[2].y, eh[1].y);
+        l[2] = yy ? band_odd(gv.z, eh[1].z + eh[2].z, 2, T()) : gv.z - exp_v(eh[0].z + eh[2].z, eh[1].z);
+        l[3] = yy ? band_odd(gv.w, eh[1].w + eh[2].w, 3, T()) : gv.w - exp_v(eh[0].w + eh[2].w, eh[1].w);
+        store4(mg<T>(lv.l_out) + slot * lv.l_plane + y * lv.l_row, (X0 >> d) + 4 * mm - lv.lw_x, lv.lw_w, l);
+      }
+    }
+    // the tile's own coarse samples, four columns a thread (waves 0 and 1; above the finest
+    // level, where wave 0 has the band, wave 1)
+    {
+      const int e = d == 0 ? tid : tid - 64;
+      const int i = e >> (3 - d), m = e & ((8 >> d) - 1), y = (Y0 >> (d + 1)) + i - lv.croi_y;
+      if ((e >= 0) & (i < (16 >> d)) & (y >= 0) & (y < lv.croi_h)) {
+        const float* q = c + (cy + i) * cs + cx + 4 * m;
+        const float v[4] = {q[0], q[1], q[2], q[3]};
+        GLB T* out = img ? mg<T>(lv.g_out) + slot * lv.g_plane + y * lv.g_row : mg<T>(lv.gm_out) + y * lv.gm_row;
+        store4(out, (X0 >> (d + 1)) + 4 * m - lv.croi_x, lv.croi_w, v);
+      }
+    }
+    if (d + 1 == depth) break;
+    // the next REDUCE's input: samples as stored, 0 outside the level's region, reflect-101
+    // outside its canvas (a reflected position beyond the window feeds nothing that is kept:
+    // clamped into it); a wave's rows are all read before any is written
+    {
+      const TailLevel nx = ld_cst(it.lev + d + 1);
+      const int x0 = (X0 >> (d + 1)) - cx, y0 = (Y0 >> (d + 1)) - cy;
+      const int x = fold_loop(x0 + min(lane, cs - 1), nx.w), xc = min(max(x - x0, 0), cs - 1);
+      const bool xin = x >= nx.roi_x && x < nx.roi_x + nx.roi_w;
+      constexpr int NR = 5;
+#pragma unroll 1
+      for (int r0 = wv; r0 < cr; r0 += 4 * NR) {
+        float v[NR];
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+          const int y = fold_loop(y0 + min(r0 + 4 * i, cr - 1), nx.h);
+          v[i] = c[min(max(y - y0, 0), cr - 1) * cs + xc];
+          v[i] = xin & (y >= nx.roi_y) & (y < nx.roi_y + nx.roi_h) ? as_stored(v[i], T()) : 0.0f;
+        }
+#pragma unroll
+        for (int i = 0; i < NR; ++i)
+          if ((lane < cs) & (r0 + 4 * i < cr)) g[(r0 + 4 * i) * cs + lane] = v[i];
+      }
+    }
+    __syncthreads();
+    f = g;
+    c += cr * cs;
+    fs = cs; fr = cr; fx = cx; fy = cy;
+  }
+}
+
+// ------------------------------------------------------------------------------------
+// The small levels' collapse in one launch, bit for bit k_blend's level by level: a workgroup
+// of 512 takes a 64x16 tile of the finest level and, beside it, the windows of the coarser
+// levels its EXPANDs reach (34x10, 19x7, 11x5).  Every level's B is independent of the others',
+// so all are read at once -- chunks of 64 samples of a coarse level per wave -- and only the
+// collapse, in LDS, goes level by level.  Four launches of 5-7 us each (VGA pair, levels 4 .. 1)
+// become one of 10.4 us; four 1080p cameras' panorama, levels 5 .. 2: 24.7 -> 14.4 us.
+constexpr int kBtThreads = 512;
+constexpr int kBw[4] = {64, 34, 19, 11}, kBh[4] = {16, 10, 7, 5}, kBs[4] = {0, 35, 20, 12};
+
+constexpr int kB1 = 3 * kBh[1] * kBs[1], kB2 = 3 * kBh[2] * kBs[2], kB3 = 3 * kBh[3] * kBs[3];
+
+// Coarse sample (of m) that coarse position i stands for in EXPAND to n fine samples: 2i folded
+// by reflect-101, halved -- for the positions a window reaches, -1 .. m (beyond m nothing is
+// used).
+__device__ __forceinline__ int coarse_at(int i, int n, int m) { return i < 0 ? 1 : i >= m ? m - 1 - (n & 1) : i; }
+
+// Value at (x, y) of EXPAND of one channel's window r (stride st; its entry (0, 0) is coarse
+// position (bx, by), nx x ny entries), rows first combined horizontally, as k_blend does.
+__device__ __forceinline__ float expand_from(const float* r, int st, int nx, int ny, int bx, int by, int x, int y) {
+  const int q = (x >> 1) - bx, p = (y >> 1) - by;
+  const int c0 = min(max(q - 1, 0), nx - 1), c1 = min(max(q, 0), nx - 1), c2 = min(max(q + 1, 0), nx - 1);
+  const int cl = (x & 1) ? c1 : c0;
+  float m[3], n[3], o[3], e[3];
+#pragma unroll
+  for (int u = 0; u < 3; ++u) {
+    const float* row = r + min(max(p - 1 + u, 0), ny - 1) * st;
+    o[u] = row[cl];
+    m[u] = row[c1];
+    n[u] = row[c2];
+  }
+#pragma unroll
+  for (int u = 0; u < 3; ++u) e[u] = (x & 1) ? 0.5f * (o[u] + n[u]) : exp_h(o[u] + n[u], m[u]);
+  const float s = ((y & 1) ? e[1] : e[0]) + e[2];
+  return (y & 1) ? 0.5f * s : exp_v(s, e[1]);
+}
+
+template <typename T, bool FINAL>
+__global__ void __launch_bounds__(kBtThreads) k_blend_tail(const BlendTailItem one, PanoArg po) {
+  __shared__ float sB[kB1 + kB2 + kB3];       // levels 1, 2, 3: [channel][row][column]
+  const int tid = threadIdx.x;
+  const int t = (int)blockIdx.x;
+  const CST BlendTailItem& it = *(const CST BlendTailItem*)&one;
+  touch(&it);
+  const int tyi = t / it.tiles_x, txi = t - tyi * it.tiles_x;
+  const int X0 = txi * kBlendTX, Y0 = tyi * kBlendTY;
+  const int depth = it.depth;
+  const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  // B at canvas position (x, y) of a level, one camera: raw samples from an address valid for
+  // any (x, y), used later
+  using RawT = typename RawOf<T>::type;
+  struct Smp {
+    RawT l[3];
+    uint32_t w;
+    bool in, u8;
+  };
+  auto fetch = [&](const BlendCam& c, int x, int y, Smp& s) __attribute__((always_inline)) {
+    const GLB T* l = cg<T>(c.lap);
+    const int lx = x - c.lx, wx = x - c.wx, ly = y - c.ly, wy = y - c.wy;
+    s.in = (x >= c.vx0) & (x < c.vx1) & (y >= c.vy0) & (y < c.vy1);
+    const uint32_t loff = s.in ? __umul24((uint32_t)ly, (uint32_t)c.lap_row) + (uint32_t)lx : 0u;
+    const uint32_t woff = s.in ? __umul24((uint32_t)wy, (uint32_t)c.wgt_row) + (uint32_t)wx : 0u;
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) s.l[ch] = ld_raw(l, (uint32_t)ch * (uint32_t)c.lap_plane + loff);
+    s.u8 = c.wgt_u8 != 0;
+    s.w = s.u8 ? (uint32_t)cg<uint8_t>(c.wgt)[woff] : (uint32_t)ld_raw(cg<T>(c.wgt), woff);
+  };
+  auto add = [&](const Smp& s, float acc[3]) __attribute__((always_inline)) {
+    const float w = !s.in ? 0.0f : s.u8 ? (float)s.w * kInv255 : from_raw((RawT)s.w);
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) acc[ch] = acc[ch] + w * from_raw(s.l[ch]);
+  };
+
+  // ---- B of every level ----
+  // The cameras of every level whose band and weights meet the tile (lane i tests camera i),
+  // all levels' rectangles read together.
+  auto hits = [&](auto lc) __attribute__((always_inline)) -> uint64_t {
+    constexpr int l = decltype(lc)::value;
+    const CST BlendItem& a = it.lev[min(l, depth)];
+    const int x0 = (X0 >> l) - (l ? 2 : 0), y0 = (Y0 >> l) - (l ? 2 : 0);
+    const CST BlendCam& c = cst(a.cams)[min(lane, max(a.ncam - 1, 0))];
+    const bool h = (lane < a.ncam) & (c.vx0 < x0 + kBw[l] + 2) & (c.vx1 > x0) & (c.vy0 < y0 + kBh[l] + 2) & (c.vy1 > y0);
+    return __ballot(h);
+  };
+  const uint64_t hit0 = hits(Rows<0>()), hit1 = hits(Rows<1>()), hit2 = hits(Rows<2>()), hit3 = hits(Rows<3>());
+  // Coarse windows: entry (i, j) of level l stands for coarse position (X0 >> l) - 1 + j, row
+  // (Y0 >> l) - 1 + i, folded through the finer level's reflect-101 into the level.  A wave
+  // takes chunks wv and wv + 8 of 64 entries; with its rows of the finest level that is three
+  // positions a lane, whose first cameras' samples are all in flight together.
+  constexpr int N1 = (kBw[1] * kBh[1] + 63) / 64, N2 = (kBw[2] * kBh[2] + 63) / 64, N3 = (kBw[3] * kBh[3] + 63) / 64;
+  const int nchunk = N1 + (depth > 1 ? N2 : 0) + (depth > 2 ? N3 : 0);
+  static_assert(N1 + N2 + N3 <= 2 * (kBtThreads / 64), "two chunks a wave");
+  struct Job {
+    int l, x, y;          // level, position in it
+    float* out;           // its LDS entry, channel stride `step`
+    int step;
+    uint64_t cams;
+  };
+  auto job = [&](int chunk) __attribute__((always_inline)) {
+    Job j;
+    j.l = chunk < N1 ? 1 : chunk < N1 + N2 ? 2 : 3;
+    const int w = j.l == 1 ? kBw[1] : j.l == 2 ? kBw[2] : kBw[3], h = j.l == 1 ? kBh[1] : j.l == 2 ? kBh[2] : kBh[3];
+    const int st = j.l == 1 ? kBs[1] : j.l == 2 ? kBs[2] : kBs[3];
+    const int first = chunk - (j.l == 1 ? 0 : j.l == 2 ? N1 : N1 + N2);
+    float* sb = sB + (j.l == 1 ? 0 : j.l == 2 ? kB1 : kB1 + kB2);
+    j.cams = j.l == 1 ? hit1 : j.l == 2 ? hit2 : hit3;
+    const CST BlendItem& a = it.lev[j.l];
+    const CST BlendItem& f = it.lev[j.l - 1];
+    const int e = min(first * 64 + lane, w * h - 1);
+    const int r = j.l == 1 ? e / kBw[1] : j.l == 2 ? e / kBw[2] : e / kBw[3], c = e - r * w;
+    j.x = coarse_at((X0 >> j.l) - 1 + c, f.W, a.W);
+    j.y = coarse_at((Y0 >> j.l) - 1 + r, f.H, a.H);
+    j.out = sb + r * st + c;
+    j.step = h * st;
+    return j;
+  };
+  const CST BlendItem& a0 = it.lev[0];
+  const int X = X0 + lane, Yw = Y0 + 2 * wv;       // this thread: column X, rows Yw, Yw + 1
+  const Job ja = job(min(wv, nchunk - 1)), jb = job(min(wv + kBtThreads / 64, nchunk - 1));
+  const bool has_b = wv + kBtThreads / 64 < nchunk;      // uniform over the wave
+  float va[3] = {0.0f, 0.0f, 0.0f}, vb[3] = {0.0f, 0.0f, 0.0f}, acc[2][3] = {};
+  {
+    // each turn: the next camera of each position, every sample read before any is used
+    uint64_t ra = ja.cams, rb = has_b ? jb.cams : 0, rm = hit0;
+#pragma unroll 1
+    while (ra | rb | rm) {
+      Smp sa, sb, s0, s1;
+      const bool ca = ra != 0, cb = rb != 0, cm = rm != 0;
+      if (ca) fetch(ld_cst(cst(it.lev[ja.l].cams) + (int)__builtin_ctzll(ra)), ja.x, ja.y, sa);
+      if (cm) {
+        const BlendCam c = ld_cst(cst(a0.cams) + (int)__builtin_ctzll(rm));
+        fetch(c, X, Yw, s0);
+        fetch(c, X, Yw + 1, s1);
+      }
+      if (cb) fetch(ld_cst(cst(it.lev[jb.l].cams) + (int)__builtin_ctzll(rb)), jb.x, jb.y, sb);
+      if (ca) add(sa, va);
+      if (cm) {
+        add(s0, acc[0]);
+        add(s1, acc[1]);
+      }
+      if (cb) add(sb, vb);
+      ra &= ra - 1;
+      rb &= rb - 1;
+      rm &= rm - 1;
+    }
+  }
+#pragma unroll
+  for (int ch = 0; ch < 3; ++ch) {
+    ja.out[ch * ja.step] = va[ch];
+    if (has_b) jb.out[ch * jb.step] = vb[ch];
+  }
+  __syncthreads();
+
+  // ---- collapse, from the top (one body for all levels; a thread takes one channel of an
+  //      entry, two at level 1) ----
+#pragma unroll 1
+  for (int l = depth; l >= 1; --l) {
+    const BlendItem a = ld_cst(it.lev + l);     // every field at once, none behind a test
+    const int fW = it.lev[l - 1].W, fH = it.lev[l - 1].H;
+    const int w = l == 1 ? kBw[1] : l == 2 ? kBw[2] : kBw[3], h = l == 1 ? kBh[1] : l == 2 ? kBh[2] : kBh[3];
+    const int st = l == 1 ? kBs[1] : l == 2 ? kBs[2] : kBs[3];
+    const int nw = l == 1 ? kBw[2] : kBw[3], nh = l == 1 ? kBh[2] : kBh[3], ns = l == 1 ? kBs[2] : kBs[3];
+    float* sb = sB + (l == 1 ? 0 : l == 2 ? kB1 : kB1 + kB2);
+    const int iw = l == 1 ? 1928 : l == 2 ? 3450 : 5958;          // ceil(65536 / w)
+#pragma unroll 1
+    for (int e = tid; e < 3 * w * h; e += kBtThreads) {
+      const int q = (e * iw) >> 16, c = e - q * w;                // q = e / w: channel and row
+      const int ch = (q >= h ? 1 : 0) + (q >= 2 * h ? 1 : 0), r = q - ch * h;
+      const int ox = (X0 >> l) - 1 + c, oy = (Y0 >> l) - 1 + r;
+      float* p = sb + q * st + c;
+      float v = *p;
+      if (l < depth) {
+        const int x = coarse_at(ox, fW, a.W), y = coarse_at(oy, fH, a.H);
+        v = settled(v + expand_from(sb + 3 * h * st + ch * nh * ns, ns, nw, nh, (X0 >> (l + 1)) - 1,
+                                    (Y0 >> (l + 1)) - 1, x, y));
+      }
+      if ((c >= 1) & (c <= (kBlendTX >> l)) & (r >= 1) & (r <= (kBlendTY >> l)) & (ox < a.W) & (oy < a.H) &
+          (a.r_out != nullptr))
+        stg(mg<T>(a.r_out), ch * a.rout_plane + (int64_t)oy * a.rout_row + ox, v);
+      *p = as_stored(v, T());
+    }
+    __syncthreads();
+  }
+
+  // the finest level: this thread's two rows share their three coarse rows' horizontal EXPAND
+  GLB T* ro = mg<T>(a0.r_out);
+#pragma unroll
+  for (int ch = 0; ch < 3; ++ch) {
+    float e[3];
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+      // coarse rows wv - 1 .. wv + 1 and columns x / 2 - 1 .. x / 2 + 1 of the tile
+      const float* row = sB + (ch * kBh[1] + wv + u) * kBs[1] + (lane >> 1);
+      const float m = row[1], sum = row[lane & 1] + row[2];
+      e[u] = (lane & 1) ? 0.5f * sum : exp_h(sum, m);
+    }
+    acc[0][ch] = settled(acc[0][ch] + exp_v(e[0] + e[2], e[1]));
+    acc[1][ch] = settled(acc[1][ch] + 0.5f * (e[1] + e[2]));
+  }
+  if (ro != nullptr) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int Y = Yw + j;
+      if (X < a0.W && Y < a0.H) {
+        const int64_t off = (int64_t)Y * a0.rout_row + X;
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) stg(ro, ch * a0.rout_plane + off, acc[j][ch]);
+      }
+    }
+  }
+  if (FINAL) {
+    uint8_t* const pano_ptr = po.ptr ? po.ptr : a0.pano;
+    const int64_t pano_row = po.ptr ? po.row : a0.pano_row;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) put_row(pano_ptr, pano_row, X0, lane, Yw + j, a0.W, a0.H, acc[j]);
   }
 }
 
@@ -1364,6 +1904,36 @@ hipError_t launch_blend(bool f16, bool final_level, const BlendItem* items_dev, 
     else STITCH_BLEND(float, false);
   }
 #undef STITCH_BLEND
+  return hipGetLastError();
+}
+
+hipError_t launch_tail(bool f16, const TailItem* items_dev, int nitems, int total_tiles, int nslot, hipStream_t s,
+                       const TailItem* one) {
+  if (total_tiles <= 0 || nslot <= 0) return hipSuccess;
+  const dim3 grid(total_tiles * nslot), block(kThreads);
+  TailItem k1;
+  if (one) k1 = *one;
+  else std::memset(&k1, 0, sizeof k1);
+#define STITCH_TAIL(TT)                                                                                  \
+  do {                                                                                                   \
+    if (one) hipLaunchKernelGGL((k_tail<TT, true>), grid, block, 0, s, items_dev, nitems, k1, nslot);    \
+    else hipLaunchKernelGGL((k_tail<TT, false>), grid, block, 0, s, items_dev, nitems, k1, nslot);       \
+  } while (0)
+  if (f16) STITCH_TAIL(_Float16);
+  else STITCH_TAIL(float);
+#undef STITCH_TAIL
+  return hipGetLastError();
+}
+
+hipError_t launch_blend_tail(bool f16, bool final_level, const BlendTailItem& item, const PanoArg& po, hipStream_t s) {
+  const dim3 grid(item.lev[0].tiles_x * item.lev[0].tiles_y), block(kBtThreads);
+  if (f16) {
+    if (final_level) hipLaunchKernelGGL((k_blend_tail<_Float16, true>), grid, block, 0, s, item, po);
+    else hipLaunchKernelGGL((k_blend_tail<_Float16, false>), grid, block, 0, s, item, po);
+  } else {
+    if (final_level) hipLaunchKernelGGL((k_blend_tail<float, true>), grid, block, 0, s, item, po);
+    else hipLaunchKernelGGL((k_blend_tail<float, false>), grid, block, 0, s, item, po);
+  }
   return hipGetLastError();
 }
 

@@ -305,6 +305,13 @@ struct stitch_plan {
   size_t off_bcams[kMaxLevels] = {};
   std::vector<BlendItem> bitems;            // one per level
   size_t off_bitems = 0;
+  // the small levels in one launch each way: pyramid passes from level tail_k on, blends from
+  // level btail_k up (-1: none)
+  int tail_k = -1, btail_k = -1;
+  std::vector<TailItem> tail;
+  int tail_tiles = 0;
+  size_t off_tail = 0;
+  BlendTailItem btail;
   size_t ws_bytes = 0;
   uint8_t* ws = nullptr;
   EventLog timing;   // optional per-launch event timing (diagnostics)
@@ -431,6 +438,78 @@ void set_sub(std::vector<PyrItem>& items, int sub, int& tiles) {
   }
 }
 
+// Where a camera's band and weights meet on the level's W x H canvas; all zero when they don't.
+void set_visible(BlendCam& c, int W, int H) {
+  const int64_t x0 = std::max<int64_t>({0, c.lx, c.wx}), y0 = std::max<int64_t>({0, c.ly, c.wy});
+  const int64_t x1 = std::min<int64_t>({W, (int64_t)c.lx + c.lw, (int64_t)c.wx + c.ww});
+  const int64_t y1 = std::min<int64_t>({H, (int64_t)c.ly + c.lh, (int64_t)c.wy + c.wh});
+  c.vx0 = c.vy0 = c.vx1 = c.vy1 = 0;
+  if (x0 >= x1 || y0 >= y1) return;
+  c.vx0 = (int32_t)x0; c.vy0 = (int32_t)y0; c.vx1 = (int32_t)x1; c.vy1 = (int32_t)y1;
+}
+
+// Where the small levels' single launches begin.  A level pass or blend of a few hundred
+// workgroups costs its fixed 5-10 us; the single launch costs about as much once, plus its
+// tiles' halos: three and a half times the finest level's samples for a pyramid tail.  The
+// lines lie where that work reaches what the launches saved (four 1080p cameras, whole frame:
+// 194 us with both lines at 80 thousand, 183 at 300 to 400 thousand, 185 at a million; batches,
+// whose levels are larger together, at best gained 2% from the blends' and lost up to 5% to
+// the pyramids', and go level by level).
+constexpr int64_t kTailSamples = 400000;       // finest level's samples, all cameras
+constexpr int64_t kBlendTailPixels = 1200000;  // finest level's canvas
+
+// First level >= k_min of a tail over levels .. L-1 whose size (given per level) is within
+// `limit` and which covers at least `least` steps; -1: none.
+int tail_start(int L, const int64_t* size, int k_min, int least, int64_t limit) {
+  for (int k = std::max(k_min, L - 1 - kTailDepth); k <= L - 1 - least; ++k)
+    if (size[k] <= limit) return k;
+  return -1;
+}
+
+// The tail of one camera from level k0 to the top, from its level passes' items.
+TailItem tail_item(const std::vector<PyrItem>* items, int k0, int depth, size_t q) {
+  TailItem t;
+  std::memset(&t, 0, sizeof t);
+  const PyrItem& f = items[k0][q];
+  t.tiles_x = (f.roi_w + kTailTX - 1) / kTailTX;
+  t.depth = depth;
+  t.nch = f.nch;
+  t.tile_x0 = f.tile_x0;
+  t.tile_y0 = f.tile_y0;
+  t.padded = 1;
+  t.img = f.img; t.img_row = f.img_row; t.img_plane = f.img_plane;
+  t.msk = f.msk; t.msk_row = f.msk_row;
+  for (int d = 0; d < depth; ++d) {
+    const PyrItem& it = items[k0 + d][q];
+    TailLevel& l = t.lev[d];
+    l.w = it.fine_w; l.h = it.fine_h;
+    l.roi_x = it.roi_x; l.roi_y = it.roi_y; l.roi_w = it.roi_w; l.roi_h = it.roi_h;
+    l.croi_x = it.croi_x; l.croi_y = it.croi_y; l.croi_w = it.croi_w; l.croi_h = it.croi_h;
+    l.g_out = it.g_out; l.g_row = it.g_row; l.g_plane = it.g_plane;
+    l.gm_out = it.gm_out; l.gm_row = it.gm_row;
+    l.lw_x = it.lw_x; l.lw_y = it.lw_y; l.lw_w = it.lw_w; l.lw_h = it.lw_h;
+    l.l_out = it.l_out; l.l_row = it.l_row; l.l_plane = it.l_plane;
+  }
+  return t;
+}
+
+// Append a tail to a table, its tiles numbered after those before it.
+void push_tail(std::vector<TailItem>& table, int& tiles, TailItem t) {
+  t.tile_begin = tiles;
+  tiles += t.tiles_x * ((t.lev[0].roi_h + kTailTY - 1) / kTailTY);
+  table.push_back(t);
+}
+
+// The collapse tail of a panorama from level k0 to its top.
+BlendTailItem blend_tail_item(const std::vector<BlendItem>& items, int k0, int L) {
+  BlendTailItem t;
+  std::memset(&t, 0, sizeof t);
+  t.tiles_x = items[k0].tiles_x;
+  t.depth = L - 1 - k0;
+  for (int k = k0; k < L; ++k) t.lev[k - k0] = items[k];
+  return t;
+}
+
 // Fill the pyramid-pass and blend tables of a plan whose workspace base is ws.
 void build_tables(stitch_plan* p) {
   uint8_t* ws = p->ws;
@@ -515,6 +594,7 @@ void build_tables(stitch_plan* p) {
       }
       const Rect r = c.roi[k];
       bc.wx = r.x; bc.wy = r.y; bc.ww = r.w; bc.wh = r.h;
+      set_visible(bc, p->dw[k], p->dh[k]);
       if (k == 0) {
         bc.wgt = ws + c.off_mask0;
         bc.wgt_row = c.mask_row;
@@ -550,6 +630,19 @@ void build_tables(stitch_plan* p) {
       bi.rout_plane = p->r_plane[k];
     }
   }
+  int64_t samples[kMaxLevels] = {}, canvas[kMaxLevels] = {};
+  for (int k = 0; k < L; ++k) {
+    for (const CamPlan& c : p->cam) samples[k] += (int64_t)c.roi[k].w * c.roi[k].h;
+    canvas[k] = (int64_t)p->dw[k] * p->dh[k];
+  }
+  p->tail.clear();
+  p->tail_tiles = 0;
+  p->tail_k = tail_start(L, samples, 1, 2, kTailSamples);
+  if (p->tail_k >= 0)
+    for (size_t q = 0; q < p->items[p->tail_k].size(); ++q)
+      push_tail(p->tail, p->tail_tiles, tail_item(p->items, p->tail_k, L - 1 - p->tail_k, q));
+  p->btail_k = L > 1 ? tail_start(L, canvas, 0, 1, kBlendTailPixels) : -1;
+  if (p->btail_k >= 0) p->btail = blend_tail_item(p->bitems, p->btail_k, L);
 }
 
 // Check a frame set against the plan and collect its pointers for the level-0 pass.
@@ -815,6 +908,7 @@ stitch_status stitch_blend(int32_t n, const stitch_levels* bands, const stitch_l
       bc.wgt_u8 = w.dtype == STITCH_U8;
       bc.wgt_row = w.row_pitch / elem_size(w.dtype);
       bc.wx = weights[i].origin_x[k]; bc.wy = weights[i].origin_y[k]; bc.ww = w.width; bc.wh = w.height;
+      set_visible(bc, dw[k], dh[k]);
     }
   const hipStream_t s = (hipStream_t)stream;
   const BlendCam* dev = (const BlendCam*)workspace;
@@ -1073,6 +1167,7 @@ stitch_status stitch_plan_create(int32_t n, const int32_t* frame_w, const int32_
   for (int k = 0; k + 1 < L; ++k) p->off_items[k] = lay.take((size_t)n * sizeof(PyrItem));
   for (int k = 0; k < L; ++k) p->off_bcams[k] = lay.take((size_t)n * sizeof(BlendCam));
   p->off_bitems = lay.take((size_t)L * sizeof(BlendItem));
+  p->off_tail = lay.take((size_t)n * sizeof(TailItem));
   for (int i = 0; i < n; ++i) {
     const CamPlan& c = p->cam[i];
     for (int k = 0; k < L; ++k) {
@@ -1121,6 +1216,7 @@ stitch_status stitch_plan_bind(stitch_plan* p, void* workspace, size_t bytes, vo
                 "table upload");
   if (!st)
     st = upload(p->ws + p->off_bitems, p->bitems.data(), p->bitems.size() * sizeof(BlendItem), s, "table upload");
+  if (!st) st = upload(p->ws + p->off_tail, p->tail.data(), p->tail.size() * sizeof(TailItem), s, "table upload");
   if (!st) {
     const hipError_t e = hipStreamSynchronize(s);
     if (e != hipSuccess) st = hip_fail(e, "bind synchronise");
@@ -1161,18 +1257,30 @@ stitch_status stitch_frame(stitch_plan* p, const stitch_image* frames, stitch_im
       if ((st = mark(6))) return st;
     }
   }
-  for (int k = 0; k + 1 < L; ++k) {
+  for (int k = 0; k + 1 < L && k != p->tail_k; ++k) {
     if (p->tiles[k] <= 0) continue;
     e = launch_pyr(f16, true, k == 0, (const PyrItem*)(p->ws + p->off_items[k]), (int)p->items[k].size(),
                    p->tiles[k], fa, s, p->wg_cap[k]);
     if (e != hipSuccess) return hip_fail(e, "pyramid pass launch");
     if ((st = mark(k == 0 ? 0 : 1))) return st;
   }
-  for (int k = L - 1; k >= 0; --k) {
+  if (p->tail_k >= 0 && p->tail_tiles > 0) {
+    e = launch_tail(f16, (const TailItem*)(p->ws + p->off_tail), (int)p->tail.size(), p->tail_tiles, 4, s);
+    if (e != hipSuccess) return hip_fail(e, "pyramid tail launch");
+    if ((st = mark(1))) return st;
+  }
+  const PanoArg po{(uint8_t*)pano->data, pano->row_pitch};
+  int k_top = L - 1;
+  if (p->btail_k >= 0) {
+    e = launch_blend_tail(f16, p->btail_k == 0, p->btail, p->btail_k == 0 ? po : PanoArg{nullptr, 0}, s);
+    if (e != hipSuccess) return hip_fail(e, "blend tail launch");
+    if ((st = mark(p->btail_k == 0 ? 2 : 4))) return st;
+    k_top = p->btail_k - 1;
+  }
+  for (int k = k_top; k >= 0; --k) {
     const BlendItem& bi = p->bitems[k];
-    PanoArg po{nullptr, 0};
-    if (k == 0) { po.ptr = (uint8_t*)pano->data; po.row = pano->row_pitch; }
-    e = launch_blend(f16, k == 0, nullptr, 1, bi.tiles_x * bi.tiles_y, po, s, &bi);
+    const PanoArg pk = k == 0 ? po : PanoArg{nullptr, 0};
+    e = launch_blend(f16, k == 0, nullptr, 1, bi.tiles_x * bi.tiles_y, pk, s, &bi);
     if (e != hipSuccess) return hip_fail(e, "blend launch");
     const int kind = k == 0 ? (L > 1 ? 2 : 5) : (k + 1 < L ? 3 : 4);
     if ((st = mark(kind))) return st;

@@ -64,6 +64,7 @@ struct BlendCam {
   const void* wgt; int64_t wgt_row;               // weights: storage type or u8
   int32_t wgt_u8, pad;
   int32_t wx, wy, ww, wh;                         // weight rectangle
+  int32_t vx0, vy0, vx1, vy1;                     // where both are (half open; the blend tail's tests)
 };
 
 // One canvas level of one stitch job in a blend launch; a launch covers the tiles of
@@ -77,6 +78,35 @@ struct BlendItem {
   const void* r_in; int64_t rin_row, rin_plane;    // R_{k+1} (storage type)
   void* r_out; int64_t rout_row, rout_plane;       // R_k (storage type) or nullptr
   uint8_t* pano; int64_t pano_row;                 // U8 HWC (level 0) or nullptr
+};
+
+// Several consecutive small levels in one launch (the tail of a pyramid): level k of a tail
+// is REDUCEd to k+1 and its band stored, from samples the workgroup holds itself.
+constexpr int kTailTX = 64, kTailTY = 32;   // tile of the tail's finest level
+constexpr int kTailDepth = 3;               // levels a tail reduces at most
+struct TailLevel {
+  int32_t w, h;                           // level-k canvas sides
+  int32_t roi_x, roi_y, roi_w, roi_h;     // level-k samples outside count 0
+  int32_t croi_x, croi_y, croi_w, croi_h; // stored rectangle of level k+1
+  void* g_out; int64_t g_row, g_plane;    // image planes (elements)
+  void* gm_out; int64_t gm_row;           // weight plane
+  int32_t lw_x, lw_y, lw_w, lw_h;         // band window of level k (w == 0: not stored)
+  void* l_out; int64_t l_row, l_plane;
+};
+struct TailItem {
+  int32_t tile_begin, tiles_x, depth, nch;
+  int32_t tile_x0, tile_y0;               // finest-level origin of tile (0,0), multiples of 8
+  int32_t src_u8;                         // the image source is bytes (read as u8/255)
+  int32_t padded;                         // source rows may be read in whole 16-byte chunks
+  const void* img; int64_t img_row, img_plane;   // finest-level image planes on lev[0].roi
+  const void* msk; int64_t msk_row;              // finest-level weight plane (slot nch)
+  void* copy_out; int64_t copy_row, copy_plane;  // NULL, or where the finest level is copied
+  TailLevel lev[kTailDepth];
+};
+// Collapse of the levels lev[depth] (the top) .. lev[0] of one panorama in one launch.
+struct BlendTailItem {
+  int32_t tiles_x, depth;
+  BlendItem lev[kTailDepth + 1];
 };
 
 // Launchers (kernels.hip).  f16 selects half-precision storage.
@@ -100,6 +130,11 @@ struct PanoArg {
 // one != nullptr: a single item passed by value (items_dev unused).
 hipError_t launch_blend(bool f16, bool final_level, const BlendItem* items_dev, int nitems, int total_tiles,
                         const PanoArg& po, hipStream_t s, const BlendItem* one = nullptr);
+// Tails: nslot planes per tile (image channels, then the weight plane); one != nullptr: a
+// single item passed by value.  final_level as for launch_blend (lev[0] is level 0).
+hipError_t launch_tail(bool f16, const TailItem* items_dev, int nitems, int total_tiles, int nslot, hipStream_t s,
+                       const TailItem* one = nullptr);
+hipError_t launch_blend_tail(bool f16, bool final_level, const BlendTailItem& item, const PanoArg& po, hipStream_t s);
 hipError_t launch_warp(bool f16, const uint8_t* src, int64_t src_row, int w, int h, const float* hinv9,
                        int roi_x, int roi_y, void* dst, int64_t dst_row, int64_t dst_plane, int dw, int dh,
                        hipStream_t s);
