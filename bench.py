@@ -75,8 +75,8 @@ def parse():
 
 # rocprofv3 kernel names of the path -> the kinds this script reports
 KERNEL_KINDS = {
-    "k_pyr<float, true, true>": "warp_level0_pass (f32)", "k_pyr<float, true, false>": "level_pass (f32)",
-    "k_pyr<_Float16, true, true>": "warp_level0_pass (f16)", "k_pyr<_Float16, true, false>": "level_pass (f16)",
+    "k_pyr<float, true>": "warp_level0_pass (f32)", "k_pyr<float, false>": "level_pass (f32)",
+    "k_pyr<_Float16, true>": "warp_level0_pass (f16)", "k_pyr<_Float16, false>": "level_pass (f16)",
     "k_blend<float, true, true>": "blend_level0 (f32)", "k_blend<float, false, true>": "blend_middle/top (f32)",
     "k_blend<_Float16, true, true>": "blend_level0 (f16)", "k_blend<_Float16, false, true>": "blend_middle/top (f16)",
     "k_blend<float, true, false>": "blend_level0, batched (f32)",

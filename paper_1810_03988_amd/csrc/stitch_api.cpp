@@ -392,6 +392,17 @@ stitch_status stitch::check_image(const stitch_image* im, const char* name, int 
 
 namespace {
 
+// Whether two images share memory.
+bool overlap(const stitch_image& a, const stitch_image& b) {
+  auto bytes = [](const stitch_image& im) {
+    const int64_t es = elem_size(im.dtype), ch = im.layout == STITCH_HWC ? 1 : im.channels;
+    return (ch - 1) * im.plane_pitch + (im.height - 1) * im.row_pitch +
+           (int64_t)im.width * es * (im.layout == STITCH_HWC ? im.channels : 1);
+  };
+  const uintptr_t a0 = (uintptr_t)a.data, b0 = (uintptr_t)b.data;
+  return a0 < b0 + (uintptr_t)bytes(b) && b0 < a0 + (uintptr_t)bytes(a);
+}
+
 stitch_status check_levels_dims(int W, int H, int L, int dw[], int dh[]) {
   if (L < 1 || L > kMaxLevels) return fail(STITCH_E_LEVELS, "levels %d outside 1..%d", L, kMaxLevels);
   if (W <= 0 || H <= 0) return fail(STITCH_E_SHAPE, "canvas %dx%d is empty", W, H);
@@ -458,6 +469,11 @@ void set_visible(BlendCam& c, int W, int H) {
 constexpr int64_t kTailSamples = 400000;       // finest level's samples, all cameras
 constexpr int64_t kBlendTailPixels = 1200000;  // finest level's canvas
 
+// stitch_pyramid: a level of more samples (of all channels) than this is reduced in a launch of its
+// own, with a single level's halo.  Three 1080p cameras' pyramids, FP16, of 6.2 million samples an
+// image and 2.1 a weight map: line below both 391-420 us, between them 371, above both 392.
+constexpr int64_t kStageSamples = 3000000;
+
 // First level >= k_min of a tail over levels .. L-1 whose size (given per level) is within
 // `limit` and which covers at least `least` steps; -1: none.
 int tail_start(int L, const int64_t* size, int k_min, int least, int64_t limit) {
@@ -476,7 +492,6 @@ TailItem tail_item(const std::vector<PyrItem>* items, int k0, int depth, size_t 
   t.nch = f.nch;
   t.tile_x0 = f.tile_x0;
   t.tile_y0 = f.tile_y0;
-  t.padded = 1;
   t.img = f.img; t.img_row = f.img_row; t.img_plane = f.img_plane;
   t.msk = f.msk; t.msk_row = f.msk_row;
   for (int d = 0; d < depth; ++d) {
@@ -767,68 +782,80 @@ stitch_status stitch_pyramid(const stitch_image* g0, int32_t kind, stitch_levels
                 stitch_pyramid_workspace_bytes(L));
   const hipStream_t s = (hipStream_t)stream;
   const bool f16 = odt == STITCH_F16;
-  const int es = elem_size(odt);
-  const stitch_image& l0 = out->level[0];
-  hipError_t e = hipSuccess;
-  if (g0->data != l0.data || u8) {
-    e = launch_convert(f16, nch, u8, g0->data, g0->row_pitch / elem_size(g0->dtype),
-                       g0->plane_pitch / elem_size(g0->dtype), l0.data, l0.row_pitch / es, l0.plane_pitch / es,
-                       l0.width, l0.height, s);
-    if (e != hipSuccess) return hip_fail(e, "convert launch");
+  const int es = elem_size(odt), ges = elem_size(g0->dtype);
+  auto planes = [es](const stitch_image& im) { return Planes{im.data, im.row_pitch / es, im.plane_pitch / es}; };
+  // Buffers that overlap are taken in the order of the levels, one launch each (a deeper launch
+  // reads its source while it writes the levels above it).
+  bool apart = true;
+  for (int k = 0; k < L; ++k) {
+    if (k > 0 && overlap(*g0, out->level[k])) apart = false;
+    for (int j = 0; j < k; ++j)
+      if (overlap(out->level[j], out->level[k])) apart = false;
   }
-  if (L == 1) return STITCH_OK;
-  std::vector<PyrItem> items(L - 1);
-  std::vector<int> tiles(L - 1);
-  for (int k = 0; k + 1 < L; ++k) {
+  // Gaussian chain: each launch reduces from level k by one to three levels; the first reads g0
+  // itself and, where level 0 is wanted as it is or converted, copies it on the way.
+  bool alias0 = !u8 && g0->data == out->level[0].data;            // level 0 is G_0 already
+  const bool from_g0 = kind == 1 && L > 1 && !u8 && !alias0 && apart;      // L_0 is then formed from g0
+  hipError_t e = hipSuccess;
+  for (int k = 0; k == 0 || k + 1 < L;) {
+    const stitch_image& f = out->level[k];
+    const bool src0 = k == 0 && !alias0;
+    int depth = std::min(kTailDepth, L - 1 - k);
+    if (!apart) depth = src0 ? 0 : std::min(depth, 1);
+    else if ((int64_t)f.width * f.height * nch > kStageSamples) depth = std::min(depth, 1);
+    TailItem t;
+    std::memset(&t, 0, sizeof t);
+    t.depth = depth;
+    t.nch = nch;
+    t.src_u8 = src0 && u8;
+    t.img = src0 ? g0->data : f.data;
+    t.img_row = src0 ? g0->row_pitch / ges : f.row_pitch / es;
+    t.img_plane = src0 ? g0->plane_pitch / ges : f.plane_pitch / es;
+    if (src0 && !from_g0) {
+      t.copy_out = f.data; t.copy_row = f.row_pitch / es; t.copy_plane = f.plane_pitch / es;
+    }
+    // tiles cover every level's rectangle
+    int64_t x0 = out->origin_x[k], y0 = out->origin_y[k], x1 = x0 + f.width, y1 = y0 + f.height;
+    TailLevel& l0 = t.lev[0];
+    l0.w = dw[k]; l0.h = dh[k];
+    l0.roi_x = out->origin_x[k]; l0.roi_y = out->origin_y[k]; l0.roi_w = f.width; l0.roi_h = f.height;
+    for (int d = 0; d < depth; ++d) {
+      const stitch_image& c = out->level[k + d + 1];
+      const int cx = out->origin_x[k + d + 1], cy = out->origin_y[k + d + 1];
+      TailLevel& l = t.lev[d];
+      l.croi_x = cx; l.croi_y = cy; l.croi_w = c.width; l.croi_h = c.height;
+      l.g_out = c.data;
+      l.g_row = c.row_pitch / es;
+      l.g_plane = c.plane_pitch / es;
+      if (d + 1 < depth) {
+        TailLevel& n = t.lev[d + 1];
+        n.w = dw[k + d + 1]; n.h = dh[k + d + 1];
+        n.roi_x = cx; n.roi_y = cy; n.roi_w = c.width; n.roi_h = c.height;
+      }
+      x0 = std::min<int64_t>(x0, (int64_t)cx << (d + 1));
+      y0 = std::min<int64_t>(y0, (int64_t)cy << (d + 1));
+      x1 = std::max<int64_t>(x1, (int64_t)(cx + c.width) << (d + 1));
+      y1 = std::max<int64_t>(y1, (int64_t)(cy + c.height) << (d + 1));
+    }
+    t.tile_x0 = (int)(x0 & ~(int64_t)7);
+    t.tile_y0 = (int)(y0 & ~(int64_t)7);
+    t.tiles_x = (int)((x1 - t.tile_x0 + kTailTX - 1) / kTailTX);
+    const int tiles_y = (int)((y1 - t.tile_y0 + kTailTY - 1) / kTailTY);
+    if (depth > 0 || t.copy_out) {
+      e = launch_tail(f16, nullptr, 1, t.tiles_x * tiles_y, nch, s, &t);
+      if (e != hipSuccess) return hip_fail(e, "pyramid launch");
+    }
+    if (depth > 0) k += depth;
+    else if (L == 1) break;
+    alias0 = true;
+  }
+  for (int k = 0; kind == 1 && k + 1 < L; ++k) {
     const stitch_image& f = out->level[k];
     const stitch_image& c = out->level[k + 1];
-    PyrItem it;
-    std::memset(&it, 0, sizeof it);
-    const int fx = out->origin_x[k], fy = out->origin_y[k];
-    const int cx = out->origin_x[k + 1], cy = out->origin_y[k + 1];
-    // tiles cover the level-k rectangle and every fine sample under the level-(k+1) rectangle
-    const int x0 = std::min(fx, 2 * cx) & ~1, y0 = std::min(fy, 2 * cy) & ~1;
-    const int x1 = std::max(fx + f.width, 2 * (cx + c.width)), y1 = std::max(fy + f.height, 2 * (cy + c.height));
-    it.tiles_x = (x1 - x0 + kPyrTX - 1) / kPyrTX;
-    it.tiles_y = (y1 - y0 + kPyrTY - 1) / kPyrTY;
-    it.rows16 = it.tiles_y;
-    it.sub = 1;
-    it.tile_x0 = x0;
-    it.tile_y0 = y0;
-    it.fine_w = dw[k];
-    it.fine_h = dh[k];
-    it.roi_x = fx; it.roi_y = fy; it.roi_w = f.width; it.roi_h = f.height;
-    it.img_kind = kSrcPlanes;
-    it.nch = nch;
-    it.img = f.data;
-    it.img_row = f.row_pitch / es;
-    it.img_plane = f.plane_pitch / es;
-    it.msk_kind = kSrcNone;
-    it.croi_x = cx; it.croi_y = cy; it.croi_w = c.width; it.croi_h = c.height;
-    it.g_out = c.data;
-    it.g_row = c.row_pitch / es;
-    it.g_plane = c.plane_pitch / es;
-    items[k] = it;
-    tiles[k] = it.tiles_x * it.tiles_y;
-  }
-  st = upload(workspace, items.data(), items.size() * sizeof(PyrItem), s, "pyramid table upload");
-  if (st) return st;
-  FrameArgs fa;
-  std::memset(&fa, 0, sizeof fa);
-  const PyrItem* dev = (const PyrItem*)workspace;
-  for (int k = 0; k + 1 < L; ++k) {
-    e = launch_pyr(f16, false, false, dev + k, 1, tiles[k], fa, s);
-    if (e != hipSuccess) return hip_fail(e, "pyramid launch");
-  }
-  if (kind == 1) {
-    for (int k = 0; k + 1 < L; ++k) {
-      const stitch_image& f = out->level[k];
-      const stitch_image& c = out->level[k + 1];
-      e = launch_expand_sub(f16, nch, f.data, f.row_pitch / es, f.plane_pitch / es, out->origin_x[k],
-                            out->origin_y[k], f.width, f.height, c.data, c.row_pitch / es, c.plane_pitch / es,
-                            out->origin_x[k + 1], out->origin_y[k + 1], c.width, c.height, dw[k], dh[k], s);
-      if (e != hipSuccess) return hip_fail(e, "expand launch");
-    }
+    const Planes src = k == 0 && from_g0 ? planes(*g0) : planes(f);
+    e = launch_expand_sub(f16, nch, src, planes(f), out->origin_x[k], out->origin_y[k], f.width, f.height, planes(c),
+                          out->origin_x[k + 1], out->origin_y[k + 1], c.width, c.height, dw[k], dh[k], s);
+    if (e != hipSuccess) return hip_fail(e, "expand launch");
   }
   return STITCH_OK;
 }
@@ -912,7 +939,6 @@ stitch_status stitch_blend(int32_t n, const stitch_levels* bands, const stitch_l
     }
   const hipStream_t s = (hipStream_t)stream;
   const BlendCam* dev = (const BlendCam*)workspace;
-  const size_t items_off = (size_t)align_up((int64_t)tab.size() * (int64_t)sizeof(BlendCam), 256);
   std::vector<BlendItem> items(L);
   for (int k = 0; k < L; ++k) {
     BlendItem& a = items[k];
@@ -936,11 +962,33 @@ stitch_status stitch_blend(int32_t n, const stitch_levels* bands, const stitch_l
   }
   st = upload(workspace, tab.data(), tab.size() * sizeof(BlendCam), s, "blend table upload");
   if (st) return st;
-  st = upload((uint8_t*)workspace + items_off, items.data(), items.size() * sizeof(BlendItem), s, "blend table upload");
-  if (st) return st;
-  const BlendItem* idev = (const BlendItem*)((uint8_t*)workspace + items_off);
-  for (int k = L - 1; k >= 0; --k) {
-    const hipError_t e = launch_blend(dt == STITCH_F16, k == 0, idev + k, 1, items[k].tiles_x * items[k].tiles_y,
+  // The small levels in one launch, where nothing it writes shares memory with what it reads.
+  int64_t canvas[kMaxLevels];
+  for (int k = 0; k < L; ++k) canvas[k] = (int64_t)dw[k] * dh[k];
+  int k_tail = L > 1 ? tail_start(L, canvas, 0, 1, kBlendTailPixels) : -1;
+  for (int k = k_tail; k_tail >= 0 && k < L; ++k) {
+    if (!items[k].r_out) continue;
+    const stitch_image& r = keep_r->level[k];
+    for (int j = std::max(k_tail, 0); k_tail >= 0 && j < L; ++j) {
+      if (j < k && items[j].r_out && overlap(r, keep_r->level[j])) k_tail = -1;
+      for (int i = 0; k_tail >= 0 && i < n; ++i)
+        if (overlap(r, bands[i].level[j]) || overlap(r, weights[i].level[j])) k_tail = -1;
+    }
+  }
+  for (int j = 0; k_tail == 0 && j < L; ++j) {
+    if (items[j].r_out && overlap(*pano, keep_r->level[j])) k_tail = -1;
+    for (int i = 0; k_tail == 0 && i < n; ++i)
+      if (overlap(*pano, bands[i].level[j]) || overlap(*pano, weights[i].level[j])) k_tail = -1;
+  }
+  int k_top = L - 1;
+  if (k_tail >= 0) {
+    const hipError_t e = launch_blend_tail(dt == STITCH_F16, k_tail == 0, blend_tail_item(items, k_tail, L),
+                                           PanoArg{nullptr, 0}, s);
+    if (e != hipSuccess) return hip_fail(e, "blend launch");
+    k_top = k_tail - 1;
+  }
+  for (int k = k_top; k >= 0; --k) {
+    const hipError_t e = launch_blend(dt == STITCH_F16, k == 0, nullptr, 1, items[k].tiles_x * items[k].tiles_y,
                                       PanoArg{nullptr, 0}, s, &items[k]);
     if (e != hipSuccess) return hip_fail(e, "blend launch");
   }
@@ -1259,7 +1307,7 @@ stitch_status stitch_frame(stitch_plan* p, const stitch_image* frames, stitch_im
   }
   for (int k = 0; k + 1 < L && k != p->tail_k; ++k) {
     if (p->tiles[k] <= 0) continue;
-    e = launch_pyr(f16, true, k == 0, (const PyrItem*)(p->ws + p->off_items[k]), (int)p->items[k].size(),
+    e = launch_pyr(f16, k == 0, (const PyrItem*)(p->ws + p->off_items[k]), (int)p->items[k].size(),
                    p->tiles[k], fa, s, p->wg_cap[k]);
     if (e != hipSuccess) return hip_fail(e, "pyramid pass launch");
     if ((st = mark(k == 0 ? 0 : 1))) return st;
@@ -1445,7 +1493,7 @@ stitch_status enqueue_phases(stitch_batch* b, hipStream_t s, int k_first, int k_
   stitch_status st = STITCH_OK;
   for (int k = k_first; !st && k < k_end && k + 1 < b->maxL; ++k) {
     if (b->pyr_tiles[k] <= 0) continue;
-    const hipError_t e = launch_pyr(b->f16, true, k == 0, (const PyrItem*)(b->ws + b->off_pyr[k]),
+    const hipError_t e = launch_pyr(b->f16, k == 0, (const PyrItem*)(b->ws + b->off_pyr[k]),
                                     (int)b->pyr[k].size(), b->pyr_tiles[k], fa, s, b->wg_cap[k]);
     if (e != hipSuccess) return hip_fail(e, "batch pyramid launch");
     st = b->timing.mark(s, k);
@@ -1686,7 +1734,7 @@ stitch_status tune_passes(int np, PassTune* passes, bool f16, const FrameArgs& f
         for (int rep = 0; rep < 6 && !st; ++rep) {
           hipError_t e = hipEventRecord(e0, s);
           if (e == hipSuccess)
-            e = launch_pyr(f16, true, pt.warp, (const PyrItem*)pt.dev_table, (int)pt.items->size(), *pt.tiles, fa,
+            e = launch_pyr(f16, pt.warp, (const PyrItem*)pt.dev_table, (int)pt.items->size(), *pt.tiles, fa,
                            s, c);
           if (e == hipSuccess) e = hipEventRecord(e1, s);
           if (e == hipSuccess) e = hipEventSynchronize(e1);

@@ -97,7 +97,7 @@ struct TailItem {
   int32_t tile_begin, tiles_x, depth, nch;
   int32_t tile_x0, tile_y0;               // finest-level origin of tile (0,0), multiples of 8
   int32_t src_u8;                         // the image source is bytes (read as u8/255)
-  int32_t padded;                         // source rows may be read in whole 16-byte chunks
+  int32_t pad;
   const void* img; int64_t img_row, img_plane;   // finest-level image planes on lev[0].roi
   const void* msk; int64_t msk_row;              // finest-level weight plane (slot nch)
   void* copy_out; int64_t copy_row, copy_plane;  // NULL, or where the finest level is copied
@@ -110,9 +110,9 @@ struct BlendTailItem {
 };
 
 // Launchers (kernels.hip).  f16 selects half-precision storage.
-// warp: level-0 pass whose image source is the homography warp (always emits L_0).
+// warp: level-0 pass whose image source is the homography warp.
 // wg_per_cu: persistent workgroups per compute unit (0: as many as fit, < 0: one per tile).
-hipError_t launch_pyr(bool f16, bool emit_lap, bool warp, const PyrItem* items_dev, int nitems, int total_tiles,
+hipError_t launch_pyr(bool f16, bool warp, const PyrItem* items_dev, int nitems, int total_tiles,
                       const FrameArgs& frames, hipStream_t s, int wg_per_cu = 0);
 // Runs the occupancy queries the launchers cache, so later launches (e.g. inside a stream
 // capture) make no device queries.
@@ -140,11 +140,15 @@ hipError_t launch_warp(bool f16, const uint8_t* src, int64_t src_row, int w, int
                        hipStream_t s);
 hipError_t launch_warp_coords(const float* hinv9, int roi_x, int roi_y, float* dst, int64_t row,
                               int64_t plane, int dw, int dh, hipStream_t s);
-hipError_t launch_expand_sub(bool f16, int nch, void* fine, int64_t f_row, int64_t f_plane, int fx, int fy,
-                             int fw, int fh, const void* coarse, int64_t c_row, int64_t c_plane, int cx,
-                             int cy, int cw, int ch, int canvas_w, int canvas_h, hipStream_t s);
-hipError_t launch_convert(bool f16_out, int nch, bool src_u8, const void* src, int64_t s_row, int64_t s_plane,
-                          void* dst, int64_t d_row, int64_t d_plane, int w, int h, hipStream_t s);
+// Planes of one image in the storage type: data, row and plane strides in elements.
+struct Planes {
+  void* data;
+  int64_t row, plane;
+};
+// out = fine - EXPAND(coarse), out's rectangle being fine's (out may be fine).
+hipError_t launch_expand_sub(bool f16, int nch, const Planes& fine, const Planes& out, int fx, int fy, int fw, int fh,
+                             const Planes& coarse, int cx, int cy, int cw, int ch, int canvas_w, int canvas_h,
+                             hipStream_t s);
 
 // Geometry of a plan for the other host files: cameras, their frame sizes (arrays of at
 // least kMaxCameras), the canvas, and whether a workspace is bound.
