@@ -72,7 +72,11 @@ __global__ void __launch_bounds__(256) k_lsh_keys(const uint32_t* __restrict__ d
   lsh_keys_body(desc, count, cap, P, keys, blockIdx.x);
 }
 
-// one wave per query: lanes stride over the reference points, then a (distance, index) min
+// One wave per query: lanes stride over the reference points, then a (distance, index) min.
+// Bound by the trips to memory: a lane reads the keys of eight tables for two reference points
+// at once, and a candidate's descriptor 32 bytes at a time.  (Key by key with an exit at the
+// first hit, every read waited for the one before: three pairs of 500 points, six tables,
+// 21 us; now 10 us.)
 __device__ __forceinline__ void lsh_match_body(const uint32_t* __restrict__ desc_a,
                                                const int32_t* __restrict__ count_a, int cap_a,
                                                const uint32_t* __restrict__ desc_b,
@@ -81,7 +85,7 @@ __device__ __forceinline__ void lsh_match_body(const uint32_t* __restrict__ desc
                                                const uint32_t* __restrict__ keys_b, int max_dist,
                                                int32_t* __restrict__ match, int32_t* __restrict__ dist, int bx) {
   const int lane = threadIdx.x & 63;
-  const int i = bx * 4 + (threadIdx.x >> 6);
+  const int i = bx * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   if (i >= cap_a) return;                           // whole waves leave; no block barrier below
   const int na = min(*count_a, cap_a), nb = min(*count_b, cap_b);
   if (i >= na) {
@@ -91,23 +95,46 @@ __device__ __forceinline__ void lsh_match_body(const uint32_t* __restrict__ desc
     }
     return;
   }
-  const int W2 = 2 * P.words;
-  uint32_t ka[kMaxTables];
-  for (int l = 0; l < P.tables; ++l) ka[l] = keys_a[(int64_t)l * cap_a + i];
-  const uint32_t* da = desc_a + (int64_t)i * W2;
+  const int words = P.words, tables = P.tables;
+  const uint2* da = reinterpret_cast<const uint2*>(desc_a + (int64_t)i * 2 * words);
   unsigned long long best = ~0ull;                  // (distance << 32) | index
-  for (int j = lane; j < nb; j += 64) {
-    bool cand = false;
-    for (int l = 0; l < P.tables && !cand; ++l) cand = __popc(ka[l] ^ keys_b[(int64_t)l * cap_b + j]) <= 1;
-    if (!cand) continue;
-    const uint32_t* db = desc_b + (int64_t)j * W2;
-    int d = 0;
-    for (int w = 0; w < W2; w += 2) {                 // rows hold an even number of words
-      const uint2 x = *reinterpret_cast<const uint2*>(da + w), y = *reinterpret_cast<const uint2*>(db + w);
-      d += __popc(x.x ^ y.x) + __popc(x.y ^ y.y);
+  for (int j0 = lane; j0 < nb; j0 += 128) {
+    const int jj[2] = {j0, min(j0 + 64, nb - 1)};   // (a repeated last point changes nothing)
+    bool cand[2] = {false, false};
+    for (int l0 = 0; l0 < tables; l0 += 8) {
+      uint32_t ka[8], kb[8][2];
+#pragma unroll
+      for (int l = 0; l < 8; ++l) {                 // (so does a repeated last table)
+        const int t = min(l0 + l, tables - 1);
+        ka[l] = keys_a[(int64_t)t * cap_a + i];
+        kb[l][0] = keys_b[(int64_t)t * cap_b + jj[0]];
+        kb[l][1] = keys_b[(int64_t)t * cap_b + jj[1]];
+      }
+#pragma unroll
+      for (int l = 0; l < 8; ++l) {
+        cand[0] |= __popc(ka[l] ^ kb[l][0]) <= 1;
+        cand[1] |= __popc(ka[l] ^ kb[l][1]) <= 1;
+      }
     }
-    const unsigned long long kd = ((unsigned long long)d << 32) | (uint32_t)j;
-    best = kd < best ? kd : best;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (!cand[h]) continue;
+      const uint2* db = reinterpret_cast<const uint2*>(desc_b + (int64_t)jj[h] * 2 * words);
+      int d = 0;
+      for (int w0 = 0; w0 < words; w0 += 4) {
+        uint2 y[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) y[w] = db[min(w0 + w, words - 1)];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const uint2 x = da[min(w0 + w, words - 1)];
+          const int pc = __popc(x.x ^ y[w].x) + __popc(x.y ^ y[w].y);
+          d += w0 + w < words ? pc : 0;
+        }
+      }
+      const unsigned long long kd = ((unsigned long long)d << 32) | (uint32_t)jj[h];
+      best = kd < best ? kd : best;
+    }
   }
   for (int o = 32; o > 0; o >>= 1) {
     const unsigned long long other = __shfl_xor(best, o);
@@ -152,11 +179,17 @@ template <typename D>
 struct PairArgs {
   D p[kArgPairs];
 };
+// A block's descriptor, by scalar reads: neither the argument segment nor the table is written
+// meanwhile.  (Through a pointer to either, every field was a read per lane.)
 template <typename D>
 __device__ __forceinline__ D pair_of(const D* __restrict__ table, const PairArgs<D>& args, int i) {
+  static_assert(sizeof(D) % 4 == 0, "whole dwords");
+  typedef const __attribute__((address_space(4))) uint32_t* ConstWords;
+  const ConstWords w = table ? (ConstWords)(table + i) : (ConstWords)(&args.p[0] + i);
   D q;
-  if (table) q = table[i];
-  else q = args.p[i];
+  uint32_t* d = reinterpret_cast<uint32_t*>(&q);
+#pragma unroll
+  for (int k = 0; k < (int)(sizeof(D) / 4); ++k) d[k] = w[k];
   return q;
 }
 
@@ -183,6 +216,92 @@ struct ProsacWs {            // offsets into the workspace
   size_t misc, qa, qb, qi, tp, hyp_h, hyp_ok;
 };
 
+// ---- moves within a wave (no LDS memory, no address registers) ----
+// Lane l's value, l the same in every lane.
+__device__ __forceinline__ double lane_of(double v, int l) {
+  const long long b = __builtin_bit_cast(long long, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)b, l);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(b >> 32), l);
+  return __builtin_bit_cast(double, (long long)(((unsigned long long)hi << 32) | lo));
+}
+// Value of lane ^ X for X = 1, 2, 8 (within a row of 16 lanes), 4, 16 (within 32) and 32.
+template <int X>
+__device__ __forceinline__ int swap32(int v) {
+  if (X == 1) return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);        // quad_perm 1 0 3 2
+  if (X == 2) return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);        // quad_perm 2 3 0 1
+  if (X == 8) return __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true);       // row_ror 8
+  if (X == 4) return __builtin_amdgcn_ds_swizzle(v, (4 << 10) | 0x1F);
+  if (X == 16) return __builtin_amdgcn_ds_swizzle(v, (16 << 10) | 0x1F);
+  return __shfl_xor(v, 32);
+}
+template <int X>
+__device__ __forceinline__ double swap64(double v) {
+  const long long b = __builtin_bit_cast(long long, v);
+  const uint32_t lo = (uint32_t)swap32<X>((int)b), hi = (uint32_t)swap32<X>((int)(b >> 32));
+  return __builtin_bit_cast(double, (long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// The growth function T'_n, n = 4 .. M, by one wave: T_{n+1} = T_n (n + 1) / (n - 3) in FP64, each
+// rounded, T' the sum of ceil(T_{n+1} - T_n) from 1.  The chain of T is serial; a step is one
+// product p and, in place of a division (some fifteen dependent operations), the quotient from the
+// divisor's reciprocal r and one correction: q0 = T c with c = (n + 1) r, beside p, then
+// q = q0 + (p - b q0) r.  That is the rounded quotient: q0 is within four of its last places, b
+// is a whole number below 2^16, so p - b q0 is exact (a multiple of q0's last place, at most
+// 2^19 of them), q's error before its rounding is below 2^-50 of a last place, and p / b lies
+// no closer than 1 / 2b of one to a midpoint between two doubles (it is none itself: b
+// times an odd 54-bit number has more than 53 bits).  Sixty-four steps' r and c come from the
+// wave's lanes, and their sums go out together: 500 matches took 37 us division by division,
+// the whole kernel now takes 19.
+__device__ __forceinline__ void prosac_growth(double T_N, int M, int64_t* __restrict__ tp) {
+  const int lane = threadIdx.x & 63;
+  double T = T_N;
+  for (int i = 0; i < kSample; ++i) T = T * (double)(kSample - i) / (double)(M - i);
+  if (lane == 0) tp[kSample] = 1;
+  if (!(T > 0x1p-900)) {                            // quotients too small for the correction
+    if (lane != 0) return;
+    for (int n = kSample; n < M; ++n) {
+      const double Tn = T * (double)(n + 1) / (double)(n + 1 - kSample);
+      tp[n + 1] = tp[n] + (int64_t)ceil(Tn - T);
+      T = Tn;
+    }
+    return;
+  }
+  __shared__ double sStep[64][4];                   // r, c, n + 1 and -b of 64 steps
+  __shared__ double sT[64];
+  auto settle = [] {                                // the wave's LDS writes before its reads
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  int64_t total = 1;
+  for (int n0 = kSample; n0 < M; n0 += 64) {
+    const double b = (double)(n0 + lane + 1 - kSample), up = (double)(n0 + lane + 1), r = 1.0 / b;
+    sStep[lane][0] = r;
+    sStep[lane][1] = up * r;
+    sStep[lane][2] = up;
+    sStep[lane][3] = -b;
+    settle();
+    const double first = T;
+#pragma unroll 16
+    for (int i = 0; i < 64; ++i) {                  // (steps past M end nowhere)
+      const double p = T * sStep[i][2], q0 = T * sStep[i][1];
+      T = __builtin_fma(__builtin_fma(sStep[i][3], q0, p), sStep[i][0], q0);
+      sT[i] = T;
+    }
+    settle();
+    const int steps = min(64, M - n0);
+    const double Tl = lane ? sT[(lane + 63) & 63] : first;
+    int64_t d = lane < steps ? (int64_t)ceil(sT[lane] - Tl) : 0;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int64_t e = __shfl_up(d, o);
+      if (lane >= o) d += e;
+    }
+    if (lane < steps) tp[n0 + lane + 1] = total + d;
+    total += __shfl(d, 63);
+    settle();
+  }
+}
+
 // misc: [0] M = number of matches
 // one block of 1024 threads: matches in quality order, and T'_n for n = 4 .. M
 __device__ __forceinline__ void prosac_prepare_body(const int32_t* __restrict__ pts_a,
@@ -196,60 +315,76 @@ __device__ __forceinline__ void prosac_prepare_body(const int32_t* __restrict__ 
   constexpr int kStage = 16384;                      // ranking keys staged in LDS up to here
   __shared__ int sM;
   __shared__ __attribute__((aligned(16))) int32_t sKey[kStage];
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int na = min(*count_a, cap_a);
   // ranking key of query j: its distance when it has a match (below INT32_MAX), else
   // INT32_MAX, which precedes nothing and equals no valid key
   auto key = [&](int j) -> int {
-    const int mj = match[j];
-    return (mj >= 0 && mj < cap_b) ? min(dist[j], INT32_MAX - 1) : INT32_MAX;
+    const int mj = match[j], dj = dist[j];
+    return (mj >= 0 && mj < cap_b) ? min(dj, INT32_MAX - 1) : INT32_MAX;
   };
   const bool staged = na <= kStage;
   const int npad = (na + 3) & ~3;
   if (tid == 0) sM = 0;
-  if (staged)
-    for (int j = tid; j < npad; j += 1024) sKey[j] = j < na ? key(j) : INT32_MAX;
   __syncthreads();
-  // number of valid matches
+  // the keys, and the number of valid matches
   int local = 0;
-  for (int i = tid; i < na; i += 1024) local += key(i) != INT32_MAX;
-  atomicAdd(&sM, local);
+  for (int j = tid; j < npad; j += 1024) {
+    const int k = j < na ? key(j) : INT32_MAX;
+    if (staged) sKey[j] = k;
+    local += k != INT32_MAX;
+  }
+  for (int o = 32; o > 0; o >>= 1) local += __shfl_xor(local, o);
+  if ((tid & 63) == 0) atomicAdd(&sM, local);
   __syncthreads();
   const int M = sM;
-  // the growth function, sequentially in FP64 in the order of its definition, on the last
-  // wave's last lane while the others rank the matches
-  if (tid == 1023 && M >= kSample) {
-    double T = T_N;
-    for (int i = 0; i < kSample; ++i) T = T * (double)(kSample - i) / (double)(M - i);
-    tp[kSample] = 1;
-    for (int n = kSample; n < M; ++n) {
-      const double Tn = T * (double)(n + 1) / (double)(n + 1 - kSample);
-      tp[n + 1] = tp[n] + (int64_t)ceil(Tn - T);
-      T = Tn;
-    }
+  // the growth function, on the last wave, ahead of its share of the ranking (the others go on)
+  if (wv == 15 && M >= kSample) {
+    __builtin_amdgcn_s_setprio(2);
+    prosac_growth(T_N, M, tp);
+    __builtin_amdgcn_s_setprio(0);
   }
   if (tid == 0) misc[0] = M;
-  // rank of match i: the valid matches ordered before it by (distance, query index)
+  // rank of match i: the valid matches ordered before it by (distance, query index): keys up
+  // to its own before it, keys below its own after it
   for (int i = tid; i < na; i += 1024) {
-    const int ki = key(i);
+    const int ki = staged ? sKey[i] : key(i);
     if (ki == INT32_MAX) continue;
     int r = 0;
     if (staged) {
-      for (int j = 0; j < npad; j += 4) {
+      const int mi = match[i];                       // on its way meanwhile
+      const int2 a = make_int2(pts_a[2 * i], pts_a[2 * i + 1]);
+      const int2 b = make_int2(pts_b[2 * mi], pts_b[2 * mi + 1]);
+      const int first = i & ~63, last = min(first + 64, npad);   // the wave's own matches
+      int j = 0;
+#pragma unroll 4
+      for (; j < first; j += 4) {
         const int4 v = *reinterpret_cast<const int4*>(&sKey[j]);
-        r += (v.x < ki || (v.x == ki && j < i)) + (v.y < ki || (v.y == ki && j + 1 < i)) +
-             (v.z < ki || (v.z == ki && j + 2 < i)) + (v.w < ki || (v.w == ki && j + 3 < i));
+        r += (v.x <= ki) + (v.y <= ki) + (v.z <= ki) + (v.w <= ki);
       }
+#pragma unroll 4
+      for (; j < last; j += 4) {
+        const int4 v = *reinterpret_cast<const int4*>(&sKey[j]);
+        r += (v.x < ki + (j < i)) + (v.y < ki + (j + 1 < i)) + (v.z < ki + (j + 2 < i)) + (v.w < ki + (j + 3 < i));
+      }
+#pragma unroll 4
+      for (; j < npad; j += 4) {
+        const int4 v = *reinterpret_cast<const int4*>(&sKey[j]);
+        r += (v.x < ki) + (v.y < ki) + (v.z < ki) + (v.w < ki);
+      }
+      qa[r] = a;
+      qb[r] = b;
+      qi[r] = i;
     } else {
       for (int j = 0; j < na; ++j) {
         const int kj = key(j);
         r += kj < ki || (kj == ki && j < i);
       }
+      const int mi = match[i];
+      qa[r] = make_int2(pts_a[2 * i], pts_a[2 * i + 1]);
+      qb[r] = make_int2(pts_b[2 * mi], pts_b[2 * mi + 1]);
+      qi[r] = i;
     }
-    const int mi = match[i];
-    qa[r] = make_int2(pts_a[2 * i], pts_a[2 * i + 1]);
-    qb[r] = make_int2(pts_b[2 * mi], pts_b[2 * mi + 1]);
-    qi[r] = i;
   }
 }
 
@@ -268,50 +403,56 @@ __device__ __forceinline__ bool collinear(int2 p, int2 q, int2 r) {
   return (int64_t)(q.x - p.x) * (r.y - p.y) - (int64_t)(q.y - p.y) * (r.x - p.x) == 0;
 }
 
-__device__ bool degenerate4(const int2* p) {
-  for (int a = 0; a < 4; ++a)
-    for (int b = a + 1; b < 4; ++b)
-      for (int c = b + 1; c < 4; ++c)
-        if (collinear(p[a], p[b], p[c])) return true;
-  return false;
+__device__ __forceinline__ bool degenerate4(const int2 (&p)[4]) {
+  return collinear(p[0], p[1], p[2]) | collinear(p[0], p[1], p[3]) | collinear(p[0], p[2], p[3]) |
+         collinear(p[1], p[2], p[3]);
 }
 
 // Solve the 8 x 8 system A x = b with one wave: lane l holds a = A[l / 8][l % 8] and bv =
 // b[l / 8].  Gaussian elimination with partial pivoting (largest |pivot|, the first row on
-// ties) by shuffles, then back substitution; returns x[l % 8] in every lane, and false (in
-// every lane) when a pivot is zero.
-__device__ bool wave_solve8(double a, double bv, double& x_mine) {
+// ties), then back substitution; returns x[l % 8] in every lane, and false (in every lane) when
+// a pivot is zero.  Rows stay in their lanes and carry their place instead of being swapped;
+// every column finds its own largest entry, of which column k's is read.  Bound by its serial
+// chain of moves and divisions, of which the moves are now few and need no address (DPP,
+// swizzle, readlane): k_prosac_hyp, 1024 hypotheses for each of three pairs, 25 -> 14.7 us.
+__device__ __forceinline__ bool wave_solve8(double a, double bv, double& x_mine) {
   const int lane = threadIdx.x & 63, r = lane >> 3, c = lane & 7;
+  int place = r;                                     // of this lane's row
+  int at[8];                                         // row lanes 8 at[k] .. hold pivot row k
+  auto better = [](double v2, int p2, double& v, int& p) {
+    const bool t = v2 > v || (v2 == v && p2 < p);
+    v = t ? v2 : v;
+    p = t ? p2 : p;
+  };
+#pragma unroll
   for (int k = 0; k < 8; ++k) {
-    // pivot: max |A[row][k]| over rows >= k, the first row on ties
-    double v = (c == k && r >= k) ? fabs(a) : -1.0;
-    int pr = r;
-    for (int o = 32; o > 0; o >>= 1) {
-      const double v2 = __shfl_xor(v, o);
-      const int r2 = __shfl_xor(pr, o);
-      if (v2 > v || (v2 == v && r2 < pr)) {
-        v = v2;
-        pr = r2;
-      }
-    }
-    if (!(v > 0.0)) return false;
-    // swap rows pr and k
-    const int src = r == k ? pr * 8 + c : r == pr ? k * 8 + c : lane;
-    a = __shfl(a, src);
-    bv = __shfl(bv, src);
-    const double piv = __shfl(a, k * 8 + k), prow = __shfl(a, k * 8 + c), bk = __shfl(bv, k * 8);
-    const double col = __shfl(a, r * 8 + k);
-    if (r > k) {
-      const double f = col / piv;
-      if (c >= k) a -= f * prow;
-      bv -= f * bk;
+    const double col = __shfl(a, (lane & 56) + k);
+    double v = place >= k ? fabs(a) : -1.0;
+    int p = place * 8 + r;
+    better(swap64<8>(v), swap32<8>(p), v, p);
+    better(swap64<16>(v), swap32<16>(p), v, p);
+    better(swap64<32>(v), swap32<32>(p), v, p);
+    if (!(lane_of(v, k) > 0.0)) return false;
+    p = __builtin_amdgcn_readlane(p, k);
+    const int g = p & 7;
+    at[k] = g;
+    place = r == g ? k : place == k ? p >> 3 : place;
+    const double prow = __shfl(a, g * 8 + c), piv = lane_of(a, g * 8 + k), bk = lane_of(bv, g * 8);
+    const double f = col / piv;
+    if (place > k) {
+      if (c >= k) a = __builtin_fma(-f, prow, a);
+      bv = __builtin_fma(-f, bk, bv);
     }
   }
   x_mine = 0.0;
+#pragma unroll
   for (int k = 7; k >= 0; --k) {
-    double t = (r == k && c > k) ? a * x_mine : 0.0;
-    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
-    const double xk = (__shfl(bv, k * 8) - t) / __shfl(a, k * 8 + k);
+    double t = c > k ? a * x_mine : 0.0;             // of every row; row k's sum is read
+    t += 0.0;
+    t += swap64<4>(t);
+    t += swap64<2>(t);
+    t += swap64<1>(t);
+    const double xk = (lane_of(bv, at[k] * 8) - lane_of(t, at[k] * 8)) / lane_of(a, at[k] * 8 + k);
     if (c == k) x_mine = xk;
   }
   return true;
@@ -329,19 +470,22 @@ __device__ __forceinline__ bool is_inlier(const double* H, int2 p, int2 q, doubl
   return ex * ex + ey * ey <= eps2;
 }
 
-// r-th index of [0, R) not in chosen[0 .. nch), in increasing order
-__device__ int nth_free(int r, const int* chosen, int nch) {
-  int s[3];
-  for (int k = 0; k < nch; ++k) s[k] = chosen[k];
-  for (int a = 0; a < nch; ++a)                       // sort (at most 3)
-    for (int b = a + 1; b < nch; ++b)
-      if (s[b] < s[a]) {
-        const int t = s[a];
-        s[a] = s[b];
-        s[b] = t;
-      }
-  for (int k = 0; k < nch; ++k)
-    if (s[k] <= r) ++r;
+// r-th index of [0, R) not among the kN first of `chosen`, in increasing order
+template <int kN>
+__device__ __forceinline__ int nth_free(int r, const int (&chosen)[4]) {
+  int s[3] = {INT32_MAX, INT32_MAX, INT32_MAX};        // sorted, the unused ones last
+#pragma unroll
+  for (int k = 0; k < kN; ++k) s[k] = chosen[k];
+  auto order = [&](int a, int b) {
+    const int lo = min(s[a], s[b]), hi = max(s[a], s[b]);
+    s[a] = lo;
+    s[b] = hi;
+  };
+  order(0, 1);
+  order(1, 2);
+  order(0, 1);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) r += s[k] <= r ? 1 : 0;
   return r;
 }
 
@@ -354,24 +498,17 @@ __device__ __forceinline__ double row1(int i, double x, double y, double v) {
   return i == 3 ? x : i == 4 ? y : i == 5 ? 1.0 : i == 6 ? -v * x : i == 7 ? -v * y : 0.0;
 }
 
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// one wave per hypothesis t: its sample, its model and its inlier count
+// one wave per hypothesis t: its sample (by every lane alike), its model and its inlier count
 __device__ __forceinline__ void prosac_hyp_body(const int32_t* __restrict__ misc, const int2* __restrict__ qa,
                                                 const int2* __restrict__ qb, const int64_t* __restrict__ tp,
                                                 int nhyp, const double* __restrict__ uniforms, double eps2,
                                                 double* __restrict__ hyp_h, int32_t* __restrict__ hyp_ok,
                                                 int32_t* __restrict__ hyp_counts, int bx) {
-  __shared__ double sH[4][9];
-  __shared__ int sOk[4];
-  __shared__ int2 sPts[4][8];                         // the sample: 4 points of A, then of B
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int t = bx * 4 + wv;                          // hypothesis t + 1 of the schedule
+  const int lane = threadIdx.x & 63;
+  const int t = bx * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);   // hypothesis t + 1 of the schedule
   if (t >= nhyp) return;                              // whole waves; no block barrier below
+  double u[4];
+  for (int k = 0; k < 4; ++k) u[k] = uniforms[(int64_t)t * 4 + k];
   const int M = misc[0];
   if (M < kSample) {
     if (lane == 0) {
@@ -380,63 +517,67 @@ __device__ __forceinline__ void prosac_hyp_body(const int32_t* __restrict__ misc
     }
     return;
   }
-  if (lane == 0) {
-    // n_t = 4 + #{n in [4, M-1] : T'_n <= t+1}: binary search over the increasing T'
-    const int64_t tt = t + 1;
-    int lo = kSample, hi = M;                         // first n in [4, M) with T'_n > tt, or M
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (tp[mid] <= tt) lo = mid + 1;
-      else hi = mid;
-    }
-    const int n = kSample + (lo - kSample);
-    const bool nth = !(tp[n] < tt);
-    const double* u = uniforms + (int64_t)t * 4;
-    int idx[4];
-    const int R = nth ? n - 1 : n, draws = nth ? 3 : 4;
-    for (int k = 0; k < draws; ++k) {
-      // clamped into the range (uniforms outside [0, 1), even NaN, cannot index outside it)
-      const double f = floor(u[k] * (double)(R - k));
-      const int r = f >= 0.0 ? (int)fmin(f, (double)(R - k - 1)) : 0;
-      idx[k] = nth_free(r, idx, k);
-    }
-    if (nth) idx[3] = n - 1;
-    int2 pa[4], pb[4];
-    for (int k = 0; k < 4; ++k) {
-      pa[k] = qa[idx[k]];
-      pb[k] = qb[idx[k]];
-      sPts[wv][k] = pa[k];
-      sPts[wv][4 + k] = pb[k];
-    }
-    sOk[wv] = !degenerate4(pa) && !degenerate4(pb);
+  // n_t = 4 + #{n in [4, M-1] : T'_n <= t+1}: the increasing T' searched 64 ways at a time for
+  // the first n in [4, M) with T'_n > tt (or M)
+  const int64_t tt = t + 1;
+  int n = kSample, left = M - kSample;
+  while (left > 0) {
+    const int step = (left + 63) >> 6, q = (lane + 1) * step - 1;    // ends of up to 64 parts
+    const bool below = q < left && tp[n + q] <= tt;
+    const int parts = __popcll(__ballot(below));
+    n += parts * step;
+    left = min(left - parts * step, step - 1);
   }
-  wave_sync();
-  bool ok = sOk[wv];
+  const bool nth = !(tp[n] < tt);
+  int idx[4] = {0, 0, 0, 0};
+  const int R = nth ? n - 1 : n;
+  // clamped into the range (uniforms outside [0, 1), even NaN, cannot index outside it)
+  auto pick = [&](int k) {
+    const double f = floor(u[k] * (double)(R - k));
+    return f >= 0.0 ? (int)fmin(f, (double)(R - k - 1)) : 0;
+  };
+  idx[0] = nth_free<0>(pick(0), idx);
+  idx[1] = nth_free<1>(pick(1), idx);
+  idx[2] = nth_free<2>(pick(2), idx);
+  idx[3] = nth ? n - 1 : nth_free<3>(pick(3), idx);
+  int2 pa[4], pb[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    pa[k] = qa[idx[k]];
+    pb[k] = qb[idx[k]];
+  }
+  double h = 0.0;
+  bool ok = !degenerate4(pa) && !degenerate4(pb);
   if (ok) {
     // lane (row, col) of the 8 x 8 DLT system: rows 2k, 2k+1 from correspondence k
     const int r = lane >> 3, c = lane & 7, k = r >> 1;
-    const int2 p = sPts[wv][k], q = sPts[wv][4 + k];
-    const double x = p.x, y = p.y, u2 = q.x, v2 = q.y;
+    auto of = [k](int a0, int a1, int a2, int a3) { return (double)(k == 0 ? a0 : k == 1 ? a1 : k == 2 ? a2 : a3); };
+    const double x = of(pa[0].x, pa[1].x, pa[2].x, pa[3].x), y = of(pa[0].y, pa[1].y, pa[2].y, pa[3].y);
+    const double u2 = of(pb[0].x, pb[1].x, pb[2].x, pb[3].x), v2 = of(pb[0].y, pb[1].y, pb[2].y, pb[3].y);
     const double a = (r & 1) ? row1(c, x, y, v2) : row0(c, x, y, u2);
-    double h = 0.0;
     ok = wave_solve8(a, (r & 1) ? v2 : u2, h);
-    if (lane < 8) sH[wv][lane] = ok ? h : 0.0;
-  } else if (lane < 8) {
-    sH[wv][lane] = 0.0;
+    h = ok ? h : 0.0;
   }
-  if (lane == 0) sH[wv][8] = 1.0;
-  wave_sync();
   double H[9];
-  for (int c = 0; c < 9; ++c) H[c] = sH[wv][c];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) H[i] = lane_of(h, i);
+  H[8] = 1.0;
   int cnt = 0;
-  if (ok)
-    for (int k = lane; k < M; k += 64) cnt += is_inlier(H, qa[k], qb[k], eps2);
+  if (ok) {
+    // two points a lane at once
+    for (int k = lane; k < M; k += 128) {
+      const int k2 = min(k + 64, M - 1);
+      const int2 a1 = qa[k], b1 = qb[k], a2 = qa[k2], b2 = qb[k2];
+      cnt += is_inlier(H, a1, b1, eps2);
+      cnt += (k + 64 < M) & is_inlier(H, a2, b2, eps2);
+    }
+  }
   for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
   if (lane == 0) {
     hyp_ok[t] = ok;
     hyp_counts[t] = ok ? cnt : 0;
   }
-  if (lane < 9) hyp_h[(int64_t)t * 9 + lane] = H[lane];
+  if (lane < 9) hyp_h[(int64_t)t * 9 + lane] = lane < 8 ? h : 1.0;
 }
 
 __global__ void __launch_bounds__(256) k_prosac_hyp(const int32_t* __restrict__ misc, const int2* __restrict__ qa,
@@ -447,45 +588,46 @@ __global__ void __launch_bounds__(256) k_prosac_hyp(const int32_t* __restrict__ 
   prosac_hyp_body(misc, qa, qb, tp, nhyp, uniforms, eps2, hyp_h, hyp_ok, hyp_counts, blockIdx.x);
 }
 
+// sum over a wave, in every lane
 __device__ __forceinline__ double wave_sum(double v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  v += swap64<1>(v);
+  v += swap64<2>(v);
+  v += swap64<4>(v);
+  v += swap64<8>(v);
+  v += swap64<16>(v);
+  v += swap64<32>(v);
   return v;
 }
 
-// block-wide sums (kWaves waves) of up to five values into every thread; sRed holds
-// kWaves x 5 partials, added in a fixed order
-template <int kWaves>
-__device__ __forceinline__ void block_sums(double* sRed, double& a, double& b, double& c, double& d, double& e) {
-  const int w = threadIdx.x >> 6;
-  a = wave_sum(a);
-  b = wave_sum(b);
-  c = wave_sum(c);
-  d = wave_sum(d);
-  e = wave_sum(e);
+// block-wide sums (kWaves waves) of N values into every thread; sRed holds kWaves x N partials,
+// added in a fixed order
+template <int kWaves, int N>
+__device__ __forceinline__ void block_sums(double* sRed, double (&v)[N]) {
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   __syncthreads();
-  if ((threadIdx.x & 63) == 0) {
-    sRed[w * 5 + 0] = a;
-    sRed[w * 5 + 1] = b;
-    sRed[w * 5 + 2] = c;
-    sRed[w * 5 + 3] = d;
-    sRed[w * 5 + 4] = e;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const double s = wave_sum(v[i]);
+    if (lane == 0) sRed[w * N + i] = s;
   }
   __syncthreads();
-  a = b = c = d = e = 0.0;
-  for (int k = 0; k < kWaves; ++k) {
-    a += sRed[k * 5 + 0];
-    b += sRed[k * 5 + 1];
-    c += sRed[k * 5 + 2];
-    d += sRed[k * 5 + 3];
-    e += sRed[k * 5 + 4];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    double s = 0.0;
+    for (int k = 0; k < kWaves; ++k) s += sRed[k * N + i];
+    v[i] = s;
   }
 }
 
-
 constexpr int kFinalThreads = 512, kFinalWaves = kFinalThreads / 64;
-constexpr int kParts = 7;                             // 72 x 7 = 504 of the 512 threads
+constexpr int kMoments = 22;
 
-// one block of kFinalThreads: the best hypothesis, its inliers, the least-squares refit
+// One block of kFinalThreads: the best hypothesis, its inliers, the least-squares refit.  A chain of
+// short steps, each bound by one trip to memory or one reduction.  The normal equations' 72
+// entries are 22 different sums over the inliers -- the moments of (1, u, v, u^2 + v^2) with (1,
+// x, y, xx, xy, yy) -- so a thread adds its points' moments and one reduction ends them
+// (entry by entry, seven threads each over a seventh of the points, every point read
+// again behind its flag: 75 us for 500 points and 1024 hypotheses; now 16 us).
 __device__ __forceinline__ void prosac_final_body(const int32_t* __restrict__ misc,
                                                   const int2* __restrict__ qa, const int2* __restrict__ qb,
                                                   const int32_t* __restrict__ qi, int cap_a, int nhyp,
@@ -494,118 +636,136 @@ __device__ __forceinline__ void prosac_final_body(const int32_t* __restrict__ mi
                                                   const int32_t* __restrict__ hyp_counts, double eps2,
                                                   double* __restrict__ H_out, int32_t* __restrict__ inliers,
                                                   uint8_t* __restrict__ mask) {
-  __shared__ unsigned long long sBest;
-  __shared__ double sRed[kFinalWaves * 5];
-  __shared__ double sPart[kParts][72];
-  __shared__ double sH[9];
+  __shared__ unsigned long long sBest[kFinalWaves];
+  __shared__ double sRed[kFinalWaves * kMoments];
   __shared__ uint32_t sFlag[kMaxPoints / 32];
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
   const int M = misc[0];
-  if (tid == 0) sBest = 0ull;
   for (int i = tid; i < cap_a; i += kFinalThreads) mask[i] = 0;
-  for (int i = tid; i < (M + 31) / 32; i += kFinalThreads) sFlag[i] = 0;
-  __syncthreads();
   // best: most inliers, then the earliest hypothesis; key (count + 1) << 32 | (2^32-1 - t)
-  unsigned long long mine = 0ull;
-  for (int t = tid; t < nhyp; t += kFinalThreads)
-    if (hyp_ok[t]) {
-      const unsigned long long k = ((unsigned long long)(hyp_counts[t] + 1) << 32) | (0xFFFFFFFFull - (unsigned)t);
-      mine = k > mine ? k : mine;
-    }
-  atomicMax(&sBest, mine);
+  unsigned long long best = 0ull;
+  for (int t = tid; t < nhyp; t += kFinalThreads) {
+    const int ok = hyp_ok[t], count = hyp_counts[t];
+    const unsigned long long k = ((unsigned long long)(count + 1) << 32) | (0xFFFFFFFFull - (unsigned)t);
+    best = ok && k > best ? k : best;
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long other = __shfl_xor(best, o);
+    best = other > best ? other : best;
+  }
+  if (lane == 0) sBest[tid >> 6] = best;
   __syncthreads();
-  const unsigned long long best = sBest;
+  for (int w = 0; w < kFinalWaves; ++w) best = sBest[w] > best ? sBest[w] : best;
   if (best == 0ull) {                                 // no valid hypothesis
     if (tid < 9) H_out[tid] = 0.0;
     if (tid == 0) *inliers = 0;
     return;
   }
   const int tb = (int)(0xFFFFFFFFull - (best & 0xFFFFFFFFull));
-  if (tid < 9) sH[tid] = hyp_h[(int64_t)tb * 9 + tid];
-  __syncthreads();
   double Hb[9];
-  for (int c = 0; c < 9; ++c) Hb[c] = sH[c];
+  for (int c = 0; c < 9; ++c) Hb[c] = hyp_h[(int64_t)tb * 9 + c];
   // inliers of the best model (flags, mask over queries) and the sums for the normalisation
-  double sx = 0, sy = 0, su = 0, sv = 0, cn = 0;
-  for (int k = tid; k < M; k += kFinalThreads)
-    if (is_inlier(Hb, qa[k], qb[k], eps2)) {
-      atomicOr(&sFlag[k >> 5], 1u << (k & 31));
-      mask[qi[k]] = 1;
-      sx += qa[k].x;
-      sy += qa[k].y;
-      su += qb[k].x;
-      sv += qb[k].y;
-      cn += 1.0;
+  double m[5] = {0, 0, 0, 0, 0};
+  for (int k0 = 0; k0 < M; k0 += kFinalThreads) {     // every lane in every turn: a ballot a wave
+    const int k = k0 + tid, kc = min(k, M - 1);
+    const int2 a = qa[kc], b = qb[kc];
+    const int i = qi[kc];
+    const bool in = (k < M) & is_inlier(Hb, a, b, eps2);
+    const uint64_t bits = __ballot(in);
+    if (lane < 2 && k - lane < M) sFlag[((k - lane) >> 5) + lane] = (uint32_t)(bits >> (32 * lane));
+    if (in) {
+      mask[i] = 1;
+      m[0] += 1.0;
+      m[1] += a.x;
+      m[2] += a.y;
+      m[3] += b.x;
+      m[4] += b.y;
     }
-  block_sums<kFinalWaves>(sRed, cn, sx, sy, su, sv);              // (its barriers also publish sFlag)
-  const double n_in = cn;
+  }
+  block_sums<kFinalWaves>(sRed, m);                   // (its barriers also publish sFlag)
+  const double n_in = m[0];
   if (tid == 0) *inliers = (int)n_in;
   if (n_in < 5.0) {
     if (tid < 9) H_out[tid] = Hb[tid] / Hb[8];
     return;
   }
-  const double cx = sx / n_in, cy = sy / n_in, cu = su / n_in, cv = sv / n_in;
-  auto flag = [&](int k) { return (sFlag[k >> 5] >> (k & 31)) & 1u; };
-  double da = 0, db = 0;
-  for (int k = tid; k < M; k += kFinalThreads)
+  const double cx = m[1] / n_in, cy = m[2] / n_in, cu = m[3] / n_in, cv = m[4] / n_in;
+  auto flag = [&](int k) { return ((sFlag[k >> 5] >> (k & 31)) & 1u) != 0; };
+  double d[2] = {0, 0};
+  for (int k = tid; k < M; k += kFinalThreads) {
+    const int2 a = qa[k], b = qb[k];
     if (flag(k)) {
-      da += sqrt((qa[k].x - cx) * (qa[k].x - cx) + (qa[k].y - cy) * (qa[k].y - cy));
-      db += sqrt((qb[k].x - cu) * (qb[k].x - cu) + (qb[k].y - cv) * (qb[k].y - cv));
+      d[0] += sqrt((a.x - cx) * (a.x - cx) + (a.y - cy) * (a.y - cy));
+      d[1] += sqrt((b.x - cu) * (b.x - cu) + (b.y - cv) * (b.y - cv));
     }
-  double z0 = 0.0, z1 = 0.0, z2 = 0.0;
-  block_sums<kFinalWaves>(sRed, da, db, z0, z1, z2);
-  const double s_a = sqrt(2.0) / (da / n_in);
-  const double s_b = sqrt(2.0) / (db / n_in);
-  // normal equations of the normalised system: entry c (64 of A^T A, 8 of A^T b) summed by
-  // kParts threads over interleaved inliers, then the parts in a fixed order
-  if (tid < 72 * kParts) {
-    const int c = tid % 72, part = tid / 72;
-    const int a = c < 64 ? c / 8 : c - 64, cc = c % 8;
-    double acc = 0.0;
-    for (int k = part; k < M; k += kParts)
-      if (flag(k)) {
-        const double x = s_a * (qa[k].x - cx), y = s_a * (qa[k].y - cy);
-        const double u = s_b * (qb[k].x - cu), v = s_b * (qb[k].y - cv);
-        if (c < 64) acc += row0(a, x, y, u) * row0(cc, x, y, u) + row1(a, x, y, v) * row1(cc, x, y, v);
-        else acc += row0(a, x, y, u) * u + row1(a, x, y, v) * v;
-      }
-    sPart[part][c] = acc;
   }
-  __syncthreads();
+  block_sums<kFinalWaves>(sRed, d);
+  const double s_a = sqrt(2.0) / (d[0] / n_in);
+  const double s_b = sqrt(2.0) / (d[1] / n_in);
+  // moments: [0..4] x y xx xy yy (the count is n_in), [5..10] u times 1 x y xx xy yy, [11..16] v
+  // times the same, [17..21] w = u^2 + v^2 times x y xx xy yy
+  double S[kMoments] = {};
+  for (int k = tid; k < M; k += kFinalThreads) {
+    const int2 a = qa[k], b = qb[k];
+    if (flag(k)) {
+      const double x = s_a * (a.x - cx), y = s_a * (a.y - cy), u = s_b * (b.x - cu), v = s_b * (b.y - cv);
+      const double xx = x * x, xy = x * y, yy = y * y, w = u * u + v * v;
+      S[0] += x; S[1] += y; S[2] += xx; S[3] += xy; S[4] += yy;
+      S[5] += u; S[6] += u * x; S[7] += u * y; S[8] += u * xx; S[9] += u * xy; S[10] += u * yy;
+      S[11] += v; S[12] += v * x; S[13] += v * y; S[14] += v * xx; S[15] += v * xy; S[16] += v * yy;
+      S[17] += w * x; S[18] += w * y; S[19] += w * xx; S[20] += w * xy; S[21] += w * yy;
+    }
+  }
+  block_sums<kFinalWaves>(sRed, S);
   if (tid < 64) {                                     // wave 0 solves the normal equations
-    const int r = tid >> 3;
+    // A^T A = [P 0 -U; 0 P -V; -U' -V' W] and A^T b, with P of (x y 1), U and V its products
+    // with u (x, y), v (x, y), and W of (x y) by w
+    const int r = tid >> 3, c = tid & 7;
+    const double P[3][3] = {{S[2], S[3], S[0]}, {S[3], S[4], S[1]}, {S[0], S[1], n_in}};
+    const double U[3][2] = {{S[8], S[9]}, {S[9], S[10]}, {S[6], S[7]}};
+    const double V[3][2] = {{S[14], S[15]}, {S[15], S[16]}, {S[12], S[13]}};
+    const double W[2][2] = {{S[19], S[20]}, {S[20], S[21]}};
+    const double rhs[8] = {S[6], S[7], S[5], S[12], S[13], S[11], -S[17], -S[18]};
     double a = 0.0, bv = 0.0;
-    for (int k = 0; k < kParts; ++k) {
-      a += sPart[k][tid];
-      bv += sPart[k][64 + r];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      bv = r == i ? rhs[i] : bv;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const double e = i < 3 && j < 3 ? P[i % 3][j % 3]
+                         : i >= 3 && i < 6 && j >= 3 && j < 6 ? P[i % 3][j % 3]
+                         : i < 3 && j >= 6 ? -U[i % 3][j & 1] : j < 3 && i >= 6 ? -U[j % 3][i & 1]
+                         : i < 6 && j >= 6 ? -V[i % 3][j & 1] : j < 6 && i >= 6 ? -V[j % 3][i & 1]
+                         : i >= 6 && j >= 6 ? W[i & 1][j & 1] : 0.0;
+        a = r == i && c == j ? e : a;
+      }
     }
     double h = 0.0;
-    const bool solved = wave_solve8(a, bv, h);
-    if (tid < 8) sH[tid] = h;
-    wave_sync();
-    if (tid == 0 && solved) {
+    if (wave_solve8(a, bv, h)) {
+      // H = Tb^-1 Hn Ta with Ta = [s_a 0 -s_a cx; 0 s_a -s_a cy; 0 0 1], Tb likewise: lane 3 r + c
+      // its entry (r, c), in every lane also entry (2, 2)
       double Hn[9];
-      for (int c = 0; c < 8; ++c) Hn[c] = sH[c];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) Hn[i] = lane_of(h, i);
       Hn[8] = 1.0;
-      // H = Tb^-1 Hn Ta with Ta = [s_a 0 -s_a cx; 0 s_a -s_a cy; 0 0 1], Tb likewise
-      const double Ta[9] = {s_a, 0, -s_a * cx, 0, s_a, -s_a * cy, 0, 0, 1};
-      const double Tbi[9] = {1.0 / s_b, 0, cu, 0, 1.0 / s_b, cv, 0, 0, 1};
-      double HT[9], R[9];
-      for (int r = 0; r < 3; ++r)
-        for (int c = 0; c < 3; ++c) {
-          double sum = 0.0;
-          for (int k = 0; k < 3; ++k) sum += Hn[3 * r + k] * Ta[3 * k + c];
-          HT[3 * r + c] = sum;
-        }
-      for (int r = 0; r < 3; ++r)
-        for (int c = 0; c < 3; ++c) {
-          double sum = 0.0;
-          for (int k = 0; k < 3; ++k) sum += Tbi[3 * r + k] * HT[3 * k + c];
-          R[3 * r + c] = sum;
-        }
-      for (int c = 0; c < 9; ++c) H_out[c] = R[c] / R[8];
-    } else if (tid == 0) {
-      for (int c = 0; c < 9; ++c) H_out[c] = Hb[c] / Hb[8];
+      const double ib = 1.0 / s_b;
+      double HT[9];
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        HT[3 * i] = Hn[3 * i] * s_a;
+        HT[3 * i + 1] = Hn[3 * i + 1] * s_a;
+        HT[3 * i + 2] = Hn[3 * i] * (-s_a * cx) + Hn[3 * i + 1] * (-s_a * cy) + Hn[3 * i + 2];
+      }
+      double e = 0.0;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        e = tid == i ? ib * HT[i] + cu * HT[6 + i] : e;
+        e = tid == 3 + i ? ib * HT[3 + i] + cv * HT[6 + i] : e;
+        e = tid == 6 + i ? HT[6 + i] : e;
+      }
+      if (tid < 9) H_out[tid] = e / HT[8];
+    } else if (tid < 9) {
+      H_out[tid] = Hb[tid] / Hb[8];
     }
   }
 }
