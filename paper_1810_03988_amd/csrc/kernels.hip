@@ -446,30 +446,47 @@ __global__ void __launch_bounds__(kThreads, 4) k_pyr(const PyrItem* __restrict__
       auto stage_a = [&](auto rows_c, auto r0_c) __attribute__((always_inline)) {
         constexpr int NR = decltype(rows_c)::value;
         constexpr int R0 = decltype(r0_c)::value;
+        // Slots.  Level 0: a lane keeps one of the window's first 64 columns and its wave takes
+        // every fourth row, so rows, their ring offsets and their tabled products are the wave's
+        // own; the remaining 7 columns of every row are one last round.  (One numbering of
+        // all samples cost divisions and per-lane row addresses: the pass of 8 jobs at 640 to 3840
+        // columns, FP16, took 174 million instructions and 409 us; with B's shorter rows 144
+        // million and 385 us.)  Above it, samples are numbered through.
         constexpr int NE = NR * EW;
-        constexpr int NQ = (NE + kThreads - 1) / kThreads;
+        constexpr int NM = (NR + 3) / 4;
+        constexpr int NQ = WARP ? NM + 1 : (NE + kThreads - 1) / kThreads;
         // recomputed per sub-step (cheap) rather than held in registers across the loop
         int tid_l = tid;
         asm volatile("" : "+v"(tid_l));
+        const int wvu = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;
         int rr[NQ], cc[NQ];                       // logical row (-1: idle slot) and column
-        uint32_t lo[NQ];                          // byte offset of the slot in a channel's rows, unrotated
+        uint32_t row4[NQ], col4[NQ];              // byte offsets of the slot in a channel's rows, unrotated
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-          const int e = tid_l + q * kThreads;
-          rr[q] = e < NE ? R0 + e / EW : -1;
-          cc[q] = e < NE ? e % EW : 0;
+          if (WARP && q < NM) {
+            rr[q] = R0 + wvu + 4 * q;
+            cc[q] = tid_l & 63;
+          } else {
+            const int e = WARP ? tid_l : tid_l + q * kThreads;
+            constexpr int W = WARP ? EW - 64 : EW;
+            rr[q] = e < NR * W ? R0 + e / W : -1;
+            cc[q] = e < NR * W ? EW - W + e % W : 0;
+          }
           // idle slots write the padding column EW (read by stage B's last float4 but never
           // used), so stores need no branch and loads are never sunk into one
-          lo[q] = (uint32_t)((rr[q] < 0 ? R0 : rr[q]) * SW + (rr[q] < 0 ? EW : cc[q])) * 4u;
+          row4[q] = (uint32_t)((rr[q] < 0 ? R0 : rr[q]) * SW) * 4u;
+          col4[q] = (uint32_t)(rr[q] < 0 ? EW : cc[q]) * 4u;
         }
-        // When the stage's samples end inside its last round of slots, that round is idle
-        // for whole waves (the 16-row stage: the waves of threads 128 .. 255); they skip it.
-        const bool last_live = NE % kThreads == 0 || __builtin_amdgcn_readfirstlane(tid >> 6) * 64 + (NQ - 1) * kThreads < NE;
-        auto live = [&](int q) { return q < NQ - 1 || last_live; };
+        // A round that is idle for whole waves (the 16-row stage's last one: the waves of threads
+        // 128 .. 255) is skipped by them.
+        auto live = [&](int q) {
+          if (WARP) return q < NM ? NR % 4 == 0 || wvu + 4 * q < NR : wvu * 64 < NR * (EW - 64);
+          return q < NQ - 1 || NE % kThreads == 0 || wvu * 64 + (NQ - 1) * kThreads < NE;
+        };
         // the slot's cell in channel plane ch, rotated into the ring
         auto cell = [&](int ch, int q) -> float& {
-          const uint32_t a = lo[q] + off4;
-          return *reinterpret_cast<float*>(reinterpret_cast<char*>(&sIn[ch][0][0]) + min(a, a - kPlaneRing));
+          const uint32_t a = row4[q] + off4;
+          return *reinterpret_cast<float*>(reinterpret_cast<char*>(&sIn[ch][0][0]) + (min(a, a - kPlaneRing) + col4[q]));
         };
         // canvas position of a slot (idle slots take the window's first sample)
         auto canvas = [&](int q, int& X, int& Y) {
@@ -824,32 +841,48 @@ __global__ void __launch_bounds__(kThreads, 4) k_pyr(const PyrItem* __restrict__
         return reinterpret_cast<const float*>(plane + min(a, a - kPlaneRing));
       };
       // B+C: REDUCE -> extended coarse tile (CH x CW with a one-sample halo) in sC[ch].
-      // Lane (g, jp), g < 3: coarse columns 2jp, 2jp+1 of coarse rows 3g .. 3g+3, from the
-      // eleven fine rows 6g .. 6g+10, each reduced horizontally from two b128 reads; rows 3
-      // and 6 are written by the group that starts there.
-      if (lane < 3 * (CW / 2)) {
-        const int g = lane / (CW / 2), jp = lane - (CW / 2) * g, rs = 3 * g;
-        float2 hr[11];
+      // Lane (g, jp), g < 3: coarse columns 2jp, 2jp+1 of NG coarse rows from F + 3g on, from the
+      // 2 NG + 3 fine rows they need, each reduced horizontally from two b128 reads.  A tile's
+      // first sub-step makes rows 0 .. 9 (NG = 4; rows 3 and 6 are written by the group that
+      // starts there); the others keep the last two of the sub-step before as rows 0 and 1 and
+      // make the remaining eight (NG = 3; the last group's third is past them).  Rows are
+      // reduced to 16 times their value -- the same roundings, one product less -- and the
+      // columns' weights take the 16 back.
+      auto reduce = [&](auto ng_c, auto first_c) __attribute__((always_inline)) {
+        constexpr int NG = decltype(ng_c)::value, F = decltype(first_c)::value;
+        if (lane < 3 * (CW / 2)) {
+          const int g = lane / (CW / 2), jp = lane - (CW / 2) * g, rs = F + 3 * g;
+          float2 hr[2 * NG + 3];
 #pragma unroll
-        for (int u = 0; u < 11; ++u) {
-          const float* row = rowp(2 * rs + u) + 4 * jp;
-          const float4 a = *reinterpret_cast<const float4*>(row);
-          const float4 bq = *reinterpret_cast<const float4*>(row + 4);
-          hr[u].x = kW0 * (a.x + bq.x) + kW1 * (a.y + a.w) + kW2 * a.z;
-          hr[u].y = kW0 * (a.z + bq.z) + kW1 * (a.w + bq.y) + kW2 * bq.x;
-        }
+          for (int u = 0; u < 2 * NG + 3; ++u) {
+            // (the last group's last rows are past the window: any row will do)
+            const float* row = rowp(2 * (F + 6) + u < EH ? 2 * rs + u : min(2 * rs + u, EH - 1)) + 4 * jp;
+            const float4 a = *reinterpret_cast<const float4*>(row);
+            const float4 bq = *reinterpret_cast<const float4*>(row + 4);
+            hr[u].x = __builtin_fmaf(6.0f, a.z, __builtin_fmaf(4.0f, a.y + a.w, a.x + bq.x));
+            hr[u].y = __builtin_fmaf(6.0f, bq.x, __builtin_fmaf(4.0f, a.w + bq.y, a.z + bq.z));
+          }
+          constexpr float V0 = kW0 / 16.0f, V1 = kW1 / 16.0f, V2 = kW2 / 16.0f;
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          if (m == 0 && g > 0) continue;
-          float2 o;
-          o.x = kW0 * (hr[2 * m].x + hr[2 * m + 4].x) + kW1 * (hr[2 * m + 1].x + hr[2 * m + 3].x) +
-                kW2 * hr[2 * m + 2].x;
-          o.y = kW0 * (hr[2 * m].y + hr[2 * m + 4].y) + kW1 * (hr[2 * m + 1].y + hr[2 * m + 3].y) +
-                kW2 * hr[2 * m + 2].y;
-          float* c = &sC[ch][rs + m][CO + 2 * jp];
-          c[0] = o.x;
-          c[1] = o.y;
+          for (int m = 0; m < NG; ++m) {
+            if (NG == 4 ? m == 0 && g > 0 : m == 2 && g == 2) continue;
+            float* c = &sC[ch][rs + m][CO + 2 * jp];
+            c[0] = __builtin_fmaf(V2, hr[2 * m + 2].x, __builtin_fmaf(V1, hr[2 * m + 1].x + hr[2 * m + 3].x,
+                                                                      V0 * (hr[2 * m].x + hr[2 * m + 4].x)));
+            c[1] = __builtin_fmaf(V2, hr[2 * m + 2].y, __builtin_fmaf(V1, hr[2 * m + 1].y + hr[2 * m + 3].y,
+                                                                      V0 * (hr[2 * m].y + hr[2 * m + 4].y)));
+          }
         }
+      };
+      if (s == 0) {
+        reduce(Rows<4>(), Rows<0>());
+      } else {
+        if (lane < CW) {
+          const float c0 = sC[ch][CH - 2][CO + lane], c1 = sC[ch][CH - 1][CO + lane];
+          sC[ch][0][CO + lane] = c0;
+          sC[ch][1][CO + lane] = c1;
+        }
+        reduce(Rows<3>(), Rows<2>());
       }
       // the wave's own sC[ch] rows: LDS accesses of one wave complete in order
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
