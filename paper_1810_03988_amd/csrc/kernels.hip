@@ -1029,6 +1029,54 @@ __global__ void __launch_bounds__(kThreads, 4) k_pyr(const PyrItem* __restrict__
 // 64x16 tile; thread (x = tid & 63) handles rows 4 (tid >> 6) + j, j = 0..3, so every
 // global access of a wave is one contiguous row segment, and a wave's four consecutive rows
 // share the four coarse rows their vertical EXPAND reads.
+// Four adjacent samples as read, from or to any sample address (global memory takes vectors at
+// any byte).
+typedef uint32_t __attribute__((aligned(1))) u32_unaligned;
+template <typename T>
+struct Quad;
+template <>
+struct Quad<float> {
+  uint32_t d[4];
+  // (load_dwords: dword by dword, `step` bytes apart -- four bytes' worth at step 0 -- so that the
+  // choice between byte and sample weights is not a branch)
+  __device__ __forceinline__ void load(const GLB float* p) {
+    typedef uint32_t vu __attribute__((ext_vector_type(4), aligned(4)));
+    const vu t = *reinterpret_cast<const GLB vu*>(p);
+    d[0] = t.x; d[1] = t.y; d[2] = t.z; d[3] = t.w;
+  }
+  __device__ __forceinline__ void load_dwords(const GLB uint8_t* p, int step) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) d[i] = *(const GLB u32_unaligned*)(p + i * step);
+  }
+  __device__ __forceinline__ void clear() { d[0] = d[1] = d[2] = d[3] = 0; }
+  __device__ __forceinline__ void put(int u, uint32_t raw) { d[u] = raw; }
+  __device__ __forceinline__ float at(int u) const { return __builtin_bit_cast(float, d[u]); }
+};
+template <>
+struct Quad<_Float16> {
+  uint32_t d[2];
+  __device__ __forceinline__ void load(const GLB _Float16* p) {
+    typedef uint32_t vu __attribute__((ext_vector_type(2), aligned(2)));
+    const vu t = *reinterpret_cast<const GLB vu*>(p);
+    d[0] = t.x; d[1] = t.y;
+  }
+  __device__ __forceinline__ void load_dwords(const GLB uint8_t* p, int step) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) d[i] = *(const GLB u32_unaligned*)(p + i * step);
+  }
+  __device__ __forceinline__ void clear() { d[0] = d[1] = 0; }
+  __device__ __forceinline__ void put(int u, uint32_t raw) { d[u >> 1] |= raw << (16 * (u & 1)); }
+  __device__ __forceinline__ float at(int u) const { return from_raw((uint16_t)(d[u >> 1] >> (16 * (u & 1)))); }
+};
+__device__ __forceinline__ void store4_any(GLB float* p, const float v[4]) {
+  typedef float vf __attribute__((ext_vector_type(4), aligned(4)));
+  *reinterpret_cast<GLB vf*>(p) = vf{v[0], v[1], v[2], v[3]};
+}
+__device__ __forceinline__ void store4_any(GLB _Float16* p, const float v[4]) {
+  typedef _Float16 vh __attribute__((ext_vector_type(4), aligned(2)));
+  *reinterpret_cast<GLB vh*>(p) = vh{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
+}
+
 __device__ __forceinline__ int find_blend_item(const BlendItem* __restrict__ items, int nitems, int t) {
   int lo = 0, hi = nitems - 1;
   while (lo < hi) {
@@ -1067,7 +1115,8 @@ __global__ void __launch_bounds__(kThreads) k_blend(const BlendItem* __restrict_
                                                     PanoArg po) {
   constexpr int TX = kBlendTX, TY = kBlendTY;
   constexpr int CW = TX / 2 + 2, CH = TY / 2 + 2;
-  constexpr int HS = 36, ES = TX + 4;
+  // coarse column j at index j + CO, so that columns 1 .. 32 start on a 16-byte boundary
+  constexpr int HS = 40, CO = 3, ES = TX + 4;
   __shared__ __attribute__((aligned(16))) float sC[3][CH][HS];
   __shared__ __attribute__((aligned(16))) float sE[3][CH][ES];
 
@@ -1093,50 +1142,80 @@ __global__ void __launch_bounds__(kThreads) k_blend(const BlendItem* __restrict_
     cams = __ballot(hit);
   }
 
-  // one camera's band and weight samples of this thread's four pixels, as raw bits from
-  // always-valid addresses (offset 0 outside the windows); used after the coarse stage
-  const int x = tid & 63, ybase = 4 * (tid >> 6);   // wave w: tile rows 4w .. 4w+3
-  const int X = X0 + x;
-  using RawT = typename RawOf<T>::type;
+  // A thread has four adjacent pixels of one row (a wave rows of one parity, so its EXPAND takes
+  // one form): bands, weights, R and panorama bytes go as vectors.  Bound by memory; by the vector
+  // arithmetic when a thread had one column of four rows, sample by sample (8 jobs at 640 to 3840
+  // columns, FP16, level 0, 47.7 million pixels: 109 instructions a pixel, 154 us); now 135 us
+  // at 4.1 TB/s, four fifths of a copy's rate.
+  const int m = tid & 15, wvi = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int odd = wvi & 1, y = 8 * (wvi >> 1) + odd + 2 * ((tid >> 4) & 3);
+  const int X = X0 + 4 * m, Y = Y0 + y;
+  // One camera's band and weight samples of the four pixels, as read; used after the coarse
+  // stage.  Its descriptor is read once (scalar loads issued together), offsets are 32-bit (the
+  // host keeps every band and weight plane under 2^31 elements and its rows under 2^23).
   struct CamSamples {
-    RawT l[4][3];
-    uint32_t w[4];
-    bool in[4];
-    bool u8;
+    Quad<T> l[3], w;        // (byte weights: w.d[0])
+    bool in, u8;
   };
-  // The camera's descriptor is read once (scalar loads issued together); bounds tests are
-  // evaluated without branches and offsets are 32-bit (the host keeps every band and
-  // weight plane under 2^31 elements and its rows under 2^23).
   auto fetch = [&](int ci, CamSamples& cs) __attribute__((always_inline)) {
     const BlendCam c = ld_cst(cst(a.cams) + ci);
-    const GLB T* l = cg<T>(c.lap);
-    const int lx = X - c.lx, wx = X - c.wx;
-    const bool xin = (lx >= 0) & (lx < c.lw) & (wx >= 0) & (wx < c.ww);
-    const uint32_t lrow = (uint32_t)c.lap_row, lplane = (uint32_t)c.lap_plane, wrow = (uint32_t)c.wgt_row;
+    const int lx = X - c.lx, wx = X - c.wx, ly = Y - c.ly, wy = Y - c.wy;
+    const bool yin = (ly >= 0) & (ly < c.lh) & (wy >= 0) & (wy < c.wh);
+    const int u0 = max(max(-lx, -wx), 0), u1 = min(min(c.lw - lx, c.ww - wx), 4);   // pixels u0 .. u1-1 are inside
+    cs.in = yin & (u0 < u1);
     cs.u8 = c.wgt_u8 != 0;
+    const uint32_t loff = __umul24((uint32_t)ly, (uint32_t)c.lap_row) + (uint32_t)lx;
+    const uint32_t woff = __umul24((uint32_t)wy, (uint32_t)c.wgt_row) + (uint32_t)wx;
+    const GLB T* l = cg<T>(c.lap);
+    const uint32_t wes = cs.u8 ? 1u : (uint32_t)sizeof(T);
+    if (cs.in & (u0 == 0) & (u1 == 4)) {
+      cs.w.load_dwords(cg<uint8_t>(c.wgt) + woff * wes, cs.u8 ? 0 : 4);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int Y = Y0 + ybase + j;
-      const int ly = Y - c.ly, wy = Y - c.wy;
-      cs.in[j] = xin & (ly >= 0) & (ly < c.lh) & (wy >= 0) & (wy < c.wh);
-      const uint32_t loff = cs.in[j] ? __umul24((uint32_t)ly, lrow) + (uint32_t)lx : 0u;
-      const uint32_t woff = cs.in[j] ? __umul24((uint32_t)wy, wrow) + (uint32_t)wx : 0u;
+      for (int ch = 0; ch < 3; ++ch) cs.l[ch].load(l + ((uint32_t)ch * (uint32_t)c.lap_plane + loff));
+    } else if (cs.in) {
+      // the few quads across a window's edge, pixel by pixel: pixels outside repeat one inside,
+      // every read in flight, and then weigh 0
+      typename RawOf<T>::type lv[3][4];
+      uint32_t wv[4][sizeof(T)];
 #pragma unroll
-      for (int ch = 0; ch < 3; ++ch) cs.l[j][ch] = ld_raw(l, (uint32_t)ch * lplane + loff);
-      cs.w[j] = cs.u8 ? (uint32_t)cg<uint8_t>(c.wgt)[woff] : (uint32_t)ld_raw(cg<T>(c.wgt), woff);
+      for (int u = 0; u < 4; ++u) {
+        const int v = min(max(u, u0), u1 - 1);
+        const GLB uint8_t* wp = cg<uint8_t>(c.wgt) + (woff + v) * wes;
+#pragma unroll
+        for (int b = 0; b < (int)sizeof(T); ++b) wv[u][b] = wp[cs.u8 ? 0 : b];
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) lv[ch][u] = ld_raw(l, (uint32_t)ch * (uint32_t)c.lap_plane + loff + v);
+      }
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch) cs.l[ch].clear();
+      cs.w.clear();
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const bool ok = (u >= u0) & (u < u1);
+        uint32_t w = 0;                              // the sample's bytes
+#pragma unroll
+        for (int b = 0; b < (int)sizeof(T); ++b) w |= wv[u][b] << (8 * b);
+        if (cs.u8) cs.w.d[0] |= ok ? wv[u][0] << (8 * u) : 0u;
+        else cs.w.put(u, ok ? w : 0u);
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) cs.l[ch].put(u, lv[ch][u]);
+      }
     }
   };
-  float acc[4][3];
+  float acc[3][4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) acc[j][0] = acc[j][1] = acc[j][2] = 0.0f;
-  auto accumulate = [&](int ci, const CamSamples& cs) __attribute__((always_inline)) {
-    (void)ci;
+  for (int ch = 0; ch < 3; ++ch)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float wv = !cs.in[j] ? 0.0f : (cs.u8 ? (float)cs.w[j] * kInv255 : from_raw((RawT)cs.w[j]));
+    for (int u = 0; u < 4; ++u) acc[ch][u] = 0.0f;
+  auto accumulate = [&](const CamSamples& cs) __attribute__((always_inline)) {
+    if (!cs.in) return;
+    float w[4];
 #pragma unroll
-      for (int ch = 0; ch < 3; ++ch) acc[j][ch] = acc[j][ch] + wv * from_raw(cs.l[j][ch]);
-    }
+    for (int u = 0; u < 4; ++u) w[u] = cs.u8 ? (float)((cs.w.d[0] >> (8 * u)) & 255u) * kInv255 : cs.w.at(u);
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc[ch][u] = __builtin_fmaf(w[u], cs.l[ch].at(u), acc[ch][u]);
   };
   // the first camera's reads fly together with the coarse level's
   const int first = cams ? (int)__builtin_ctzll(cams) : -1;
@@ -1146,46 +1225,30 @@ __global__ void __launch_bounds__(kThreads) k_blend(const BlendItem* __restrict_
   if (has_coarse) {
     const GLB T* r = cg<T>(a.r_in);
     const int cx0 = X0 / 2 - 1, cy0 = Y0 / 2 - 1;
-    constexpr int NC = 3 * CH * CW;
-    constexpr int NIT = (NC + kThreads - 1) / kThreads;
-    // Sample e = tid + q kThreads of the coarse tile is (channel c, row i, column j); the
-    // triple steps from q to q + 1 by kThreads = DI rows + DJ columns, without a division.
-    // Round q's samples past the tile repeat the tile's last one.
-    constexpr int DI = kThreads / CW, DJ = kThreads % CW;
-    static_assert(kThreads < CH * CW && DI + 1 < 2 * CH, "one carry per step");
-    int cq[NIT], iq[NIT], jq[NIT];
-    {
-      int c = 0, i = tid / CW, j = tid - (tid / CW) * CW;
-#pragma unroll
+    // A tile whose coarse samples all have their fine position inside the level needs no
+    // folding: eight quads of every row and channel, and the two columns beside them.
+    const bool inner = cx0 >= 0 && 2 * (cx0 + CW - 1) < a.W && cy0 >= 0 && 2 * (cy0 + CH - 1) < a.H;
+    if (inner) {
+      const int rowq = min(tid >> 3, 3 * CH - 1), cq = rowq / CH, iq = rowq - cq * CH, k = tid & 7;
+      const int rowe = min(tid >> 1, 3 * CH - 1), ce = rowe / CH, ie = rowe - ce * CH;
+      Quad<T> v;
+      v.load(r + (cq * a.rin_plane + (int64_t)(cy0 + iq) * a.rin_row + (X0 / 2 + 4 * k)));
+      float e = 0.0f;
+      if (tid < 2 * 3 * CH)
+        e = from_raw(ld_raw(r, ce * a.rin_plane + (int64_t)(cy0 + ie) * a.rin_row + cx0 + (tid & 1) * (CW - 1)));
+      // (threads past the last row repeat it: the same values to the same place)
+      *reinterpret_cast<float4*>(&sC[cq][iq][CO + 1 + 4 * k]) = float4{v.at(0), v.at(1), v.at(2), v.at(3)};
+      if (tid < 2 * 3 * CH) sC[ce][ie][CO + (tid & 1) * (CW - 1)] = e;
+    } else {
+      constexpr int NC = 3 * CH * CW, NIT = (NC + kThreads - 1) / kThreads;
+#pragma unroll 1
       for (int q = 0; q < NIT; ++q) {
-        const bool past = c >= 3;
-        cq[q] = past ? 2 : c;
-        iq[q] = past ? CH - 1 : i;
-        jq[q] = past ? CW - 1 : j;
-        j += DJ;
-        i += DI + (j >= CW ? 1 : 0);
-        j -= j >= CW ? CW : 0;
-        c += i >= CH ? 1 : 0;
-        i -= i >= CH ? CH : 0;
+        const int e = min(tid + q * kThreads, NC - 1), row = e / CW, j = e - row * CW, c = row / CH, i = row - c * CH;
+        const int cy = min(fold(2 * (cy0 + i), a.H) >> 1, a.cH - 1);
+        const int cx = min(fold(2 * (cx0 + j), a.W) >> 1, a.cW - 1);
+        sC[c][i][CO + j] = from_raw(ld_raw(r, c * a.rin_plane + (int64_t)cy * a.rin_row + cx));
       }
     }
-    // A tile whose coarse samples all have their fine position inside the level needs no
-    // folding (the fold is then the identity and the coarse index is in range); the offsets
-    // come first and the reads after them, one straight run.
-    const bool inner = cx0 >= 0 && 2 * (cx0 + CW - 1) < a.W && cy0 >= 0 && 2 * (cy0 + CH - 1) < a.H;
-    int64_t off[NIT];
-#pragma unroll
-    for (int q = 0; q < NIT; ++q) {
-      const int cy = inner ? cy0 + iq[q] : min(fold(2 * (cy0 + iq[q]), a.H) >> 1, a.cH - 1);
-      const int cx = inner ? cx0 + jq[q] : min(fold(2 * (cx0 + jq[q]), a.W) >> 1, a.cW - 1);
-      off[q] = cq[q] * a.rin_plane + (int64_t)cy * a.rin_row + cx;
-    }
-    typename RawOf<T>::type v[NIT];
-#pragma unroll
-    for (int q = 0; q < NIT; ++q) v[q] = ld_raw(r, off[q]);
-#pragma unroll
-    for (int q = 0; q < NIT; ++q)
-      if (tid + q * kThreads < NC) sC[cq[q]][iq[q]][jq[q]] = from_raw(v[q]);
     __syncthreads();
     // horizontal EXPAND: item e = tid + k kThreads is (channel, row, quad m) of the
     // 3 x CH x 16 quads
@@ -1196,54 +1259,85 @@ __global__ void __launch_bounds__(kThreads) k_blend(const BlendItem* __restrict_
       const int e = tid + k * kThreads;
       if (e < 3 * PER) {
         const int ch = (e >= PER ? 1 : 0) + (e >= 2 * PER ? 1 : 0), rem = e - ch * PER;
-        const int i = rem >> 4, m = rem & 15;
-        const float2 lo = *reinterpret_cast<const float2*>(&sC[ch][i][2 * m]);
-        const float2 hi = *reinterpret_cast<const float2*>(&sC[ch][i][2 * m + 2]);
+        const int i = rem >> 4, q = rem & 15;
+        const float* c = &sC[ch][i][CO + 2 * q];
+        const float2 lo = {c[0], c[1]}, hi = {c[2], c[3]};
         float4 o;
         o.x = exp_h(lo.x + hi.x, lo.y);
         o.y = 0.5f * (lo.y + hi.x);
         o.z = exp_h(lo.y + hi.y, hi.x);
         o.w = 0.5f * (hi.x + hi.y);
-        *reinterpret_cast<float4*>(&sE[ch][i][4 * m]) = o;
+        *reinterpret_cast<float4*>(&sE[ch][i][4 * q]) = o;
       }
     }
     __syncthreads();
   }
   // cameras in ascending index order
   if (first >= 0) {
-    accumulate(first, cs0);
+    accumulate(cs0);
     for (uint64_t rest = cams & (cams - 1); rest; rest &= rest - 1) {
-      const int ci = (int)__builtin_ctzll(rest);
       CamSamples cs;
-      fetch(ci, cs);
-      accumulate(ci, cs);
+      fetch((int)__builtin_ctzll(rest), cs);
+      accumulate(cs);
     }
   }
-  GLB T* ro = mg<T>(a.r_out);
+  if (has_coarse) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int y = ybase + j;
-    const int Y = Y0 + y;
-    if (has_coarse) {
-      const int yh = y >> 1;
-#pragma unroll
-      for (int ch = 0; ch < 3; ++ch) {
-        const float ev = (y & 1) ? 0.5f * (sE[ch][yh + 1][x] + sE[ch][yh + 2][x])
-                                 : exp_v(sE[ch][yh][x] + sE[ch][yh + 2][x], sE[ch][yh + 1][x]);
-        acc[j][ch] = acc[j][ch] + ev;
+    for (int ch = 0; ch < 3; ++ch) {
+      const float* e = &sE[ch][y >> 1][4 * m];       // rows e, e + ES, e + 2 ES
+      const float4 e1 = *reinterpret_cast<const float4*>(e + ES), e2 = *reinterpret_cast<const float4*>(e + 2 * ES);
+      if (odd) {
+        acc[ch][0] = __builtin_fmaf(0.5f, e1.x + e2.x, acc[ch][0]);
+        acc[ch][1] = __builtin_fmaf(0.5f, e1.y + e2.y, acc[ch][1]);
+        acc[ch][2] = __builtin_fmaf(0.5f, e1.z + e2.z, acc[ch][2]);
+        acc[ch][3] = __builtin_fmaf(0.5f, e1.w + e2.w, acc[ch][3]);
+      } else {
+        const float4 e0 = *reinterpret_cast<const float4*>(e);
+        acc[ch][0] = acc[ch][0] + exp_v(e0.x + e2.x, e1.x);
+        acc[ch][1] = acc[ch][1] + exp_v(e0.y + e2.y, e1.y);
+        acc[ch][2] = acc[ch][2] + exp_v(e0.z + e2.z, e1.z);
+        acc[ch][3] = acc[ch][3] + exp_v(e0.w + e2.w, e1.w);
       }
     }
-    if (X < a.W && Y < a.H && ro != nullptr) {
-      const int64_t off = (int64_t)Y * a.rout_row + X;
+  }
+  if (X >= a.W || Y >= a.H) return;
+  const bool whole = X + 3 < a.W;
+  if (a.r_out != nullptr) {
+    GLB T* ro = mg<T>(a.r_out) + (int64_t)Y * a.rout_row + X;
 #pragma unroll
-      for (int ch = 0; ch < 3; ++ch) stg(ro, ch * a.rout_plane + off, acc[j][ch]);
+    for (int ch = 0; ch < 3; ++ch) {
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = settled(acc[ch][u]);
+      GLB T* p = ro + ch * a.rout_plane;
+      if (whole) {
+        store4_any(p, v);
+      } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (X + u < a.W) stg(p, u, v[u]);
+      }
     }
   }
   if (FINAL) {
+    // rint(255 R_0) clamped to [0, 255] by the byte conversion, packed byte by byte; four pixels
+    // are three dwords, stored as such at any byte (byte by byte, as a
+    // panorama of odd pitch would need at dword alignment, the 8 jobs took 181 us)
     uint8_t* const pano_ptr = po.ptr ? po.ptr : a.pano;
     const int64_t pano_row = po.ptr ? po.row : a.pano_row;
+    GLB uint8_t* prow = mg<uint8_t>(pano_ptr) + (int64_t)Y * pano_row + (int64_t)X * 3;
+    uint32_t d[3] = {0, 0, 0};
 #pragma unroll
-    for (int j = 0; j < 4; ++j) put_row(pano_ptr, pano_row, X0, x, Y0 + ybase + j, a.W, a.H, acc[j]);
+    for (int k = 0; k < 12; ++k)
+      d[k >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(255.0f * acc[k % 3][k / 3], (uint32_t)(k & 3), d[k >> 2]);
+    if (whole) {
+      typedef uint32_t vu3 __attribute__((ext_vector_type(3), aligned(1)));
+      *reinterpret_cast<GLB vu3*>(prow) = vu3{d[0], d[1], d[2]};
+    } else {
+#pragma unroll
+      for (int k = 0; k < 12; ++k)
+        if (X + k / 3 < a.W) prow[k] = (uint8_t)(d[k >> 2] >> (8 * (k & 3)));
+    }
   }
 }
 
