@@ -16,11 +16,10 @@
 //
 // Five launches per call, each covering every area of every frame of the call:
 //   k_lorb_clear    zero the areas' survivor counts
-//   k_lorb_detect   64x16 tiles: gray tile with a 4-sample halo in LDS, the horizontal pass
-//                   of the window over the gradient products (formed on the fly) in LDS,
-//                   the vertical pass, the FAST test and R on the tile plus a 1-sample
-//                   ring, suppression from LDS; survivors are appended to the area's list
-//                   (one atomic per block; list order is arbitrary)
+//   k_lorb_detect   64x16 tiles: gray tile with a 4-sample halo in LDS, the FAST test on the
+//                   tile plus a 1-sample ring, R where it passes, suppression from LDS;
+//                   survivors are appended to the area's list (one atomic per block; list
+//                   order is arbitrary)
 //   k_lorb_select   one block per area: a histogram of the survivors over a monotone bucket
 //                   of R in LDS, the highest bucket b such that the buckets >= b hold at
 //                   least N survivors (all buckets when there are fewer), and the survivors
@@ -52,8 +51,6 @@ constexpr int kMargin = 17;
 constexpr int kMaxAreas = 64;
 constexpr int kTX = 64, kTY = 16;                       // outputs per tile
 constexpr int kGW = kTX + 8, kGH = kTY + 8;             // gray: tile + 4 each side (72 x 24)
-constexpr int kPH = kTY + 6;                            // gradient-product rows: tile + 3 (22)
-constexpr int kHW = kTX + 2;                            // horizontal pass: tile + 1 (66 x 22)
 constexpr int kRW = kTX + 2, kRH = kTY + 2;             // responses: tile + 1 (66 x 18)
 constexpr int kBins = 4096;                             // response histogram per area
 constexpr int kRankGrid = 64;
@@ -80,10 +77,6 @@ struct AreaTable {
   FrameRef f[kMaxFrames];
 };
 
-__device__ __forceinline__ int luma3(uint32_t r, uint32_t g, uint32_t b) {
-  return (int)((77 * r + 150 * g + 29 * b + 128) >> 8);
-}
-
 // Bytes at any address (global memory accepts unaligned dword accesses).
 #define GLB __attribute__((address_space(1)))
 typedef unsigned long long __attribute__((aligned(1))) u64u;
@@ -91,13 +84,15 @@ typedef uint32_t __attribute__((aligned(1))) u32u;
 __device__ __forceinline__ unsigned long long ld8u(const uint8_t* p) { return *(const GLB u64u*)p; }
 __device__ __forceinline__ uint32_t ld4u(const uint8_t* p) { return *(const GLB u32u*)p; }
 
-// gray levels of the 4 RGB pixels in the 12 bytes at p
-__device__ __forceinline__ int4 luma4(const uint8_t* p) {
-  const unsigned long long lo = ld8u(p);
-  const uint32_t hi = ld4u(p + 8);
-  auto B = [&](int i) -> uint32_t { return i < 8 ? (uint32_t)(lo >> (8 * i)) & 255u : (hi >> (8 * (i - 8))) & 255u; };
-  return make_int4(luma3(B(0), B(1), B(2)), luma3(B(3), B(4), B(5)), luma3(B(6), B(7), B(8)),
-                   luma3(B(9), B(10), B(11)));
+// gray levels (77 R + 150 G + 29 B + 128) >> 8 of the 4 RGB pixels in twelve bytes, eight in lo and
+// four in w2: each a dot product of four bytes with the weights
+__device__ __forceinline__ int4 luma4(unsigned long long lo, uint32_t w2) {
+  const uint32_t w0 = (uint32_t)lo, w1 = (uint32_t)(lo >> 32);
+  constexpr uint32_t kW = 77u | (150u << 8) | (29u << 16);
+  return make_int4((int)(__builtin_amdgcn_udot4(w0, kW, 128u, false) >> 8),
+                   (int)(__builtin_amdgcn_udot4(__builtin_amdgcn_alignbyte(w1, w0, 3), kW, 128u, false) >> 8),
+                   (int)(__builtin_amdgcn_udot4(__builtin_amdgcn_alignbyte(w2, w1, 2), kW, 128u, false) >> 8),
+                   (int)(__builtin_amdgcn_udot4(w2, kW << 8, 128u, false) >> 8));
 }
 
 // FAST circle of radius 3, clockwise from the top
@@ -122,6 +117,20 @@ __device__ __forceinline__ int bucket(int64_t R) {
   return R > 0 ? kBins / 2 + 1 + k : kBins / 2 - 1 - k;
 }
 
+// Read one dword of every 64-byte line of the table that a block may need -- the head with the
+// first areas, and the frames -- at once, so that its fields, wanted one after another, come
+// from the scalar cache (each line's first read is a trip to memory otherwise).
+__device__ __forceinline__ void touch(const AreaTable& T) {
+  typedef const __attribute__((address_space(4))) int* ConstWords;
+  const ConstWords w = (ConstWords)&T;
+  int any = 0;
+#pragma unroll
+  for (int i = 0; i < 6; ++i) any |= w[16 * i];
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(FrameRef) * kMaxFrames / 64); ++i) any |= w[offsetof(AreaTable, f) / 4 + 16 * i];
+  asm volatile("" ::"s"(any));
+}
+
 __global__ void k_lorb_clear(int32_t* __restrict__ count, int m) {
   if ((int)threadIdx.x < 2 * m) count[threadIdx.x] = 0;
 }
@@ -129,16 +138,25 @@ __global__ void k_lorb_clear(int32_t* __restrict__ count, int m) {
 __global__ void __launch_bounds__(256) k_lorb_detect(const AreaTable T, int tf, int64_t t,
                                                      int32_t* __restrict__ count, int64_t* __restrict__ listR,
                                                      int32_t* __restrict__ listI) {
-  __shared__ __attribute__((aligned(16))) int sG[kGH][kGW + 4];
-  __shared__ int sWave[4];
-  __shared__ int sBase;
-  __shared__ int sH[3][kPH][kHW];
+  __shared__ __attribute__((aligned(16))) int16_t sG[kGH][kGW + 4];
+  __shared__ int sCount[3], sBase;
+  __shared__ uint16_t sNear[kRH * kRW], sCorner[kRH * kRW];
   __shared__ int64_t sR[kRH][kRW];                   // responses, kNone where no candidate
   const int tid = threadIdx.x;
   const int b = blockIdx.x;
+  if (tid < 3) sCount[tid] = 0;
+  touch(T);
   int z = 0;
-  for (int i = 0; i < T.m; ++i)
-    if (b >= T.a[i].tile_begin && b < T.a[i].tile_begin + T.a[i].ntiles) z = i;
+  for (int i0 = 0; i0 < T.m; i0 += 8) {                // eight areas' reads in flight
+    int first[8], n[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      first[i] = T.a[min(i0 + i, T.m - 1)].tile_begin;
+      n[i] = T.a[min(i0 + i, T.m - 1)].ntiles;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) z = b >= first[i] && b < first[i] + n[i] ? min(i0 + i, T.m - 1) : z;
+  }
   const AreaDesc a = T.a[z];
   const uint8_t* __restrict__ frame = T.f[a.frame].p;
   const int64_t row = T.f[a.frame].row;
@@ -153,128 +171,161 @@ __global__ void __launch_bounds__(256) k_lorb_detect(const AreaTable T, int tf, 
   // feed positions outside the area, which are never candidates.
   {
     const int xs = a.x0 + ox - 4, ys = a.y0 + oy - 4;
-    for (int e = tid; e < kGH * (kGW / 4); e += 256) {
-      const int r = e / (kGW / 4), g = e - r * (kGW / 4);
-      const int x = min(xs + 4 * g, fw - 4), y = min(ys + r, fh - 1);
-      *reinterpret_cast<int4*>(&sG[r][4 * g]) = luma4(frame + (int64_t)y * row + 3 * (int64_t)x);
+    constexpr int kItems = kGH * (kGW / 4), kRounds = (kItems + 255) / 256;
+    unsigned long long lo[kRounds];
+    uint32_t hi[kRounds];
+#pragma unroll
+    for (int q = 0; q < kRounds; ++q) {
+      const int e = min(tid + 256 * q, kItems - 1), r = e / (kGW / 4), g = e - r * (kGW / 4);
+      const uint8_t* p = frame + (int64_t)min(ys + r, fh - 1) * row + 3 * (int64_t)min(xs + 4 * g, fw - 4);
+      lo[q] = ld8u(p);
+      hi[q] = ld4u(p + 8);
+    }
+#pragma unroll
+    for (int q = 0; q < kRounds; ++q) {
+      const int e = min(tid + 256 * q, kItems - 1), r = e / (kGW / 4), g = e - r * (kGW / 4);
+      const int4 v = luma4(lo[q], hi[q]);
+      *reinterpret_cast<uint2*>(&sG[r][4 * g]) = make_uint2((uint32_t)(v.x | (v.y << 16)), (uint32_t)(v.z | (v.w << 16)));
     }
   }
   __syncthreads();
-  // gradient products (on columns ox-3 .. ox+66, rows oy-3 .. oy+18) and the binomial
-  // window [1 4 6 4 1] horizontally (columns ox-1 .. ox+64): each output forms the gradients
-  // of its five taps from the gray levels and weights their three products
-  for (int e = tid; e < kPH * kHW; e += 256) {
-    const int r = e / kHW, c = e - r * kHW;
+  // Positions are the tile and a 1-sample ring (kRH * kRW = 1188).  Few are corners and few of
+  // the rest come near, so each step runs on the list of those that the step before left:
+  //   1 of the circle's four axis samples, at least two are brighter or two darker (any nine in
+  //     a row hold two of them);
+  //   2 the segment test;
+  //   3 the response, from the position's own 7x7 gray levels;
+  //   4 suppression.
+  // Bound by the steps' latency: LDS is kept small enough (18 KB) for eight blocks a compute unit.
+  // (Every step at every position, the window's horizontal pass in 17 KB of LDS: 27 us for the
+  // six areas of four 1080p frames; now 20 us.  The lists lose where more than a third of
+  // all positions are corners; noise alone makes 6% of them.)
+  const int lane = tid & 63, wave = tid >> 6;
+  const uint64_t below = (1ull << lane) - 1;
+  // append `value` of the lanes with `hit` to a list (n its length), in any order
+  auto append = [&](uint16_t* list, int* n, bool hit, int value) {
+    const uint64_t m = __ballot(hit);
+    if (m == 0) return;
+    int at = 0;
+    if (lane == (int)__builtin_ctzll(m)) at = atomicAdd(n, __popcll(m));
+    at = __builtin_amdgcn_readlane(at, (int)__builtin_ctzll(m));
+    if (hit) list[at + __popcll(m & below)] = (uint16_t)value;
+  };
+  {
+    constexpr int kRounds = (kRH * kRW + 255) / 256;
+    uint64_t near[kRounds];
+    int total = 0;
+    constexpr int kDR = 256 / kRW, kDC = 256 % kRW;      // a round's step in rows and columns
+    int r0 = tid / kRW, c0 = tid - r0 * kRW;
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k) {
+      const bool last = r0 >= kRH;                       // past the list: its last row again
+      const int r = last ? kRH - 1 : r0, c = c0;
+      r0 += kDR + (c0 + kDC >= kRW ? 1 : 0);
+      c0 += kDC - (c0 + kDC >= kRW ? kRW : 0);
+      sR[r][c] = kNone;
+      const int ax = ox - 1 + c, ay = oy - 1 + r;
+      const int16_t* g = &sG[r + 3][c + 3];
+      const int p = g[0], n0 = g[-3 * (kGW + 4)], n1 = g[3], n2 = g[3 * (kGW + 4)], n3 = g[-3];
+      // the second largest and the second smallest of the four
+      const int m1 = min(max(n0, n1), max(n2, n3)), m2 = max(min(n0, n1), min(n2, n3));
+      const bool in = !last & ((unsigned)ax < (unsigned)a.w) & ((unsigned)ay < (unsigned)a.h);
+      near[k] = __ballot(in & ((max(m1, m2) > p + tf) | (min(m1, m2) < p - tf)));
+      total += __popcll(near[k]);
+    }
+    int at = 0;
+    if (lane == 0 && total) at = atomicAdd(&sCount[0], total);
+    at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k) {
+      if ((near[k] >> lane) & 1) sNear[at + __popcll(near[k] & below)] = (uint16_t)(tid + 256 * k);
+      at += __popcll(near[k]);
+    }
+  }
+  __syncthreads();
+  const int nnear = sCount[0];
+  for (int i0 = 0; i0 < nnear; i0 += 256) {
+    const int i = i0 + tid, e = sNear[min(i, nnear - 1)];
+    const int r = e / kRW, c = e - r * kRW, gr = r + 3, gc = c + 3;
+    const int p = sG[gr][gc];
+    unsigned bright = 0, dark = 0;                       // (a sign a bit, the last sample's the lowest)
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int v = sG[gr + kCircle[q][1]][gc + kCircle[q][0]];
+      bright = __builtin_amdgcn_alignbit(bright, (unsigned)(p + tf - v), 31);
+      dark = __builtin_amdgcn_alignbit(dark, (unsigned)(v - (p - tf)), 31);
+    }
+    // 9 contiguous set bits on the cyclic circle: bit i survives the shifts when bits
+    // i .. i+8 of the doubled mask are all set
+    unsigned mb = bright | (bright << 16), md = dark | (dark << 16);
+#pragma unroll
+    for (int s = 1; s < 9; ++s) {
+      mb &= mb >> 1;
+      md &= md >> 1;
+    }
+    append(sCorner, &sCount[1], (i < nnear) & (((mb | md) & 0xFFFFu) != 0), e);
+  }
+  __syncthreads();
+  const int ncorner = sCount[1];
+  // the binomial window [1 4 6 4 1] squared over the gradient products ix ix, iy iy, ix iy
+  auto taps = [&](int r, int c, int (&h)[3]) {       // horizontally, row r of the products, columns c .. c + 4
     int pxx[5], pyy[5], pxy[5];
 #pragma unroll
-    for (int i = 0; i < 5; ++i) {                  // product column c + i (gray column c + i + 1)
+    for (int i = 0; i < 5; ++i) {                    // product column c + i (gray column c + i + 1)
       const int ix = sG[r + 1][c + i + 2] - sG[r + 1][c + i], iy = sG[r + 2][c + i + 1] - sG[r][c + i + 1];
       pxx[i] = ix * ix;
       pyy[i] = iy * iy;
       pxy[i] = ix * iy;
     }
-    sH[0][r][c] = (pxx[0] + pxx[4]) + 4 * (pxx[1] + pxx[3]) + 6 * pxx[2];
-    sH[1][r][c] = (pyy[0] + pyy[4]) + 4 * (pyy[1] + pyy[3]) + 6 * pyy[2];
-    sH[2][r][c] = (pxy[0] + pxy[4]) + 4 * (pxy[1] + pxy[3]) + 6 * pxy[2];
-  }
-  __syncthreads();
-  // vertically, the response and the segment test on the tile and a 1-sample ring
-  // (kRH * kRW = 1188 positions: at most 5 per thread)
-  int64_t resp[5];
+    h[0] = (pxx[0] + pxx[4]) + 4 * (pxx[1] + pxx[3]) + 6 * pxx[2];
+    h[1] = (pyy[0] + pyy[4]) + 4 * (pyy[1] + pyy[3]) + 6 * pyy[2];
+    h[2] = (pxy[0] + pxy[4]) + 4 * (pxy[1] + pxy[3]) + 6 * pxy[2];
+  };
+  for (int i = tid; i < ncorner; i += 256) {
+    const int e = sCorner[i], r = e / kRW, c = e - r * kRW;
+    int64_t mm[3] = {0, 0, 0};
 #pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    const int e = tid + 256 * k;
-    int64_t out = kNone;
-    if (e < kRH * kRW) {
-      const int r = e / kRW, c = e - r * kRW;
-      const int ax = ox - 1 + c, ay = oy - 1 + r;
-      if (ax >= 0 && ax < a.w && ay >= 0 && ay < a.h) {
-        const int gr = r + 3, gc = c + 3;
-        const int p = sG[gr][gc];
-        unsigned bright = 0, dark = 0;
+    for (int j = 0; j < 5; ++j) {
+      int h[3];
+      taps(r + j, c, h);
+      const int w = j == 0 || j == 4 ? 1 : j == 2 ? 6 : 4;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-          const int v = sG[gr + kCircle[q][1]][gc + kCircle[q][0]];
-          bright |= (unsigned)(v > p + tf) << q;
-          dark |= (unsigned)(v < p - tf) << q;
-        }
-        // 9 contiguous set bits on the cyclic circle: bit i survives the shifts when bits
-        // i .. i+8 of the doubled mask are all set
-        unsigned mb = bright | (bright << 16), md = dark | (dark << 16);
-#pragma unroll
-        for (int s = 1; s < 9; ++s) {
-          mb &= mb >> 1;
-          md &= md >> 1;
-        }
-        if (((mb | md) & 0xFFFFu) != 0) {
-          int64_t mm[3];
-#pragma unroll
-          for (int q = 0; q < 3; ++q)
-            mm[q] = (int64_t)(sH[q][r][c] + sH[q][r + 4][c]) + 4 * (int64_t)(sH[q][r + 1][c] + sH[q][r + 3][c]) +
-                    6 * (int64_t)sH[q][r + 2][c];
-          const int64_t A = mm[0], B = mm[1], C = mm[2];
-          const int64_t R = 64 * (A * B - C * C) - 3 * (A + B) * (A + B);
-          if (R >= t) out = R;
-        }
-      }
+      for (int q = 0; q < 3; ++q) mm[q] += w * (int64_t)h[q];
     }
-    resp[k] = out;
-  }
-#pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    const int e = tid + 256 * k;
-    if (e < kRH * kRW) sR[e / kRW][e % kRW] = resp[k];
+    const int64_t A = mm[0], B = mm[1], C = mm[2];
+    const int64_t R = 64 * (A * B - C * C) - 3 * (A + B) * (A + B);
+    if (R >= t) sR[r][c] = R;
   }
   __syncthreads();
   // suppression on the tile: a candidate survives when every neighbouring candidate has a
-  // smaller R, or an equal R and a later raster position
-  const int lane = tid & 63, wave = tid >> 6;
-  constexpr int kPer = kTX * kTY / 256;              // 4 positions per thread
-  int64_t keepR[kPer];
-  uint64_t mask[kPer];
-  int nwave = 0;
-#pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    const int e = tid + 256 * k;
-    const int r = e / kTX, c = e - r * kTX;
-    const int64_t R = sR[r + 1][c + 1];
-    bool keep = R != kNone;
+  // smaller R, or an equal R and a later raster position.  The block's survivors are appended
+  // to the area's list with one atomic (a wave's each: 2 us more).
+  for (int i0 = 0; i0 < ncorner; i0 += 256) {
+    const int i = i0 + tid, e = sCorner[min(i, ncorner - 1)], r = e / kRW, c = e - r * kRW;
+    const int64_t R = sR[r][c];
+    bool keep = (i < ncorner) & (R != kNone) & (r >= 1) & (r <= kTY) & (c >= 1) & (c <= kTX);
     if (keep) {
 #pragma unroll
       for (int dy = -1; dy <= 1; ++dy)
 #pragma unroll
         for (int dx = -1; dx <= 1; ++dx) {
           if (!dx && !dy) continue;
-          const int64_t q = sR[r + 1 + dy][c + 1 + dx];
+          const int64_t q = sR[r + dy][c + dx];
           const bool earlier = dy < 0 || (dy == 0 && dx < 0);
-          if (q != kNone && (q > R || (q == R && earlier))) keep = false;
+          keep &= !((q > R) | (earlier & (q == R)));       // (kNone is below every R)
         }
     }
-    keepR[k] = keep ? R : kNone;
-    mask[k] = __ballot(keep);
-    nwave += __popcll(mask[k]);
-  }
-  // append the block's survivors to the area's list with one atomic
-  if (lane == 0) sWave[wave] = nwave;
-  __syncthreads();
-  if (tid == 0) {
-    const int total = sWave[0] + sWave[1] + sWave[2] + sWave[3];
-    sBase = total ? atomicAdd(&count[2 * z], total) : 0;
+    append(sNear, &sCount[2], keep, e);
   }
   __syncthreads();
-  int run = sBase;
-  for (int w = 0; w < wave; ++w) run += sWave[w];
-  const uint64_t below = (1ull << lane) - 1;
-#pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    if (keepR[k] != kNone) {
-      const int e = tid + 256 * k;
-      const int r = e / kTX, c = e - r * kTX;
-      const int pos = a.list_off + run + __popcll(mask[k] & below);
-      listR[pos] = keepR[k];
-      listI[pos] = (oy + r) * a.w + (ox + c);
-    }
-    run += __popcll(mask[k]);
+  const int nkept = sCount[2];
+  if (nkept == 0) return;
+  if (tid == 0) sBase = atomicAdd(&count[2 * z], nkept);
+  __syncthreads();
+  for (int i = tid; i < nkept; i += 256) {
+    const int e = sNear[i], r = e / kRW, c = e - r * kRW;
+    listR[a.list_off + sBase + i] = sR[r][c];
+    listI[a.list_off + sBase + i] = (oy + r - 1) * a.w + (ox + c - 1);
   }
 }
 
@@ -443,19 +494,25 @@ __global__ void __launch_bounds__(256) k_lorb_brief(const AreaTable T,
   const uint8_t* __restrict__ frame = T.f[T.a[z].frame].p;
   const int64_t row = T.f[T.a[z].frame].row;
   const uint8_t* base = frame + (int64_t)(y - kHalfPatch) * row + 3 * (int64_t)(x - kHalfPatch);
-  // per row: 8 groups of 4 pixels (12 bytes) and a tail of 3 pixels (9 bytes); every byte
-  // read belongs to the patch, which lies inside the frame
-  for (int e = lane; e < kPatch * 9; e += 64) {
-    const int r = e / 9, g = e - r * 9;
-    const uint8_t* p = base + (int64_t)r * row + 12 * g;
-    if (g < 8) {
-      *reinterpret_cast<int4*>(&sPG[wv][r][4 * g]) = luma4(p);
-    } else {
-      const unsigned long long lo = ld8u(p);
-      const uint32_t b8 = p[8];
-      sPG[wv][r][32] = luma3((uint32_t)lo & 255u, (uint32_t)(lo >> 8) & 255u, (uint32_t)(lo >> 16) & 255u);
-      sPG[wv][r][33] = luma3((uint32_t)(lo >> 24) & 255u, (uint32_t)(lo >> 32) & 255u, (uint32_t)(lo >> 40) & 255u);
-      sPG[wv][r][34] = luma3((uint32_t)(lo >> 48) & 255u, (uint32_t)(lo >> 56) & 255u, b8);
+  // per row: 8 groups of 4 pixels (12 bytes) and a tail of 3 pixels (9 bytes, its fourth column
+  // is never used); every byte read belongs to the patch, which lies inside the frame.  All
+  // reads are issued before any is used (a round at a time, each waited for: 10.2 us for six
+  // areas of 500 points; now 8.4 us).
+  {
+    constexpr int kItems = kPatch * 9, kRounds = (kItems + 63) / 64;
+    unsigned long long lo[kRounds];
+    uint32_t hi[kRounds];
+#pragma unroll
+    for (int q = 0; q < kRounds; ++q) {
+      const int e = min(lane + 64 * q, kItems - 1), r = e / 9, g = e - r * 9;
+      const uint8_t* p = base + (int64_t)r * row + 12 * g;
+      lo[q] = ld8u(p);
+      hi[q] = ld4u(p + (g < 8 ? 8 : 5));
+    }
+#pragma unroll
+    for (int q = 0; q < kRounds; ++q) {
+      const int e = min(lane + 64 * q, kItems - 1), r = e / 9, g = e - r * 9;
+      *reinterpret_cast<int4*>(&sPG[wv][r][4 * g]) = luma4(lo[q], g < 8 ? hi[q] : hi[q] >> 24);
     }
   }
   wave_sync_lds();
@@ -473,23 +530,25 @@ __global__ void __launch_bounds__(256) k_lorb_brief(const AreaTable T,
   auto off = [](int32_t v) { return min(max(v, -15), 15); };
   const int words = nd / 32;
   uint32_t* d = desc + slot * 2 * words;
-  for (int b0 = 0; b0 < nd; b0 += 64) {
-    const int pk = b0 + lane;
-    bool gt = false, lt = false;
-    if (pk < nd) {
-      const int4 pp = *reinterpret_cast<const int4*>(pattern + 4 * pk);
-      const int s1 = S(off(pp.x), off(pp.y)), s2 = S(off(pp.z), off(pp.w));
-      gt = s1 > s2;
-      lt = s1 < s2;
-    }
-    const uint64_t mg = __ballot(gt), ml = __ballot(lt);
-    const int w0 = b0 / 32;
-    // lanes 0-3 store the (up to) two words of each string
-    if (lane < 4) {
-      const int hi = lane & 1, str = lane >> 1;
-      if (w0 + hi < words) {
-        const uint64_t mk = str ? ml : mg;
-        d[str * words + w0 + hi] = (uint32_t)(hi ? (mk >> 32) : mk);
+  for (int b1 = 0; b1 < nd; b1 += 256) {               // 256 tests' positions in flight
+    int4 pp[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) pp[q] = *reinterpret_cast<const int4*>(pattern + 4 * min(b1 + 64 * q + lane, nd - 1));
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int b0 = b1 + 64 * q;
+      if (b0 >= nd) break;
+      const int s1 = S(off(pp[q].x), off(pp[q].y)), s2 = S(off(pp[q].z), off(pp[q].w));
+      const bool in = b0 + lane < nd;
+      const uint64_t mg = __ballot(in & (s1 > s2)), ml = __ballot(in & (s1 < s2));
+      const int w0 = b0 / 32;
+      // lanes 0-3 store the (up to) two words of each string
+      if (lane < 4) {
+        const int hi = lane & 1, str = lane >> 1;
+        if (w0 + hi < words) {
+          const uint64_t mk = str ? ml : mg;
+          d[str * words + w0 + hi] = (uint32_t)(hi ? (mk >> 32) : mk);
+        }
       }
     }
   }
