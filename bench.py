@@ -106,11 +106,10 @@ def _short_kernel(name: str) -> str:
     if m:
         return m.group(1) + "<" + m.group(2) + ">"
     # mangled names (as some rocprofv3 builds report them): this library's kernels
-    m = re.search(r"\d+(k_[a-z_]+?)I(DF16_|f)Lb([01])ELb([01])E", name)
+    m = re.search(r"\d+(k_[a-z_]+?)I(DF16_|f)((?:Lb[01]E)*)E", name)
     if m:
-        t = "_Float16" if m.group(2) == "DF16_" else "float"
-        b = lambda v: "true" if v == "1" else "false"
-        return f"{m.group(1)}<{t}, {b(m.group(3))}, {b(m.group(4))}>"
+        flags = ["true" if v == "1" else "false" for v in re.findall(r"Lb([01])E", m.group(3))]
+        return f"{m.group(1)}<{', '.join(['_Float16' if m.group(2) == 'DF16_' else 'float'] + flags)}>"
     m = re.search(r"_GLOBAL__N_1\d+(k_[a-z0-9_]+?)E", name)
     if m:
         return m.group(1)
