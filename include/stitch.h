@@ -279,7 +279,8 @@ stitch_status stitch_batch_autotune(stitch_batch* batch, const stitch_image* con
 /* Per-launch timing of stitch_batch_run (tracing, as for plans).  While enabled, runs are
  * launched eagerly (no graph) with one HIP event before the first launch and one after
  * every launch; kind k < 16 is the pyramid pass from level k (k = 0: warp + level 0), kind
- * 16 + k the blend of level k.  set_timing clears the totals; read_timing waits for the
+ * 16 + k the blend of level k; small levels that share a launch count as the finest of
+ * them.  set_timing clears the totals; read_timing waits for the
  * recorded events and returns accumulated milliseconds and launch counts per kind.
  * Errors: NULL, DEVICE. */
 #define STITCH_BATCH_TIMING_KINDS (2 * STITCH_MAX_LEVELS)

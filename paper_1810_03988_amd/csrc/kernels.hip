@@ -1733,14 +1733,26 @@ __device__ __forceinline__ float expand_from(const float* r, int st, int nx, int
   return (y & 1) ? 0.5f * s : exp_v(s, e[1]);
 }
 
-template <typename T, bool FINAL>
-__global__ void __launch_bounds__(kBtThreads) k_blend_tail(const BlendTailItem one, PanoArg po) {
+template <typename T, bool FINAL, bool KARG>
+__global__ void __launch_bounds__(kBtThreads) k_blend_tail(const BlendTailItem* __restrict__ items, int nitems,
+                                                           const BlendTailItem one, PanoArg po) {
   __shared__ float sB[kB1 + kB2 + kB3];       // levels 1, 2, 3: [channel][row][column]
   const int tid = threadIdx.x;
   const int t = (int)blockIdx.x;
-  const CST BlendTailItem& it = *(const CST BlendTailItem*)&one;
-  touch(&it);
-  const int tyi = t / it.tiles_x, txi = t - tyi * it.tiles_x;
+  const CST BlendTailItem* itp;
+  if (KARG) {
+    itp = (const CST BlendTailItem*)&one;
+  } else {
+    int lo = 0, hi = nitems - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (cst(items)[mid].tile_begin <= t) lo = mid; else hi = mid - 1;
+    }
+    itp = cst(items) + lo;
+  }
+  const CST BlendTailItem& it = *itp;
+  touch(itp);
+  const int lt = t - it.tile_begin, tyi = lt / it.tiles_x, txi = lt - tyi * it.tiles_x;
   const int X0 = txi * kBlendTX, Y0 = tyi * kBlendTY;
   const int depth = it.depth;
   const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2189,15 +2201,26 @@ hipError_t launch_tail(bool f16, const TailItem* items_dev, int nitems, int tota
   return hipGetLastError();
 }
 
-hipError_t launch_blend_tail(bool f16, bool final_level, const BlendTailItem& item, const PanoArg& po, hipStream_t s) {
-  const dim3 grid(item.lev[0].tiles_x * item.lev[0].tiles_y), block(kBtThreads);
-  if (f16) {
-    if (final_level) hipLaunchKernelGGL((k_blend_tail<_Float16, true>), grid, block, 0, s, item, po);
-    else hipLaunchKernelGGL((k_blend_tail<_Float16, false>), grid, block, 0, s, item, po);
+hipError_t launch_blend_tail(bool f16, bool final_level, const BlendTailItem* items_dev, int nitems, int total_tiles,
+                             const PanoArg& po, hipStream_t s, const BlendTailItem* one) {
+  if (total_tiles <= 0) return hipSuccess;
+  const dim3 grid(total_tiles), block(kBtThreads);
+  BlendTailItem k1;
+  if (one) k1 = *one;
+  else std::memset(&k1, 0, sizeof k1);
+#define STITCH_BTAIL(TT, FIN, KA) \
+  hipLaunchKernelGGL((k_blend_tail<TT, FIN, KA>), grid, block, 0, s, items_dev, nitems, k1, po)
+  if (!one) {                        // a batch's middle levels
+    if (f16) STITCH_BTAIL(_Float16, false, false);
+    else STITCH_BTAIL(float, false, false);
+  } else if (f16) {
+    if (final_level) STITCH_BTAIL(_Float16, true, true);
+    else STITCH_BTAIL(_Float16, false, true);
   } else {
-    if (final_level) hipLaunchKernelGGL((k_blend_tail<float, true>), grid, block, 0, s, item, po);
-    else hipLaunchKernelGGL((k_blend_tail<float, false>), grid, block, 0, s, item, po);
+    if (final_level) STITCH_BTAIL(float, true, true);
+    else STITCH_BTAIL(float, false, true);
   }
+#undef STITCH_BTAIL
   return hipGetLastError();
 }
 

@@ -463,11 +463,13 @@ void set_visible(BlendCam& c, int W, int H) {
 // workgroups costs its fixed 5-10 us; the single launch costs about as much once, plus its
 // tiles' halos: three and a half times the finest level's samples for a pyramid tail.  The
 // lines lie where that work reaches what the launches saved (four 1080p cameras, whole frame:
-// 194 us with both lines at 80 thousand, 183 at 300 to 400 thousand, 185 at a million; batches,
-// whose levels are larger together, at best gained 2% from the blends' and lost up to 5% to
-// the pyramids', and go level by level).
-constexpr int64_t kTailSamples = 400000;       // finest level's samples, all cameras
-constexpr int64_t kBlendTailPixels = 1200000;  // finest level's canvas
+// 194 us with both lines at 80 thousand, 183 at 300 to 400 thousand, 185 at a million).  A batch
+// counts all its jobs together (three jobs of 200 to 400 columns: 61 us level by level, 47 with
+// both; eight of 640 to 3840, where only the last levels are within the lines, 747 and 742; a
+// pyramid tail of up to ten million samples made these 818, and five of 321 to 1283 columns 173
+// where level by level took 165).
+constexpr int64_t kTailSamples = 400000;       // finest levels' samples, all cameras
+constexpr int64_t kBlendTailPixels = 1200000;  // finest levels' canvases
 
 // stitch_pyramid: a level of more samples (of all channels) than this is reduced in a launch of its
 // own, with a single level's halo.  Three 1080p cameras' pyramids, FP16, of 6.2 million samples an
@@ -982,8 +984,9 @@ stitch_status stitch_blend(int32_t n, const stitch_levels* bands, const stitch_l
   }
   int k_top = L - 1;
   if (k_tail >= 0) {
-    const hipError_t e = launch_blend_tail(dt == STITCH_F16, k_tail == 0, blend_tail_item(items, k_tail, L),
-                                           PanoArg{nullptr, 0}, s);
+    const BlendTailItem bt = blend_tail_item(items, k_tail, L);
+    const hipError_t e = launch_blend_tail(dt == STITCH_F16, k_tail == 0, nullptr, 1,
+                                           items[k_tail].tiles_x * items[k_tail].tiles_y, PanoArg{nullptr, 0}, s, &bt);
     if (e != hipSuccess) return hip_fail(e, "blend launch");
     k_top = k_tail - 1;
   }
@@ -1320,7 +1323,9 @@ stitch_status stitch_frame(stitch_plan* p, const stitch_image* frames, stitch_im
   const PanoArg po{(uint8_t*)pano->data, pano->row_pitch};
   int k_top = L - 1;
   if (p->btail_k >= 0) {
-    e = launch_blend_tail(f16, p->btail_k == 0, p->btail, p->btail_k == 0 ? po : PanoArg{nullptr, 0}, s);
+    const BlendItem& bi = p->bitems[p->btail_k];
+    e = launch_blend_tail(f16, p->btail_k == 0, nullptr, 1, bi.tiles_x * bi.tiles_y,
+                          p->btail_k == 0 ? po : PanoArg{nullptr, 0}, s, &p->btail);
     if (e != hipSuccess) return hip_fail(e, "blend tail launch");
     if ((st = mark(p->btail_k == 0 ? 2 : 4))) return st;
     k_top = p->btail_k - 1;
@@ -1448,6 +1453,12 @@ struct stitch_batch {
   std::vector<BlendItem> blend[kMaxLevels];
   int blend_tiles[kMaxLevels] = {};
   size_t off_blend[kMaxLevels] = {};
+  // the small levels of the jobs that have a tail, in one launch each way (tail_kind,
+  // btail_kind: the finest level among them, for the timing)
+  std::vector<TailItem> tail;
+  std::vector<BlendTailItem> btail;
+  int tail_tiles = 0, btail_tiles = 0, tail_kind = 0, btail_kind = 0;
+  size_t off_tail = 0, off_btail = 0;
   std::vector<int> frame_item;                // per job and camera: index into pyr[0] (or -1)
   std::vector<int> frame_job, frame_cam;
   size_t ws_bytes = 0;
@@ -1497,6 +1508,18 @@ stitch_status enqueue_phases(stitch_batch* b, hipStream_t s, int k_first, int k_
                                     (int)b->pyr[k].size(), b->pyr_tiles[k], fa, s, b->wg_cap[k]);
     if (e != hipSuccess) return hip_fail(e, "batch pyramid launch");
     st = b->timing.mark(s, k);
+  }
+  if (blends && !st && b->tail_tiles > 0) {
+    const hipError_t e = launch_tail(b->f16, (const TailItem*)(b->ws + b->off_tail), (int)b->tail.size(), b->tail_tiles,
+                                     4, s);
+    if (e != hipSuccess) return hip_fail(e, "batch pyramid tail launch");
+    st = b->timing.mark(s, b->tail_kind);
+  }
+  if (blends && !st && b->btail_tiles > 0) {
+    const hipError_t e = launch_blend_tail(b->f16, false, (const BlendTailItem*)(b->ws + b->off_btail),
+                                           (int)b->btail.size(), b->btail_tiles, PanoArg{nullptr, 0}, s);
+    if (e != hipSuccess) return hip_fail(e, "batch blend tail launch");
+    st = b->timing.mark(s, kMaxLevels + b->btail_kind);
   }
   for (int k = b->maxL - 1; blends && !st && k >= 0; --k) {
     if (b->blend_tiles[k] <= 0) continue;
@@ -1587,6 +1610,10 @@ stitch_status batch_prepare(stitch_batch* b, const stitch_image* const* frames, 
                          "batch table upload");
     if (st) return st;
   }
+  stitch_status st = upload(b->ws + b->off_tail, b->tail.data(), b->tail.size() * sizeof(TailItem), s, "batch table upload");
+  if (!st)
+    st = upload(b->ws + b->off_btail, b->btail.data(), b->btail.size() * sizeof(BlendTailItem), s, "batch table upload");
+  if (st) return st;
   b->uploaded = true;
   return STITCH_OK;
 }
@@ -1810,9 +1837,51 @@ stitch_status stitch_batch_create(int32_t njobs, stitch_plan* const* plans, stit
     b->plans.push_back(p);
     b->maxL = std::max(b->maxL, p->L);
   }
+  // the jobs' tails: the deepest ones whose finest levels together are within the limit (level 0's
+  // blend, which writes a panorama a job, keeps its own launch)
+  std::vector<int> tail_k(njobs, -1), btail_k(njobs, -1);
+  for (int steps = kTailDepth; steps >= 2; --steps) {
+    int64_t total = 0;
+    for (int j = 0; j < njobs; ++j) {
+      const stitch_plan* p = b->plans[j];
+      const int k = std::max(1, p->L - 1 - steps);
+      tail_k[j] = p->L - 1 - k >= 2 ? k : -1;
+      if (tail_k[j] >= 0)
+        for (const CamPlan& c : p->cam) total += (int64_t)c.roi[k].w * c.roi[k].h;
+    }
+    if (total <= kTailSamples) break;
+    std::fill(tail_k.begin(), tail_k.end(), -1);
+  }
+  for (int steps = kTailDepth; steps >= 1; --steps) {
+    int64_t total = 0;
+    for (int j = 0; j < njobs; ++j) {
+      const stitch_plan* p = b->plans[j];
+      const int k = std::max(1, p->L - 1 - steps);
+      btail_k[j] = p->L - 1 - k >= 1 ? k : -1;
+      if (btail_k[j] >= 0) total += (int64_t)p->dw[k] * p->dh[k];
+    }
+    if (total <= kBlendTailPixels) break;
+    std::fill(btail_k.begin(), btail_k.end(), -1);
+  }
+  b->tail_kind = b->btail_kind = kMaxLevels - 1;
+  for (int j = 0; j < njobs; ++j) {
+    const stitch_plan* p = b->plans[j];
+    if (tail_k[j] >= 0) {
+      for (size_t q = 0; q < p->items[tail_k[j]].size(); ++q)
+        push_tail(b->tail, b->tail_tiles, tail_item(p->items, tail_k[j], p->L - 1 - tail_k[j], q));
+      b->tail_kind = std::min(b->tail_kind, tail_k[j]);
+    }
+    if (btail_k[j] >= 0) {
+      BlendTailItem t = blend_tail_item(p->bitems, btail_k[j], p->L);
+      t.tile_begin = b->btail_tiles;
+      b->btail_tiles += t.tiles_x * t.lev[0].tiles_y;
+      b->btail.push_back(t);
+      b->btail_kind = std::min(b->btail_kind, btail_k[j]);
+    }
+  }
   for (int j = 0; j < njobs; ++j) {
     stitch_plan* p = b->plans[j];
-    for (int k = 0; k + 1 < p->L; ++k)
+    for (int k = 0; k + 1 < p->L && k != tail_k[j]; ++k)
       for (size_t q = 0; q < p->items[k].size(); ++q) {
         PyrItem it = p->items[k][q];
         it.tile_begin = b->pyr_tiles[k];
@@ -1837,7 +1906,7 @@ stitch_status stitch_batch_create(int32_t njobs, stitch_plan* const* plans, stit
   for (int k = 0; k < b->maxL; ++k)
     for (int j = 0; j < njobs; ++j) {
       stitch_plan* p = b->plans[j];
-      if (k >= p->L) continue;
+      if (k >= p->L || (btail_k[j] >= 0 && k >= btail_k[j])) continue;
       BlendItem bi = p->bitems[k];
       bi.tile_begin = b->blend_tiles[k];
       b->blend_tiles[k] += bi.tiles_x * bi.tiles_y;
@@ -1848,10 +1917,15 @@ stitch_status stitch_batch_create(int32_t njobs, stitch_plan* const* plans, stit
     b->off_pyr[k] = lay.take(std::max<size_t>(1, b->pyr[k].size()) * sizeof(PyrItem));
     b->off_blend[k] = lay.take(std::max<size_t>(1, b->blend[k].size()) * sizeof(BlendItem));
   }
+  b->off_tail = lay.take(b->tail.size() * sizeof(TailItem));
+  b->off_btail = lay.take(b->btail.size() * sizeof(BlendTailItem));
   b->own_bytes = lay.top;
   // room for the tables of up to kMaxGroups groups (stitch_batch_set_groups): together they
   // hold every item once, plus each group's per-level alignment
-  b->ws_bytes = 2 * b->own_bytes + (size_t)kMaxGroups * 2 * kMaxLevels * 256;
+  // (a group may take deeper tails than the whole batch: room for every job's and camera's)
+  b->ws_bytes = 2 * b->own_bytes + (size_t)kMaxGroups * (2 * kMaxLevels + 2) * 256 + (size_t)njobs * sizeof(BlendTailItem);
+  for (int j = 0; j < njobs; ++j) b->ws_bytes += (size_t)plans[j]->n * sizeof(TailItem);
+  b->ws_bytes = (size_t)align_up((int64_t)b->ws_bytes, 256);
   *out = b;
   b = nullptr;
   return STITCH_OK;

@@ -105,7 +105,7 @@ struct TailItem {
 };
 // Collapse of the levels lev[depth] (the top) .. lev[0] of one panorama in one launch.
 struct BlendTailItem {
-  int32_t tiles_x, depth;
+  int32_t tile_begin, tiles_x, depth, pad;
   BlendItem lev[kTailDepth + 1];
 };
 
@@ -134,7 +134,9 @@ hipError_t launch_blend(bool f16, bool final_level, const BlendItem* items_dev, 
 // single item passed by value.  final_level as for launch_blend (lev[0] is level 0).
 hipError_t launch_tail(bool f16, const TailItem* items_dev, int nitems, int total_tiles, int nslot, hipStream_t s,
                        const TailItem* one = nullptr);
-hipError_t launch_blend_tail(bool f16, bool final_level, const BlendTailItem& item, const PanoArg& po, hipStream_t s);
+// (a table of several blend tails: middle levels only)
+hipError_t launch_blend_tail(bool f16, bool final_level, const BlendTailItem* items_dev, int nitems, int total_tiles,
+                             const PanoArg& po, hipStream_t s, const BlendTailItem* one = nullptr);
 hipError_t launch_warp(bool f16, const uint8_t* src, int64_t src_row, int w, int h, const float* hinv9,
                        int roi_x, int roi_y, void* dst, int64_t dst_row, int64_t dst_plane, int dw, int dh,
                        hipStream_t s);
