@@ -84,9 +84,12 @@ KERNEL_KINDS = {
     "k_blend<_Float16, true, false>": "blend_level0, batched (f16)",
     "k_blend<_Float16, false, false>": "blend_middle/top, batched (f16)",
     "k_tail<float, false>": "level_pass (f32), small levels", "k_tail<_Float16, false>": "level_pass (f16), small levels",
-    "k_blend_tail<float, false>": "blend_middle/top (f32), small levels",
-    "k_blend_tail<_Float16, false>": "blend_middle/top (f16), small levels",
-    "k_blend_tail<float, true>": "blend of every level (f32)", "k_blend_tail<_Float16, true>": "blend of every level (f16)",
+    "k_blend_tail<float, false, false>": "blend_middle/top, batched (f32), small levels",
+    "k_blend_tail<_Float16, false, false>": "blend_middle/top, batched (f16), small levels",
+    "k_blend_tail<float, false, true>": "blend_middle/top (f32), small levels",
+    "k_blend_tail<_Float16, false, true>": "blend_middle/top (f16), small levels",
+    "k_blend_tail<float, true, true>": "blend of every level (f32)",
+    "k_blend_tail<_Float16, true, true>": "blend of every level (f16)",
     "k_lorb_clear": "L-ORB clear", "k_lorb_detect": "L-ORB detect (FAST, R, suppression)",
     "k_lorb_select": "L-ORB select (histogram threshold)", "k_lorb_rank": "L-ORB rank",
     "k_lorb_brief": "L-ORB BRIEF",
