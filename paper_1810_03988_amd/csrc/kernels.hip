@@ -1152,7 +1152,8 @@ __global__ void __launch_bounds__(kThreads) k_blend(const BlendItem* __restrict_
   const int X = X0 + 4 * m, Y = Y0 + y;
   // One camera's band and weight samples of the four pixels, as read; used after the coarse
   // stage.  Its descriptor is read once (scalar loads issued together), offsets are 32-bit (the
-  // host keeps every band and weight plane under 2^31 elements and its rows under 2^23).
+  // host keeps every band and weight plane under 2^31 elements and its rows under 2^23); a weight's
+  // place in bytes is not (2^30 FP32 samples are 2^32 bytes).
   struct CamSamples {
     Quad<T> l[3], w;        // (byte weights: w.d[0])
     bool in, u8;
@@ -1169,7 +1170,7 @@ __global__ void __launch_bounds__(kThreads) k_blend(const BlendItem* __restrict_
     const GLB T* l = cg<T>(c.lap);
     const uint32_t wes = cs.u8 ? 1u : (uint32_t)sizeof(T);
     if (cs.in & (u0 == 0) & (u1 == 4)) {
-      cs.w.load_dwords(cg<uint8_t>(c.wgt) + woff * wes, cs.u8 ? 0 : 4);
+      cs.w.load_dwords(cg<uint8_t>(c.wgt) + (uint64_t)woff * wes, cs.u8 ? 0 : 4);
 #pragma unroll
       for (int ch = 0; ch < 3; ++ch) cs.l[ch].load(l + ((uint32_t)ch * (uint32_t)c.lap_plane + loff));
     } else if (cs.in) {
@@ -1180,7 +1181,7 @@ __global__ void __launch_bounds__(kThreads) k_blend(const BlendItem* __restrict_
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int v = min(max(u, u0), u1 - 1);
-        const GLB uint8_t* wp = cg<uint8_t>(c.wgt) + (woff + v) * wes;
+        const GLB uint8_t* wp = cg<uint8_t>(c.wgt) + (uint64_t)(woff + v) * wes;
 #pragma unroll
         for (int b = 0; b < (int)sizeof(T); ++b) wv[u][b] = wp[cs.u8 ? 0 : b];
 #pragma unroll
