@@ -1175,7 +1175,7 @@ __global__ void __launch_bounds__(kThreads) k_blend(const BlendItem* __restrict_
       for (int ch = 0; ch < 3; ++ch) cs.l[ch].load(l + ((uint32_t)ch * (uint32_t)c.lap_plane + loff));
     } else if (cs.in) {
       // the few quads across a window's edge, pixel by pixel: pixels outside repeat one inside,
-      // every read in flight, and then weigh 0
+      // every read in flight, and then count 0 (weight and sample: the one inside may be infinite)
       typename RawOf<T>::type lv[3][4];
       uint32_t wv[4][sizeof(T)];
 #pragma unroll
@@ -1199,7 +1199,7 @@ __global__ void __launch_bounds__(kThreads) k_blend(const BlendItem* __restrict_
         if (cs.u8) cs.w.d[0] |= ok ? wv[u][0] << (8 * u) : 0u;
         else cs.w.put(u, ok ? w : 0u);
 #pragma unroll
-        for (int ch = 0; ch < 3; ++ch) cs.l[ch].put(u, lv[ch][u]);
+        for (int ch = 0; ch < 3; ++ch) cs.l[ch].put(u, ok ? lv[ch][u] : 0);
       }
     }
   };
@@ -1780,7 +1780,7 @@ __global__ void __launch_bounds__(kBtThreads) k_blend_tail(const BlendTailItem* 
   auto add = [&](const Smp& s, float acc[3]) __attribute__((always_inline)) {
     const float w = !s.in ? 0.0f : s.u8 ? (float)s.w * kInv255 : from_raw((RawT)s.w);
 #pragma unroll
-    for (int ch = 0; ch < 3; ++ch) acc[ch] = acc[ch] + w * from_raw(s.l[ch]);
+    for (int ch = 0; ch < 3; ++ch) acc[ch] = __builtin_fmaf(w, s.in ? from_raw(s.l[ch]) : 0.0f, acc[ch]);
   };
 
   // ---- B of every level ----
