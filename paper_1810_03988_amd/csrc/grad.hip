@@ -373,13 +373,12 @@ __global__ void __launch_bounds__(kT) k_vreduce(const ReduceArgs a) {
   const int x = q.out.x + lx, y = q.out.y + ly;
   const double wt[5] = {0.0625, 0.25, 0.375, 0.25, 0.0625};
   int ox[5];
-  double wx[5];
+  bool in[5];             // (outside, the value counts 0, not its weight: a sample read there may be infinite)
 #pragma unroll
   for (int b = 0; b < 5; ++b) {
     const int i = fold1(2 * x + b - 2, a.nw) - q.in.x;
-    const bool in = i >= 0 && i < q.in.w;
-    ox[b] = in ? i : 0;
-    wx[b] = in ? wt[b] : 0.0;
+    in[b] = i >= 0 && i < q.in.w;
+    ox[b] = in[b] ? i : 0;
   }
   const int64_t plane = (int64_t)q.in.w * q.in.h, oplane = (int64_t)q.out.w * q.out.h;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -392,7 +391,12 @@ __global__ void __launch_bounds__(kT) k_vreduce(const ReduceArgs a) {
       const double* s = c < 3 ? q.g : q.gm;
       if (!s) continue;
       s += (c < 3 ? c * plane : 0) + (int64_t)i * q.in.w;
-      acc[c] += wt[u] * ((wx[0] * s[ox[0]] + wx[4] * s[ox[4]]) + (wx[1] * s[ox[1]] + wx[3] * s[ox[3]]) + wx[2] * s[ox[2]]);
+      double v[5];
+#pragma unroll
+      for (int b = 0; b < 5; ++b) v[b] = s[ox[b]];
+#pragma unroll
+      for (int b = 0; b < 5; ++b) v[b] = in[b] ? v[b] : 0.0;
+      acc[c] += wt[u] * ((wt[0] * v[0] + wt[4] * v[4]) + (wt[1] * v[1] + wt[3] * v[3]) + wt[2] * v[2]);
     }
   }
   const int64_t at = (int64_t)ly * q.out.w + lx;
@@ -496,12 +500,13 @@ __global__ void __launch_bounds__(kT) k_vexpandT(Img3 d, int nw, int nh, double*
   double acc[3] = {0.0, 0.0, 0.0};
   double wx[5];
   int ox[5];
+  bool in[5];             // (outside, the value counts 0, as in k_vreduce)
 #pragma unroll
   for (int b = 0; b < 5; ++b) {
     const int i = 2 * x + b - 2;
-    const bool in = i >= 0 && i < nw;
-    ox[b] = in ? i : 0;
-    wx[b] = in ? expand_coef(i, x, nw) : 0.0;
+    in[b] = i >= 0 && i < nw;
+    ox[b] = in[b] ? i : 0;
+    wx[b] = expand_coef(i, x, nw);
   }
 #pragma unroll
   for (int u = 0; u < 5; ++u) {
@@ -513,7 +518,7 @@ __global__ void __launch_bounds__(kT) k_vexpandT(Img3 d, int nw, int nh, double*
     for (int b = 0; b < 5; ++b) {
       double v[3];
       ld3(d, ox[b], i, v);
-      for (int c = 0; c < 3; ++c) t[c] += wx[b] * v[c];
+      for (int c = 0; c < 3; ++c) t[c] += wx[b] * (in[b] ? v[c] : 0.0);
     }
     for (int c = 0; c < 3; ++c) acc[c] += wy * t[c];
   }
@@ -556,11 +561,13 @@ __global__ void __launch_bounds__(kT) k_vdg(const DgArgs a) {
   if (q.fband.w > 0 && 2 * x + 2 >= q.fband.x && 2 * x - 2 < q.fband.x + q.fband.w) {
     double wx[5];
     int ix[5];
+    bool in[5];           // (outside, the product counts 0, as in k_vreduce)
 #pragma unroll
     for (int b = 0; b < 5; ++b) {
       const int i = 2 * x + b - 2;
       ix[b] = min(max(i, q.fband.x), q.fband.x + q.fband.w - 1);
-      wx[b] = i == ix[b] ? expand_coef(i, x, a.nw) : 0.0;
+      in[b] = i == ix[b];
+      wx[b] = expand_coef(i, x, a.nw);
     }
 #pragma unroll
     for (int u = 0; u < 5; ++u) {
@@ -574,7 +581,7 @@ __global__ void __launch_bounds__(kT) k_vdg(const DgArgs a) {
         double d[3];
         ld3(a.fdr, ix[b], i, d);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) s[c] += m * d[c];
+        for (int c = 0; c < 3; ++c) s[c] += m * (in[b] ? d[c] : 0.0);
       }
 #pragma unroll
       for (int c = 0; c < 3; ++c) t[c] += wy * s[c];
