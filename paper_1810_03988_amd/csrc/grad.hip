@@ -172,7 +172,8 @@ __device__ __forceinline__ void warp3(const VCam& c, int W, int X, int Y, double
 
 // ---------------------------------------------------------------------------- pyramids
 // EXPAND along one axis at fine index i of n: three coarse indices and weights (odd samples
-// have two taps; the middle weight is then 0).
+// have two taps: the first then stands twice, at half its weight each time, which changes no bit
+// of the sum; a third tap of weight 0 would make NaN of an infinity).
 struct Tap3 {
   int j[3];
   double w[3];
@@ -182,8 +183,8 @@ __device__ __forceinline__ Tap3 expand_taps(int i, int n) {
   if (i & 1) {
     t.j[0] = t.j[1] = i >> 1;
     t.j[2] = fold1(i + 1, n) >> 1;
-    t.w[0] = t.w[2] = 0.5;
-    t.w[1] = 0.0;
+    t.w[0] = t.w[1] = 0.25;
+    t.w[2] = 0.5;
   } else {
     t.j[0] = fold1(i - 2, n) >> 1;
     t.j[1] = i >> 1;
@@ -195,23 +196,24 @@ __device__ __forceinline__ Tap3 expand_taps(int i, int n) {
 }
 
 // Separable 3 x 3 sum over NP planes stored on box b: rows jy with weights wy, columns jx with
-// weights wx; positions outside the box count 0 (read from the nearest position inside, which
-// is another tap of the stencil or of no weight, so no read is under a condition).
+// weights wx; positions outside the box count 0 (read from the nearest position inside, so that
+// no read is under a condition, and then replaced, in the few waves that have any).
 template <int NP>
 __device__ __forceinline__ void stencil3(const double* __restrict__ g, const Box& b, const int jx[3],
-                                         const double wx_in[3], const int jy[3], const double wy_in[3], double e[NP]) {
+                                         const double wx[3], const int jy[3], const double wy[3], double e[NP]) {
   const int64_t plane = (int64_t)b.w * b.h;
   int ox[3];
   int64_t oy[3];
-  double wx[3], wy[3];
+  bool xin[3], yin[3], all = true;
 #pragma unroll
   for (int v = 0; v < 3; ++v) {
     const int i = jx[v] - b.x, k = jy[v] - b.y;
     ox[v] = min(max(i, 0), b.w - 1);
-    wx[v] = i == ox[v] ? wx_in[v] : 0.0;
+    xin[v] = i == ox[v];
     const int kc = min(max(k, 0), b.h - 1);
     oy[v] = (int64_t)kc * b.w;
-    wy[v] = k == kc ? wy_in[v] : 0.0;
+    yin[v] = k == kc;
+    all &= xin[v] & yin[v];
   }
   double q[NP][3][3];
 #pragma unroll
@@ -220,6 +222,14 @@ __device__ __forceinline__ void stencil3(const double* __restrict__ g, const Box
     for (int u = 0; u < 3; ++u)
 #pragma unroll
       for (int v = 0; v < 3; ++v) q[c][u][v] = g[c * plane + oy[u] + ox[v]];
+  if (!all) {
+#pragma unroll
+    for (int c = 0; c < NP; ++c)
+#pragma unroll
+      for (int u = 0; u < 3; ++u)
+#pragma unroll
+        for (int v = 0; v < 3; ++v) q[c][u][v] = xin[v] && yin[u] ? q[c][u][v] : 0.0;
+  }
 #pragma unroll
   for (int c = 0; c < NP; ++c) {
     e[c] = 0.0;
@@ -254,30 +264,34 @@ __device__ __forceinline__ double reduce_coef(int i, int j, int n) {
   return w;
 }
 
-// The coefficients of fine sample i in coarse samples j0 = (i - 1) >> 1 and the two after it:
-// away from the borders they depend on the parity alone.
-__device__ __forceinline__ void reduce_coefs(int i, int j0, int n, double w[3]) {
+// The coarse samples that fine sample i has a share in and its coefficients there: j0 = (i - 1) >> 1
+// and the two after it where i is even, the one after it where i is odd (j0 then stands twice, as
+// in expand_taps).  Away from the borders the coefficients depend on the parity alone.
+__device__ __forceinline__ void reduce_taps(int i, int n, int j[3], double w[3]) {
+  const int j0 = (i - 1) >> 1;                         // coarse ceil((i - 2) / 2)
   const bool odd = (i & 1) != 0;
-  w[0] = odd ? 0.25 : 0.0625;
-  w[1] = odd ? 0.25 : 0.375;
-  w[2] = odd ? 0.0 : 0.0625;
-  if (i < 3 || i > n - 4)
-    for (int v = 0; v < 3; ++v) w[v] = reduce_coef(i, j0 + v, n);
+  j[0] = j0;
+  j[1] = odd ? j0 : j0 + 1;
+  j[2] = odd ? j0 + 1 : j0 + 2;
+  w[0] = odd ? 0.125 : 0.0625;
+  w[1] = odd ? 0.125 : 0.375;
+  w[2] = odd ? 0.25 : 0.0625;
+  if (i < 3 || i > n - 4) {
+    for (int v = 0; v < 3; ++v) w[v] = reduce_coef(i, j[v], n);
+    if (odd) {
+      w[0] *= 0.5;
+      w[1] *= 0.5;
+    }
+  }
 }
 
 // REDUCE^T of three planes on box b (0 outside) of a coarse level, at fine sample (x, y).
 __device__ __forceinline__ void reduceT_at(const double* __restrict__ d, const Box& b, int x, int y, int nw, int nh,
                                            double e[3]) {
-  const int j0 = (x - 1) >> 1, i0 = (y - 1) >> 1;      // coarse ceil((x - 2) / 2) .. floor((x + 2) / 2)
   int jx[3], jy[3];
   double wx[3], wy[3];
-#pragma unroll
-  for (int v = 0; v < 3; ++v) {
-    jx[v] = j0 + v;
-    jy[v] = i0 + v;
-  }
-  reduce_coefs(x, j0, nw, wx);
-  reduce_coefs(y, i0, nh, wy);
+  reduce_taps(x, nw, jx, wx);
+  reduce_taps(y, nh, jy, wy);
   stencil3<3>(d, b, jx, wx, jy, wy, e);
 }
 

@@ -37,12 +37,31 @@ def _forward(fo):
     return R
 
 
+def _vjp(fo, u, direct):
+    L = fo.L
+    dR = [u]
+    for _ in range(L - 1):
+        dR.append(o.expand_T(dR[-1]))
+    out = []
+    for i, f in enumerate(fo.frames):
+        dL = [_mul(fo.gm[i][k], dR[k]) for k in range(L)]
+        g = dL[L - 1]
+        for k in range(L - 1, 0, -1):
+            g = (g if k == L - 1 else dL[k] + g) - o.expand_T(dL[k - 1])
+            g = o.reduce_T(g, *fo.dims[k - 1])
+        g = dL[0] + g if L > 1 else g
+        if direct is not None:
+            g = g + direct[i]
+        out.append(fo._warp_T(f, fo.M[i], fo.cells[i], g)[0])
+    return out
+
+
 def _agree(got, want, what):
     got = got.astype(np.float64)
     fin = np.isfinite(want)
     bad = np.argwhere(np.isfinite(got) != fin)
     assert bad.size == 0, f"{what}: {len(bad)} samples differ in being finite, first {bad[0]}: {want[tuple(bad[0])]}"
-    assert np.max(np.abs(got - want)[fin], initial=0.0) <= 1e-6 * max(1.0, np.max(np.abs(want[fin]), initial=0.0)), what
+    assert np.max(np.abs(got[fin] - want[fin]), initial=0.0) <= 1e-6 * max(1.0, np.max(np.abs(want[fin]), initial=0.0)), what
     inf = np.isinf(want)
     assert np.array_equal(got[inf], want[inf]), what
     assert fin.any() and not fin.all(), f"{what}: the case shows nothing"
@@ -50,6 +69,13 @@ def _agree(got, want, what):
 
 def _shift(x, y):
     return np.array([[1.0, 0.0, x], [0.0, 1.0, y], [0.0, 0.0, 1.0]])
+
+
+def _cuts(W, H, at):
+    m = np.zeros((2, H, W), np.uint8)
+    m[0, :, :at] = 255
+    m[1, :, at:] = 255
+    return [m[0], m[1]]
 
 
 @pytest.mark.parametrize("value", [NAN, INF])
@@ -80,3 +106,47 @@ def test_the_first_column_stays_left(L, value):
     got = plan.backward([torch.from_numpy(f).to(DEV)], torch.from_numpy(u).to(DEV))[0][0]
     assert not torch.isfinite(got[:, 23, :2]).any()
     assert torch.isfinite(got[:, :, W // 2:]).all()
+
+
+@pytest.mark.parametrize("value", [NAN, INF])
+@pytest.mark.parametrize("L, x", [(1, 9), (2, 0), (3, 0), (4, 0), (2, 77), (4, 40), (3, 118), (4, 117)])
+def test_upstream_gradient(L, x, value):
+    """A camera over the whole canvas."""
+    W, H = 119, 37
+    rng = np.random.default_rng(x)
+    f = rng.random((3, H, W)).astype(np.float32)
+    u = rng.normal(size=(3, H, W)).astype(np.float32)
+    u[:, 19, x] = value
+    masks = [np.full((H, W), 255, np.uint8)]
+    plan = P.Plan([(W, H)], [_shift(0.25, 0.5)], masks, W, H, L, bind=False)
+    fo = o.FrameVjpOracle([f.astype(np.float64)], [_shift(0.25, 0.5)], masks, W, H, L)
+    got = plan.backward([torch.from_numpy(f).to(DEV)], torch.from_numpy(u).to(DEV))[0]
+    with np.errstate(invalid="ignore"):
+        _agree(got[0].cpu().numpy(), _vjp(fo, u.astype(np.float64), None)[0], "d_frame")
+
+
+@pytest.mark.parametrize("value", [NAN, INF])
+@pytest.mark.parametrize("L", [2, 3, 4])
+@pytest.mark.parametrize("x", [150, 157, 159, 160, 163])
+def test_upstream_gradient_at_a_seam(x, L, value):
+    """Two frames over the whole canvas that meet at a seam, with direct terms: dG_0 is wanted beyond the
+    cameras' regions, whose dG_1 ends beside the seam."""
+    W, H = 333, 37
+    rng = np.random.default_rng(x)
+    frames = [rng.random((3, H, W)).astype(np.float32) for _ in range(2)]
+    Hs = [_shift(0.25, 0.5), _shift(-0.5, 0.25)]
+    u = rng.normal(size=(3, H, W)).astype(np.float32)
+    u[:, 18, x] = value
+    direct = [rng.normal(size=(3, H, W)).astype(np.float32) for _ in range(2)]
+    masks = _cuts(W, H, 160)
+    plan = P.Plan([(W, H)] * 2, Hs, masks, W, H, L, bind=False)
+    fo = o.FrameVjpOracle([f.astype(np.float64) for f in frames], Hs, masks, W, H, L)
+    dev = lambda v: torch.from_numpy(v).to(DEV)
+    got = plan.backward([dev(f) for f in frames], dev(u), [dev(d) for d in direct])[0]
+    with np.errstate(invalid="ignore"):
+        want = _vjp(fo, u.astype(np.float64), [d.astype(np.float64) for d in direct])
+    for i in range(2):
+        if np.isfinite(want[i]).all():
+            assert np.isfinite(got[i].cpu().numpy()).all(), i
+        else:
+            _agree(got[i].cpu().numpy(), want[i], f"d_frame {i}")
