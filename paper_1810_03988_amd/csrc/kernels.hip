@@ -1491,8 +1491,8 @@ __global__ void __launch_bounds__(kThreads) k_tail(const TailItem* __restrict__ 
     const int wx0 = X0 - 24, wy0 = Y0 - 22;
     // the rows that this depth reads (a shallower tail repeats the outermost ones: cheaper than
     // other windows for it)
-    const int rlo = KARG ? (it.depth == 0 ? 22 : it.depth == 1 ? 18 : it.depth == 2 ? 12 : 0) : 0;
-    const int rhi = KARG ? (it.depth == 0 ? 53 : it.depth == 1 ? 56 : it.depth == 2 ? 60 : kT0R - 1) : kT0R - 1;
+    const int rlo = KARG ? (it.depth == 1 ? 18 : it.depth == 2 ? 12 : 0) : 0;
+    const int rhi = KARG ? (it.depth == 1 ? 56 : it.depth == 2 ? 60 : kT0R - 1) : kT0R - 1;
     const int rx = l0.roi_x, ry = l0.roi_y, rw = l0.roi_w, rh = l0.roi_h, lw = l0.w, lh = l0.h;
     const int64_t row = img ? it.img_row : it.msk_row;
     const bool u8 = KARG && img && it.src_u8 != 0;
@@ -1694,6 +1694,38 @@ __global__ void __launch_bounds__(kThreads) k_tail(const TailItem* __restrict__ 
     f = g;
     c += cr * cs;
     fs = cs; fr = cr; fx = cx; fy = cy;
+  }
+}
+
+// ------------------------------------------------------------------------------------
+// stitch_pyramid's level 0 where no level is reduced from it in the same launch: four adjacent samples
+// of one row and channel a thread, converted as k_tail converts them.  Bound by memory: three
+// channels of 4000x3000, FP16, 25.5 us (38 with a sample a thread, 68 as a k_tail of no steps, which
+// stages the halo of three); FP32 47 (67 and 78); 8192x4096 bytes to FP16 19.7 (53 and 72).
+template <typename T, bool U8>
+__global__ void __launch_bounds__(kThreads) k_level0(const void* __restrict__ s, int64_t srow, int64_t splane,
+                                                     T* __restrict__ d, int64_t drow, int64_t dplane, int w, int h) {
+  const int x = 4 * ((int)blockIdx.x * 64 + ((int)threadIdx.x & 63));
+  const int y = (int)blockIdx.y * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  if (x >= w || y >= h) return;
+  const int64_t from = (int64_t)blockIdx.z * splane + (int64_t)y * srow + x;
+  GLB T* to = mg<T>(d) + (int64_t)blockIdx.z * dplane + (int64_t)y * drow + x;
+  if (x + 3 < w) {
+    float v[4];
+    if (U8) {
+      const uint32_t b = *reinterpret_cast<const GLB u32_unaligned*>(cg<uint8_t>(s) + from);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = byte_as_stored((b >> (8 * u)) & 255u, T());
+    } else {
+      Quad<T> q;
+      q.load(cg<T>(s) + from);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = q.at(u);
+    }
+    store4_any(to, v);
+  } else {
+    for (int u = 0; x + u < w; ++u)
+      stg(to, u, U8 ? one_sample(cg<uint8_t>(s), from + u, T()) : one_sample(cg<T>(s), from + u, T()));
   }
 }
 
@@ -2247,6 +2279,21 @@ hipError_t launch_warp_coords(const float* hinv9, int roi_x, int roi_y, float* d
   for (int i = 0; i < 9; ++i) hi.h[i] = hinv9[i];
   const dim3 grid((dw + 63) / 64, (dh + 3) / 4), block(kThreads);
   hipLaunchKernelGGL(k_warp_coords, grid, block, 0, s, hi, roi_x, roi_y, dst, row, plane, dw, dh);
+  return hipGetLastError();
+}
+
+hipError_t launch_level0(bool f16, bool u8, int nch, const Planes& src, const Planes& out, int w, int h, hipStream_t s) {
+  const dim3 grid((w + 255) / 256, (h + 3) / 4, nch), block(kThreads);
+#define STITCH_LEVEL0(TT, U)                                                                                         \
+  hipLaunchKernelGGL((k_level0<TT, U>), grid, block, 0, s, src.data, src.row, src.plane, (TT*)out.data, out.row, out.plane, w, h)
+  if (f16) {
+    if (u8) STITCH_LEVEL0(_Float16, true);
+    else STITCH_LEVEL0(_Float16, false);
+  } else {
+    if (u8) STITCH_LEVEL0(float, true);
+    else STITCH_LEVEL0(float, false);
+  }
+#undef STITCH_LEVEL0
   return hipGetLastError();
 }
 

@@ -805,6 +805,16 @@ stitch_status stitch_pyramid(const stitch_image* g0, int32_t kind, stitch_levels
     int depth = std::min(kTailDepth, L - 1 - k);
     if (!apart) depth = src0 ? 0 : std::min(depth, 1);
     else if ((int64_t)f.width * f.height * nch > kStageSamples) depth = std::min(depth, 1);
+    if (depth == 0) {
+      if (src0) {
+        e = launch_level0(f16, u8, nch, Planes{g0->data, g0->row_pitch / ges, g0->plane_pitch / ges}, planes(f), f.width,
+                          f.height, s);
+        if (e != hipSuccess) return hip_fail(e, "level-0 launch");
+      }
+      if (L == 1) break;
+      alias0 = true;
+      continue;
+    }
     TailItem t;
     std::memset(&t, 0, sizeof t);
     t.depth = depth;
@@ -843,12 +853,9 @@ stitch_status stitch_pyramid(const stitch_image* g0, int32_t kind, stitch_levels
     t.tile_y0 = (int)(y0 & ~(int64_t)7);
     t.tiles_x = (int)((x1 - t.tile_x0 + kTailTX - 1) / kTailTX);
     const int tiles_y = (int)((y1 - t.tile_y0 + kTailTY - 1) / kTailTY);
-    if (depth > 0 || t.copy_out) {
-      e = launch_tail(f16, nullptr, 1, t.tiles_x * tiles_y, nch, s, &t);
-      if (e != hipSuccess) return hip_fail(e, "pyramid launch");
-    }
-    if (depth > 0) k += depth;
-    else if (L == 1) break;
+    e = launch_tail(f16, nullptr, 1, t.tiles_x * tiles_y, nch, s, &t);
+    if (e != hipSuccess) return hip_fail(e, "pyramid launch");
+    k += depth;
     alias0 = true;
   }
   for (int k = 0; kind == 1 && k + 1 < L; ++k) {

@@ -147,6 +147,8 @@ struct Planes {
   void* data;
   int64_t row, plane;
 };
+// out = src, converted where src holds bytes (strides of src in its own elements).
+hipError_t launch_level0(bool f16, bool u8, int nch, const Planes& src, const Planes& out, int w, int h, hipStream_t s);
 // out = fine - EXPAND(coarse), out's rectangle being fine's (out may be fine).
 hipError_t launch_expand_sub(bool f16, int nch, const Planes& fine, const Planes& out, int fx, int fy, int fw, int fh,
                              const Planes& coarse, int cx, int cy, int cw, int ch, int canvas_w, int canvas_h,
