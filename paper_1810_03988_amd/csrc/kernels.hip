@@ -20,6 +20,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstring>
+#include <type_traits>
 
 #include "stitch_internal.h"
 
@@ -1152,8 +1153,8 @@ __global__ void __launch_bounds__(kThreads) k_blend(const BlendItem* __restrict_
   const int X = X0 + 4 * m, Y = Y0 + y;
   // One camera's band and weight samples of the four pixels, as read; used after the coarse
   // stage.  Its descriptor is read once (scalar loads issued together), offsets are 32-bit (the
-  // host keeps every band and weight plane under 2^31 elements and its rows under 2^23); a weight's
-  // place in bytes is not (2^30 FP32 samples are 2^32 bytes).
+  // host keeps every band and weight plane under 2^31 elements and its rows under 2^23); an FP32
+  // weight's place in bytes is not (2^30 samples are 2^32 bytes).
   struct CamSamples {
     Quad<T> l[3], w;        // (byte weights: w.d[0])
     bool in, u8;
@@ -1168,9 +1169,10 @@ __global__ void __launch_bounds__(kThreads) k_blend(const BlendItem* __restrict_
     const uint32_t loff = __umul24((uint32_t)ly, (uint32_t)c.lap_row) + (uint32_t)lx;
     const uint32_t woff = __umul24((uint32_t)wy, (uint32_t)c.wgt_row) + (uint32_t)wx;
     const GLB T* l = cg<T>(c.lap);
-    const uint32_t wes = cs.u8 ? 1u : (uint32_t)sizeof(T);
+    using Bytes = std::conditional_t<sizeof(T) == 4, uint64_t, uint32_t>;
+    const Bytes wes = cs.u8 ? 1 : sizeof(T);
     if (cs.in & (u0 == 0) & (u1 == 4)) {
-      cs.w.load_dwords(cg<uint8_t>(c.wgt) + (uint64_t)woff * wes, cs.u8 ? 0 : 4);
+      cs.w.load_dwords(cg<uint8_t>(c.wgt) + woff * wes, cs.u8 ? 0 : 4);
 #pragma unroll
       for (int ch = 0; ch < 3; ++ch) cs.l[ch].load(l + ((uint32_t)ch * (uint32_t)c.lap_plane + loff));
     } else if (cs.in) {
@@ -1181,7 +1183,7 @@ __global__ void __launch_bounds__(kThreads) k_blend(const BlendItem* __restrict_
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int v = min(max(u, u0), u1 - 1);
-        const GLB uint8_t* wp = cg<uint8_t>(c.wgt) + (uint64_t)(woff + v) * wes;
+        const GLB uint8_t* wp = cg<uint8_t>(c.wgt) + (woff + v) * wes;
 #pragma unroll
         for (int b = 0; b < (int)sizeof(T); ++b) wv[u][b] = wp[cs.u8 ? 0 : b];
 #pragma unroll
