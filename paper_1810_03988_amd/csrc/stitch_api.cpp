@@ -469,18 +469,38 @@ void set_visible(BlendCam& c, int W, int H) {
 // pyramid tail of up to ten million samples made these 818, and five of 321 to 1283 columns 173
 // where level by level took 165).
 constexpr int64_t kTailSamples = 400000;       // finest levels' samples, all cameras
-constexpr int64_t kBlendTailPixels = 1200000;  // finest levels' canvases
+// Blends: one step saves one launch only, and level 0 costs the most (the panorama, and every sample
+// read by itself where the level blend reads four), so these have a lower line.  Whole frames, 3
+// levels, from level 0: a canvas of 311 thousand pixels 31.2 us for 37.0 level by level, of 540
+// thousand (eight cameras over the whole of it, FP16) 89.7 for 93.0, of 553 thousand (a pair) 36.9 for
+// 35.6 but one launch less for the host (a pair's single stages, bound by it: 199 for 203), of 864
+// thousand 41.5 for 39.2, of 1.08 million 78.5 for 71.4, and 158 for 138 with eight cameras.
+// One step from level 1: 550 to 930 thousand within 2% either way (FP16, 800 thousand: 127 for
+// 125).  Two or three steps from level 1: 660 thousand 82.8 for 85.4, 930 thousand 97.4 for 98.5;
+// six jobs of 300 to 900 columns, 1.1 million together, 124 for 131.
+constexpr int64_t kBlendTailNear = 600000;     // canvas of level 0, or of a level with one step
+constexpr int64_t kBlendTailFar = 1200000;     // of a coarser level with more
 
 // stitch_pyramid: a level of more samples (of all channels) than this is reduced in a launch of its
 // own, with a single level's halo.  Three 1080p cameras' pyramids, FP16, of 6.2 million samples an
 // image and 2.1 a weight map: line below both 391-420 us, between them 371, above both 392.
 constexpr int64_t kStageSamples = 3000000;
 
-// First level >= k_min of a tail over levels .. L-1 whose size (given per level) is within
-// `limit` and which covers at least `least` steps; -1: none.
-int tail_start(int L, const int64_t* size, int k_min, int least, int64_t limit) {
-  for (int k = std::max(k_min, L - 1 - kTailDepth); k <= L - 1 - least; ++k)
-    if (size[k] <= limit) return k;
+// First level of a pyramid tail over levels .. L-1, of two steps or more (samples given per
+// level); -1: none.
+int tail_start(int L, const int64_t* samples) {
+  for (int k = std::max(1, L - 1 - kTailDepth); k <= L - 3; ++k)
+    if (samples[k] <= kTailSamples) return k;
+  return -1;
+}
+
+// The line for a blend tail from level k over `steps` steps.
+int64_t blend_tail_line(int k, int steps) { return k == 0 || steps == 1 ? kBlendTailNear : kBlendTailFar; }
+
+// First level of a panorama's blend tail (canvases given per level); -1: none.
+int blend_tail_start(int L, const int64_t* canvas) {
+  for (int k = std::max(0, L - 1 - kTailDepth); k <= L - 2; ++k)
+    if (canvas[k] <= blend_tail_line(k, L - 1 - k)) return k;
   return -1;
 }
 
@@ -654,11 +674,11 @@ void build_tables(stitch_plan* p) {
   }
   p->tail.clear();
   p->tail_tiles = 0;
-  p->tail_k = tail_start(L, samples, 1, 2, kTailSamples);
+  p->tail_k = tail_start(L, samples);
   if (p->tail_k >= 0)
     for (size_t q = 0; q < p->items[p->tail_k].size(); ++q)
       push_tail(p->tail, p->tail_tiles, tail_item(p->items, p->tail_k, L - 1 - p->tail_k, q));
-  p->btail_k = L > 1 ? tail_start(L, canvas, 0, 1, kBlendTailPixels) : -1;
+  p->btail_k = blend_tail_start(L, canvas);
   if (p->btail_k >= 0) p->btail = blend_tail_item(p->bitems, p->btail_k, L);
 }
 
@@ -974,7 +994,7 @@ stitch_status stitch_blend(int32_t n, const stitch_levels* bands, const stitch_l
   // The small levels in one launch, where nothing it writes shares memory with what it reads.
   int64_t canvas[kMaxLevels];
   for (int k = 0; k < L; ++k) canvas[k] = (int64_t)dw[k] * dh[k];
-  int k_tail = L > 1 ? tail_start(L, canvas, 0, 1, kBlendTailPixels) : -1;
+  int k_tail = blend_tail_start(L, canvas);
   for (int k = k_tail; k_tail >= 0 && k < L; ++k) {
     if (!items[k].r_out) continue;
     const stitch_image& r = keep_r->level[k];
@@ -1867,7 +1887,7 @@ stitch_status stitch_batch_create(int32_t njobs, stitch_plan* const* plans, stit
       btail_k[j] = p->L - 1 - k >= 1 ? k : -1;
       if (btail_k[j] >= 0) total += (int64_t)p->dw[k] * p->dh[k];
     }
-    if (total <= kBlendTailPixels) break;
+    if (total <= blend_tail_line(1, steps)) break;
     std::fill(btail_k.begin(), btail_k.end(), -1);
   }
   b->tail_kind = b->btail_kind = kMaxLevels - 1;
