@@ -462,12 +462,11 @@ void set_visible(BlendCam& c, int W, int H) {
 // Where the small levels' single launches begin.  A level pass or blend of a few hundred
 // workgroups costs its fixed 5-10 us; the single launch costs about as much once, plus its
 // tiles' halos: three and a half times the finest level's samples for a pyramid tail.  The
-// lines lie where that work reaches what the launches saved (four 1080p cameras, whole frame:
-// 194 us with both lines at 80 thousand, 183 at 300 to 400 thousand, 185 at a million).  A batch
-// counts all its jobs together (three jobs of 200 to 400 columns: 61 us level by level, 47 with
-// both; eight of 640 to 3840, where only the last levels are within the lines, 747 and 742; a
-// pyramid tail of up to ten million samples made these 818, and five of 321 to 1283 columns 173
-// where level by level took 165).
+// lines lie where that work reaches what the launches saved.  Pyramids, over whole frames of 2 to 8
+// cameras (320x240 to 2000x1600, 3 to 7 levels) and batches of 2 to 16 jobs, 160 in all: a line of
+// 400 thousand samples is within 2% of each one's best; of 200 thousand at most 15% above it, of 1
+// million 10%, none at all 35%.  A batch counts all its jobs together (three jobs of 200 to 400
+// columns: 61 us level by level, 45 with both tails).
 constexpr int64_t kTailSamples = 400000;       // finest levels' samples, all cameras
 // Blends: one step saves one launch only, and level 0 costs the most (the panorama, and every sample
 // read by itself where the level blend reads four), so these have a lower line.  Whole frames, 3
@@ -482,8 +481,11 @@ constexpr int64_t kBlendTailNear = 600000;     // canvas of level 0, or of a lev
 constexpr int64_t kBlendTailFar = 1200000;     // of a coarser level with more
 
 // stitch_pyramid: a level of more samples (of all channels) than this is reduced in a launch of its
-// own, with a single level's halo.  Three 1080p cameras' pyramids, FP16, of 6.2 million samples an
-// image and 2.1 a weight map: line below both 391-420 us, between them 371, above both 392.
+// own, with a single level's halo.  Over 288 pyramids (77 thousand to 60 million samples; 1 and 3
+// channels; bytes, FP16, FP32; 2 to 6 levels; both kinds) this line is on average 0.9% and at most 9% above
+// each one's best; a line of 1 million 2.8% and 25%, 2 million 1.4% and 19%, 5 million 1.1% and 9%,
+// 8 million 1.7% and 20%, none 4.9% and 36%.  (1920x1080, three channels of FP16, 4 levels: 34 us a
+// level a launch, 30.5 with the first alone, 36 all together; 640x480: 18, -, 10.)
 constexpr int64_t kStageSamples = 3000000;
 
 // First level of a pyramid tail over levels .. L-1, of two steps or more (samples given per
