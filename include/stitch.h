@@ -223,7 +223,8 @@ stitch_status stitch_plan_read_timing(stitch_plan* plan, double ms[STITCH_TIMING
  * or 128) on wg_per_cu[k] persistent workgroups per compute unit (-1: one per tile, 0: as
  * many as fit, 1, 2).  Until set or tuned, the planner picks the tallest tile that leaves
  * about eight tiles per compute unit and as many workgroups as fit.  The results do not
- * depend on the settings.  stitch_plan_config reads them (0 for levels with no pass).
+ * depend on the settings.  Small levels whose passes share a launch keep theirs without using
+ * them.  stitch_plan_config reads them (0 for levels with no pass).
  * stitch_plan_set_config sets them (tile_rows[k] = 0 keeps pass k's height); on a bound plan
  * it uploads the changed tables on the stream and waits for them.  Errors: NULL, SHAPE,
  * DEVICE. */
@@ -233,11 +234,11 @@ stitch_status stitch_plan_set_config(stitch_plan* plan, const int32_t wg_per_cu[
                                      const int32_t tile_rows[STITCH_MAX_LEVELS], void* stream);
 /* Autotuner of the plain form (the paper sizes its thread grids by analysing the resources
  * an image needs, Sec. 4.3.2; here they are measured): times every (tile height, workgroups
- * per compute unit) pair of each pyramid pass of stitch_frame on these frames (U8 HWC, as for
- * stitch_frame) and keeps the fastest; synchronises the stream.  cache_path (optional): a
- * text file of earlier choices keyed by the device, the storage type and the plan's tile
- * counts; a hit skips the timing, a miss appends the new choice.  The choice survives a
- * rebind.  Errors: NULL, SHAPE, STATE (not bound), DEVICE. */
+ * per compute unit) pair of each pyramid pass that stitch_frame launches by itself on these
+ * frames (U8 HWC, as for stitch_frame) and keeps the fastest; synchronises the stream.
+ * cache_path (optional): a text file of earlier choices keyed by the device, the storage type
+ * and the plan's tile counts; a hit skips the timing, a miss appends the new choice.  The
+ * choice survives a rebind.  Errors: NULL, SHAPE, STATE (not bound), DEVICE. */
 stitch_status stitch_autotune(stitch_plan* plan, const stitch_image* frames, void* stream, const char* cache_path);
 
 void stitch_plan_destroy(stitch_plan* plan);

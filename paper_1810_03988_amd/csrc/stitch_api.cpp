@@ -1703,6 +1703,7 @@ struct PassTune {
   int* cap;                      // persistent workgroups per compute unit
   int64_t t16;                   // 16-row tiles of the pass (independent of sub)
   bool warp;                     // the level-0 pass (warp + pyramid)
+  bool launched;                 // false: its level is part of a pyramid tail
 };
 
 // Use sub_k sub-steps per tile: rewrite the host table and upload it (waited for, since
@@ -1719,8 +1720,9 @@ stitch_status apply_sub(PassTune& pt, int sub_k, hipStream_t s) {
 // Pick, per pass, the tile height (16 * sub rows, sub in 1, 2, 4, 8; the taller ones only
 // while the pass still has a tile per compute unit) and the workgroups per compute unit
 // (as many as fit, 1, 2, or one per tile) by timing every pair on the stream (the other
-// passes keep their settings).  cache_path: a text file of earlier choices keyed by the
-// device, the storage type, the form (salt) and every pass's 16-row tile count.
+// passes keep their settings, as do those that have no launch of their own).  cache_path: a text
+// file of earlier choices keyed by the device, the storage type, the form (salt) and every pass's
+// 16-row tile count.
 stitch_status tune_passes(int np, PassTune* passes, bool f16, const FrameArgs& fa, hipStream_t s,
                           const char* cache_path, uint64_t salt) {
   prepare_launches();
@@ -1779,7 +1781,7 @@ stitch_status tune_passes(int np, PassTune* passes, bool f16, const FrameArgs& f
   }
   for (int k = 0; k < np && !st; ++k) {
     PassTune& pt = passes[k];
-    if (pt.t16 <= 0) continue;
+    if (pt.t16 <= 0 || !pt.launched) continue;
     float best = 1e30f;
     int best_sub = *pt.sub, best_cap = 0;
     for (int sub_k : subs) {
@@ -2017,7 +2019,7 @@ stitch_status stitch_batch_autotune(stitch_batch* b, const stitch_image* const* 
   int np = 0;
   for (int k = 0; k + 1 < b->maxL; ++k)
     passes[np++] = PassTune{&b->pyr[k], b->ws + b->off_pyr[k], &b->pyr_tiles[k], &b->sub[k], &b->wg_cap[k],
-                            b->t16[k], k == 0};
+                            b->t16[k], k == 0, true};
   FrameArgs fa;
   std::memset(&fa, 0, sizeof fa);   // n = 0: frames come from the item tables
   st = tune_passes(np, passes, b->f16, fa, s, cache_path, 0x62617463ull /* batch */);
@@ -2192,7 +2194,7 @@ stitch_status stitch_autotune(stitch_plan* p, const stitch_image* frames, void* 
     int64_t t16 = 0;
     for (const PyrItem& it : p->items[k]) t16 += (int64_t)it.tiles_x * it.rows16;
     passes[np++] = PassTune{&p->items[k], p->ws + p->off_items[k], &p->tiles[k], &p->sub[k], &p->wg_cap[k], t16,
-                            k == 0};
+                            k == 0, p->tail_k < 0 || k < p->tail_k};
   }
   st = tune_passes(np, passes, p->storage == STITCH_F16, fa, (hipStream_t)stream, cache_path,
                    0x706c61696eull /* plain */);
