@@ -22,6 +22,7 @@
 #include <cstring>
 #include <type_traits>
 
+#include "kernarg.h"
 #include "stitch_internal.h"
 
 namespace stitch {
@@ -1461,7 +1462,7 @@ __device__ __forceinline__ float one_sample(const GLB uint8_t* p, int64_t i, T) 
 }
 
 template <typename T, bool KARG>
-__global__ void __launch_bounds__(kThreads) k_tail(const TailItem* __restrict__ items, int nitems, const TailItem one,
+__global__ void __launch_bounds__(kThreads) k_tail(const TailItem one, const TailItem* __restrict__ items, int nitems,
                                                    int nslot) {
   // sm: the finest window, then levels 1 and 2 as the next REDUCE reads them; sc: levels 1 .. 3
   // as reduced
@@ -1471,7 +1472,7 @@ __global__ void __launch_bounds__(kThreads) k_tail(const TailItem* __restrict__ 
   const int t = (int)blockIdx.x / nslot, slot = (int)blockIdx.x - t * nslot;
   const CST TailItem* itp;
   if (KARG) {
-    itp = (const CST TailItem*)&one;
+    itp = first_arg<TailItem>();
   } else {
     int lo = 0, hi = nitems - 1;
     while (lo < hi) {
@@ -1769,14 +1770,15 @@ __device__ __forceinline__ float expand_from(const float* r, int st, int nx, int
 }
 
 template <typename T, bool FINAL, bool KARG>
-__global__ void __launch_bounds__(kBtThreads) k_blend_tail(const BlendTailItem* __restrict__ items, int nitems,
-                                                           const BlendTailItem one, PanoArg po) {
+__global__ void __launch_bounds__(kBtThreads) k_blend_tail(const BlendTailItem one,
+                                                           const BlendTailItem* __restrict__ items, int nitems,
+                                                           PanoArg po) {
   __shared__ float sB[kB1 + kB2 + kB3];       // levels 1, 2, 3: [channel][row][column]
   const int tid = threadIdx.x;
   const int t = (int)blockIdx.x;
   const CST BlendTailItem* itp;
   if (KARG) {
-    itp = (const CST BlendTailItem*)&one;
+    itp = first_arg<BlendTailItem>();
   } else {
     int lo = 0, hi = nitems - 1;
     while (lo < hi) {
@@ -2227,8 +2229,8 @@ hipError_t launch_tail(bool f16, const TailItem* items_dev, int nitems, int tota
   else std::memset(&k1, 0, sizeof k1);
 #define STITCH_TAIL(TT)                                                                                  \
   do {                                                                                                   \
-    if (one) hipLaunchKernelGGL((k_tail<TT, true>), grid, block, 0, s, items_dev, nitems, k1, nslot);    \
-    else hipLaunchKernelGGL((k_tail<TT, false>), grid, block, 0, s, items_dev, nitems, k1, nslot);       \
+    if (one) hipLaunchKernelGGL((k_tail<TT, true>), grid, block, 0, s, k1, items_dev, nitems, nslot);    \
+    else hipLaunchKernelGGL((k_tail<TT, false>), grid, block, 0, s, k1, items_dev, nitems, nslot);       \
   } while (0)
   if (f16) STITCH_TAIL(_Float16);
   else STITCH_TAIL(float);
@@ -2244,7 +2246,7 @@ hipError_t launch_blend_tail(bool f16, bool final_level, const BlendTailItem* it
   if (one) k1 = *one;
   else std::memset(&k1, 0, sizeof k1);
 #define STITCH_BTAIL(TT, FIN, KA) \
-  hipLaunchKernelGGL((k_blend_tail<TT, FIN, KA>), grid, block, 0, s, items_dev, nitems, k1, po)
+  hipLaunchKernelGGL((k_blend_tail<TT, FIN, KA>), grid, block, 0, s, k1, items_dev, nitems, po)
   if (!one) {                        // a batch's middle levels
     if (f16) STITCH_BTAIL(_Float16, false, false);
     else STITCH_BTAIL(float, false, false);

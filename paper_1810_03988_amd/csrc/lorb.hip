@@ -41,6 +41,7 @@
 #include <mutex>
 #include <vector>
 
+#include "kernarg.h"
 #include "stitch_internal.h"
 
 using namespace stitch;
@@ -117,12 +118,11 @@ __device__ __forceinline__ int bucket(int64_t R) {
   return R > 0 ? kBins / 2 + 1 + k : kBins / 2 - 1 - k;
 }
 
-// Read one dword of every 64-byte line of the table that a block may need -- the head with the
-// first areas, and the frames -- at once, so that its fields, wanted one after another, come
-// from the scalar cache (each line's first read is a trip to memory otherwise).
-__device__ __forceinline__ void touch(const AreaTable& T) {
-  typedef const __attribute__((address_space(4))) int* ConstWords;
-  const ConstWords w = (ConstWords)&T;
+// Read one dword of every 64-byte line of the table (the kernel's first argument) that a block may
+// need -- the head with the first areas, and the frames -- at once, so that its fields, wanted one
+// after another, come from the scalar cache (each line's first read is a trip to memory otherwise).
+__device__ __forceinline__ void touch_first_arg() {
+  const auto* w = first_arg<int>();
   int any = 0;
 #pragma unroll
   for (int i = 0; i < 6; ++i) any |= w[16 * i];
@@ -145,7 +145,7 @@ __global__ void __launch_bounds__(256) k_lorb_detect(const AreaTable T, int tf, 
   const int tid = threadIdx.x;
   const int b = blockIdx.x;
   if (tid < 3) sCount[tid] = 0;
-  touch(T);
+  touch_first_arg();
   int z = 0;
   for (int i0 = 0; i0 < T.m; i0 += 8) {                // eight areas' reads in flight
     int first[8], n[8];
