@@ -129,8 +129,8 @@ stitch_status stitch_warp_coords(const double H[9], int32_t roi_x, int32_t roi_y
  * planes must span fewer than 2^31 elements and its rows fewer than 2^23 (SHAPE
  * otherwise: the kernels address levels with 32-bit offsets).
  * workspace: device memory of stitch_pyramid_workspace_bytes(levels) bytes, 256-byte
- * aligned, holding the launch tables (calls that may overlap must not share it; the
- * table upload comes from pageable host memory and may wait for the stream).
+ * aligned, required for two levels or more; nothing is written to it (the launches carry
+ * their descriptors), so calls may share it.
  * Errors: NULL, SHAPE, LEVELS, WORKSPACE, UNSUPPORTED, DEVICE. */
 size_t        stitch_pyramid_workspace_bytes(int32_t levels);
 stitch_status stitch_pyramid(const stitch_image* g0, int32_t kind, stitch_levels* out, void* workspace,
@@ -147,8 +147,8 @@ stitch_status stitch_pyramid(const stitch_image* g0, int32_t kind, stitch_levels
  * full-canvas pyramid (origins 0, band dtype, CHW, 3 channels) receiving R_k; it is
  * required when levels > 1 (the collapse reads R_{k+1} from it); its level[0].data may be
  * NULL to skip storing R_0.  workspace: stitch_blend_workspace_bytes(n, levels) bytes of
- * 256-byte aligned device memory for the launch tables (same sharing rule as
- * stitch_pyramid).  Errors: NULL, SHAPE, LEVELS, WORKSPACE, UNSUPPORTED, DEVICE. */
+ * 256-byte aligned device memory for the cameras' table (calls that may overlap must not
+ * share it; its upload comes from pageable host memory and may wait for the stream).  Errors: NULL, SHAPE, LEVELS, WORKSPACE, UNSUPPORTED, DEVICE. */
 size_t        stitch_blend_workspace_bytes(int32_t n, int32_t levels);
 stitch_status stitch_blend(int32_t n, const stitch_levels* bands, const stitch_levels* weights,
                            stitch_image* pano, stitch_levels* keep_r, void* workspace,

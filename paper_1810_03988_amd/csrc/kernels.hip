@@ -1,5 +1,6 @@
 // gfx950 kernels of the per-frame stitching path (wave64, LDS-tiled, no MFMA: nothing
-// here is a dense contraction; every kernel is bound by HBM traffic).
+// here is a dense contraction).  The warp pass is bound by vector arithmetic, the large blends and
+// single stages by HBM traffic, small levels by latency; each kernel says which.
 //
 //   k_pyr    fused pyramid pass from level k to k+1 for many cameras at once.  A
 //            64-column level-k tile is walked in 16-row sub-steps; each is staged in LDS
@@ -10,8 +11,9 @@
 //            Sec. 1), and the seam-weight pyramid is reduced in the same pass.
 //   k_blend  one level of the synthesis side (Alg. 4, step 6): B_k = sum_i Gm_i L_i and
 //            R_k = B_k + EXPAND(R_{k+1}); level 0 writes the uint8 panorama.
-//   k_warp, k_warp_coords, k_expand_sub, k_convert: single-stage kernels behind the
-//            stitch_warp / stitch_pyramid entry points.
+//   k_tail, k_blend_tail: the small levels of either in one launch.
+//   k_warp, k_warp_coords, k_expand_sub, k_level0: single-stage kernels behind the
+//            stitch_warp / stitch_pyramid entry points (its REDUCEs run in k_tail).
 //
 // Borders: reflect-101 folded in the fine domain.  Staging the fine tile through the
 // periodic reflect-101 extension makes the locally reduced coarse tile equal to the
@@ -99,11 +101,6 @@ __device__ __forceinline__ void stg8nt(GLB _Float16* p, uint32_t a, uint32_t b, 
   typedef uint32_t vu4s __attribute__((ext_vector_type(4)));
   __builtin_nontemporal_store(vu4s{a, b, c, d}, reinterpret_cast<GLB vu4s*>(p));
 }
-
-__device__ __forceinline__ float ldv(const float* p, int64_t i) { return p[i]; }
-__device__ __forceinline__ float ldv(const _Float16* p, int64_t i) { return (float)p[i]; }
-__device__ __forceinline__ void stv(float* p, int64_t i, float v) { p[i] = v; }
-__device__ __forceinline__ void stv(_Float16* p, int64_t i, float v) { p[i] = (_Float16)v; }
 
 // Periodic reflect-101 extension: index -> [0, n), n >= 2 (period 2(n-1)).
 __device__ __forceinline__ int fold(int i, int n) {
@@ -337,9 +334,6 @@ __global__ void __launch_bounds__(kThreads, 4) k_pyr(const PyrItem* __restrict__
     const CST PyrItem& it = cst(items)[d.item];
     const int X0 = d.X0;
     const int fw = it.fine_w, fh = it.fine_h;
-    const int nimg = it.img_kind == kSrcNone ? 0 : it.nch;
-    const bool has_mask = it.msk_kind != kSrcNone;
-    const int nact = nimg + (has_mask ? 1 : 0);
     const int rx = it.roi_x, ry = it.roi_y, rw = it.roi_w, rh = it.roi_h;
 
     for (int s = 0; s < d.nsub; ++s) {
@@ -351,9 +345,8 @@ __global__ void __launch_bounds__(kThreads, 4) k_pyr(const PyrItem* __restrict__
       // level 0; see stage A)
       constexpr int kChunk = 16 / (int)sizeof(T);
       const bool chunked = !WARP && interior && rw > 0 && rh > 0 && ((X0 - rx) % kChunk) == 0 &&
-                           (nimg == 0 || (((uintptr_t)it.img & 15) == 0 && (it.img_row % kChunk) == 0 &&
-                                          (it.img_plane % kChunk) == 0)) &&
-                           (!has_mask || (((uintptr_t)it.msk & 15) == 0 && (it.msk_row % kChunk) == 0));
+                           ((uintptr_t)it.img & 15) == 0 && (it.img_row % kChunk) == 0 &&
+                           (it.img_plane % kChunk) == 0 && ((uintptr_t)it.msk & 15) == 0 && (it.msk_row % kChunk) == 0;
       if (WARP) {
         // the coordinate tables (the columns once per tile, the rows per sub-step); their
         // last readers (the previous sub-step's stage A) finished before its closing barrier
@@ -512,7 +505,7 @@ __global__ void __launch_bounds__(kThreads, 4) k_pyr(const PyrItem* __restrict__
           uint32_t mv[NQ];
           const bool inside = interior && X0 - 4 >= rx && X0 + TX + 3 <= rx + rw && Y0 - 4 + R0 >= ry &&
                               Y0 - 4 + R0 + NR <= ry + rh;
-          if (has_mask && inside) {
+          if (inside) {
             const GLB uint8_t* m0 = msk + (int64_t)(Y0 - 4 + R0 - ry) * it.msk_row + (X0 - 4 - rx);
             const uint32_t mrow = (uint32_t)it.msk_row;
 #pragma unroll
@@ -525,8 +518,8 @@ __global__ void __launch_bounds__(kThreads, 4) k_pyr(const PyrItem* __restrict__
               int X, Y;
               canvas(q, X, Y);
               const int my = Y - ry, mx = X - rx;
-              const bool in = has_mask && my >= 0 && my < rh && mx >= 0 && mx < rw;
-              const uint32_t m = has_mask ? (uint32_t)msk[in ? (int64_t)my * it.msk_row + mx : 0] : 0u;
+              const bool in = my >= 0 && my < rh && mx >= 0 && mx < rw;
+              const uint32_t m = msk[in ? (int64_t)my * it.msk_row + mx : 0];
               mv[q] = in ? m : 0u;
             }
           }
@@ -749,9 +742,8 @@ __global__ void __launch_bounds__(kThreads, 4) k_pyr(const PyrItem* __restrict__
           for (int q = 0; q < NQC; ++q) {
             const int e = min(tid_l + q * kThreads, NT - 1);
             const int k = e % NCH, rest = e / NCH, slot = rest & 3, r = rest >> 2;
-            const bool from_img = slot < 3 ? nimg > 0 : !has_mask;
-            const GLB T* base = from_img ? gimg + (uint32_t)min(slot, max(nimg - 1, 0)) * iplane : gmsk;
-            const uint32_t pitch = from_img ? irow : mrow;
+            const GLB T* base = slot < 3 ? gimg + (uint32_t)slot * iplane : gmsk;
+            const uint32_t pitch = slot < 3 ? irow : mrow;
             const int prow = min(max(Y0 - 4 + R0 + r - ry, 0), rh - 1);
             const int pck = min(max(k0 + k, 0), rwc - 1);
             const vu4c t = *reinterpret_cast<const GLB vu4c*>(base + (__umul24((uint32_t)prow, pitch) + (uint32_t)(C * pck)));
@@ -766,7 +758,7 @@ __global__ void __launch_bounds__(kThreads, 4) k_pyr(const PyrItem* __restrict__
             if (e >= NT) continue;
             const int k = e % NCH, rest = e / NCH, slot = rest & 3, r = rest >> 2;
             const int prow = Y0 - 4 + R0 + r - ry, c0 = C * (k0 + k);
-            const bool ok = (slot < 3 ? slot < nimg : has_mask) && prow >= 0 && prow < rh;
+            const bool ok = prow >= 0 && prow < rh;
             const int keep = ok ? min(max(rw - c0, 0), (c0 < 0 ? 0 : C)) : 0;   // leading samples kept
             float v[C];
 #pragma unroll
@@ -788,13 +780,11 @@ __global__ void __launch_bounds__(kThreads, 4) k_pyr(const PyrItem* __restrict__
           }
         } else {
           // stored G_k planes and Gm_k on the ROI (0 outside): every read is issued first, as
-          // raw bits from an address inside the planes (channel clamped to the last plane,
-          // offset 0 outside the ROI); conversion and zeroing come afterwards
-          const GLB T* g = cg<T>(nimg > 0 ? it.img : it.msk);
-          const int64_t grow = nimg > 0 ? it.img_row : it.msk_row, gplane = nimg > 0 ? it.img_plane : 0;
-          const GLB T* m = has_mask ? cg<T>(it.msk) : g;
-          const int64_t mrow = has_mask ? it.msk_row : grow;
-          const int cmax = nimg > 0 ? nimg - 1 : 0;
+          // raw bits from an address inside the planes (offset 0 outside the ROI); conversion and
+          // zeroing come afterwards
+          const GLB T* g = cg<T>(it.img);
+          const GLB T* m = cg<T>(it.msk);
+          const uint32_t grow = (uint32_t)it.img_row, gplane = (uint32_t)it.img_plane, mrow = (uint32_t)it.msk_row;
           typename RawOf<T>::type raw[NQ][4];
           bool inq[NQ];
 #pragma unroll
@@ -805,18 +795,17 @@ __global__ void __launch_bounds__(kThreads, 4) k_pyr(const PyrItem* __restrict__
             Y -= ry;
             X -= rx;
             inq[q] = X >= 0 && X < rw && Y >= 0 && Y < rh;
-            const uint32_t og = inq[q] ? __umul24((uint32_t)Y, (uint32_t)grow) + (uint32_t)X : 0u;
-            const uint32_t om = inq[q] ? __umul24((uint32_t)Y, (uint32_t)mrow) + (uint32_t)X : 0u;
+            const uint32_t og = inq[q] ? __umul24((uint32_t)Y, grow) + (uint32_t)X : 0u;
+            const uint32_t om = inq[q] ? __umul24((uint32_t)Y, mrow) + (uint32_t)X : 0u;
 #pragma unroll
-            for (int ch = 0; ch < 3; ++ch) raw[q][ch] = ld_raw(g, (uint32_t)min(ch, cmax) * (uint32_t)gplane + og);
+            for (int ch = 0; ch < 3; ++ch) raw[q][ch] = ld_raw(g, (uint32_t)ch * gplane + og);
             raw[q][3] = ld_raw(m, om);
           }
 #pragma unroll
           for (int q = 0; q < NQ; ++q) {
             if (!live(q)) continue;
 #pragma unroll
-            for (int ch = 0; ch < 3; ++ch) cell(ch, q) = (inq[q] && ch < nimg) ? from_raw(raw[q][ch]) : 0.0f;
-            cell(3, q) = (inq[q] && has_mask) ? from_raw(raw[q][3]) : 0.0f;
+            for (int ch = 0; ch < 4; ++ch) cell(ch, q) = inq[q] ? from_raw(raw[q][ch]) : 0.0f;
           }
         }
       };
@@ -829,13 +818,12 @@ __global__ void __launch_bounds__(kThreads, 4) k_pyr(const PyrItem* __restrict__
       //      its own LDS rows (sC[ch]), so the next workgroup barrier is the next sub-step's ----
       const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
       const int lane = tid & 63;
-      if (wv >= nact) continue;
-      // With all four channels, the mask (whose wave has no D+E) goes to wave s & 1: a
+      // The mask (whose wave has no D+E) goes to wave s & 1: a
       // workgroup's waves run on the compute unit's four SIMDs one each, and waves 0 and 1
       // also took stage A's last, partial round of samples, so every SIMD gets about the
       // same arithmetic per two sub-steps.
       const int mw = s & 1;
-      const int ch = nact == 4 && nimg == 3 ? (wv == mw ? 3 : wv - (wv > mw ? 1 : 0)) : (wv < nimg ? wv : 3);
+      const int ch = wv == mw ? 3 : wv - (wv > mw ? 1 : 0);
       // logical row r of the channel's ring (byte offsets keep the arithmetic 32-bit)
       const char* plane = reinterpret_cast<const char*>(&sIn[ch][0][0]);
       auto rowp = [&](int r) -> const float* {
@@ -1026,11 +1014,6 @@ __global__ void __launch_bounds__(kThreads, 4) k_pyr(const PyrItem* __restrict__
   }
 }
 
-// ------------------------------------------------------------------------------------
-// One synthesis level: B_k over cameras + EXPAND(R_{k+1}) -> R_k (and the panorama at k = 0).
-// 64x16 tile; thread (x = tid & 63) handles rows 4 (tid >> 6) + j, j = 0..3, so every
-// global access of a wave is one contiguous row segment, and a wave's four consecutive rows
-// share the four coarse rows their vertical EXPAND reads.
 // Four adjacent samples as read, from or to any sample address (global memory takes vectors at
 // any byte).
 typedef uint32_t __attribute__((aligned(1))) u32_unaligned;
@@ -1112,6 +1095,9 @@ __device__ __forceinline__ void put_row(uint8_t* pano_ptr, int64_t pano_row, int
   }
 }
 
+// ------------------------------------------------------------------------------------
+// One synthesis level: B_k over cameras + EXPAND(R_{k+1}) -> R_k (and the panorama at k = 0), 64x16
+// tiles, four adjacent pixels of a row a thread.
 template <typename T, bool FINAL, bool KARG>
 __global__ void __launch_bounds__(kThreads) k_blend(const BlendItem* __restrict__ items, int nitems, BlendItem one,
                                                     PanoArg po) {

@@ -513,7 +513,7 @@ TailItem tail_item(const std::vector<PyrItem>* items, int k0, int depth, size_t 
   const PyrItem& f = items[k0][q];
   t.tiles_x = (f.roi_w + kTailTX - 1) / kTailTX;
   t.depth = depth;
-  t.nch = f.nch;
+  t.nch = 3;
   t.tile_x0 = f.tile_x0;
   t.tile_y0 = f.tile_y0;
   t.img = f.img; t.img_row = f.img_row; t.img_plane = f.img_plane;
@@ -572,22 +572,17 @@ void build_tables(stitch_plan* p) {
       it.fine_w = p->dw[k];
       it.fine_h = p->dh[k];
       it.roi_x = r.x; it.roi_y = r.y; it.roi_w = r.w; it.roi_h = r.h;
-      it.nch = 3;
       if (k == 0) {
-        it.img_kind = kSrcWarp;
         it.frame_slot = i;
         it.frame_w = c.fw;
         it.frame_h = c.fh;
         std::memcpy(it.hinv, c.hinv, sizeof it.hinv);
-        it.msk_kind = kSrcU8;
         it.msk = ws + c.off_mask0;
         it.msk_row = c.mask_row;
       } else {
-        it.img_kind = kSrcPlanes;
         it.img = ws + c.off_g[k];
         it.img_row = c.g_row[k];
         it.img_plane = c.g_plane[k];
-        it.msk_kind = kSrcPlanes;
         it.msk = ws + c.off_gm[k];
         it.msk_row = c.gm_row[k];
       }
@@ -764,6 +759,7 @@ stitch_status stitch_warp_coords(const double H[9], int32_t roi_x, int32_t roi_y
 }
 
 // ------------------------------------------------------------------------------------ pyramid
+// (One descriptor a level, as when they lay there; the launches carry them now.)
 size_t stitch_pyramid_workspace_bytes(int32_t levels) {
   return (size_t)align_up((int64_t)std::max(levels, 1) * (int64_t)sizeof(PyrItem), 256);
 }
@@ -892,6 +888,7 @@ stitch_status stitch_pyramid(const stitch_image* g0, int32_t kind, stitch_levels
 }
 
 // ------------------------------------------------------------------------------------ blend
+// (The cameras' table, and room for the levels' descriptors, which the launches carry now.)
 size_t stitch_blend_workspace_bytes(int32_t n, int32_t levels) {
   const int64_t L = std::max(levels, 1);
   return (size_t)align_up(std::max(n, 1) * L * (int64_t)sizeof(BlendCam), 256) +

@@ -17,8 +17,6 @@ constexpr int kPyrTX = 64, kPyrTY = 16;
 constexpr int kBlendTX = 64, kBlendTY = 16;
 constexpr int kThreads = 256;
 
-enum SrcKind : int32_t { kSrcNone = 0, kSrcWarp = 1, kSrcPlanes = 2, kSrcU8 = 3 };
-
 struct Hinv9 { float h[9]; };
 
 // One camera's tile range in a fused REDUCE (+ EXPAND/subtract) pass from level k
@@ -29,15 +27,13 @@ struct PyrItem {
   int32_t tile_x0, tile_y0;               // level-k origin of tile (0,0); both even
   int32_t fine_w, fine_h;                 // level-k canvas sides
   int32_t roi_x, roi_y, roi_w, roi_h;     // level-k input rectangle
-  // image source (channels nch)
-  int32_t img_kind, nch;
+  // image source: three planes, or at level 0 the warped frame
   const void* img;                        // planes (storage type) or u8 HWC frame
   int64_t img_row, img_plane;             // elements (planes) / bytes (frame row)
   int32_t frame_w, frame_h, frame_slot, pad0;
   float hinv[9];
   // weight (mask) source, one channel
-  int32_t msk_kind, pad1;
-  const void* msk;                        // u8 plane or storage-type plane on roi
+  const void* msk;                        // u8 plane (level 0) or storage-type plane on roi
   int64_t msk_row;                        // elements
   // outputs at level k+1 on croi
   int32_t croi_x, croi_y, croi_w, croi_h;
@@ -95,7 +91,7 @@ struct TailLevel {
 };
 struct TailItem {
   int32_t tile_begin, tiles_x, depth, nch;
-  int32_t tile_x0, tile_y0;               // finest-level origin of tile (0,0), multiples of 8
+  int32_t tile_x0, tile_y0;               // finest-level origin of tile (0,0), multiples of 2^depth
   int32_t src_u8;                         // the image source is bytes (read as u8/255)
   int32_t pad;
   const void* img; int64_t img_row, img_plane;   // finest-level image planes on lev[0].roi
