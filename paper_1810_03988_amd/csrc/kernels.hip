@@ -118,6 +118,13 @@ __device__ __forceinline__ int fold(int i, int n) {
 __device__ __forceinline__ float exp_h(float s, float b) { return __builtin_fmaf(0.75f, b, 0.125f * s); }
 __device__ __forceinline__ float exp_v(float s, float b) { return __builtin_fmaf(0.125f, s, 0.75f * b); }
 
+// REDUCE along one axis from its outer pair's sum, its inner pair's and the middle: one rounding each
+// for the first two products together and for the third (k_pyr's rows take the same
+// steps on 16 times the value).
+__device__ __forceinline__ float reduce5(float outer, float inner, float mid) {
+  return __builtin_fmaf(kW2, mid, __builtin_fmaf(kW1, inner, kW0 * outer));
+}
+
 // FP16 storage rounds a float to half; where that float is itself a multiply-add the compiler may
 // round the exact sum to half at once (v_fma_mixlo_f16) or to float first, and the two differ
 // about once in 10^7 samples.  Which of the two is part of a result that several kernels share,
@@ -1601,8 +1608,7 @@ __global__ void __launch_bounds__(kThreads) k_tail(const TailItem one, const Tai
         const float* rowp = f + r * fs + fo + 4 * p;
         const float4 u = *reinterpret_cast<const float4*>(rowp);
         const float4 v = *reinterpret_cast<const float4*>(rowp + 4);
-        return float2{kW0 * (u.x + v.x) + kW1 * (u.y + u.w) + kW2 * u.z,
-                      kW0 * (u.z + v.z) + kW1 * (u.w + v.y) + kW2 * v.x};
+        return float2{reduce5(u.x + v.x, u.y + u.w, u.z), reduce5(u.z + v.z, u.w + v.y, v.x)};
       };
       if (i0 < cr) {
         float2 h0 = hrow(2 * i0), h1 = hrow(2 * i0 + 1), h2 = hrow(2 * i0 + 2);
@@ -1610,8 +1616,8 @@ __global__ void __launch_bounds__(kThreads) k_tail(const TailItem one, const Tai
         for (int m = i0; m < i1; ++m) {
           const float2 h3 = hrow(2 * m + 3), h4 = hrow(2 * m + 4);
           float* o = c + m * cs + co + 2 * p;
-          o[0] = kW0 * (h0.x + h4.x) + kW1 * (h1.x + h3.x) + kW2 * h2.x;
-          o[1] = kW0 * (h0.y + h4.y) + kW1 * (h1.y + h3.y) + kW2 * h2.y;
+          o[0] = reduce5(h0.x + h4.x, h1.x + h3.x, h2.x);
+          o[1] = reduce5(h0.y + h4.y, h1.y + h3.y, h2.y);
           h0 = h2; h1 = h3; h2 = h4;
         }
       }
