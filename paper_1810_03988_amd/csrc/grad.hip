@@ -1496,22 +1496,24 @@ stitch_status stitch_grad_create(const int32_t frame_w[2], const int32_t frame_h
 size_t stitch_grad_workspace_bytes(const stitch_grad* g) { return g ? g->bytes : 0; }
 
 stitch_status stitch_grad_bind(stitch_grad* g, void* workspace, size_t bytes, void* stream) {
-  if (!g) return fail(STITCH_E_NULL, "grad is NULL");
-  if (!workspace || ((uintptr_t)workspace & 255) || bytes < g->bytes)
-    return fail(STITCH_E_WORKSPACE, "workspace missing, misaligned or smaller than %zu bytes", g->bytes);
-  const hipStream_t s = (hipStream_t)stream;
-  g->ws = (uint8_t*)workspace;
-  g->frozen = false;
-  g->have_forward = false;
-  stitch_status st = dev_ok(hipMemcpyAsync(g->ws + g->o_mask, g->masks.data(), g->masks.size(), hipMemcpyHostToDevice, s),
-                            "mask upload");
-  if (!st) {
-    launch_pyramids<true>(g->d, pair_work(g), false, true, s);
-    st = dev_ok(hipGetLastError(), "weight pyramid launch");
-  }
-  if (!st) st = dev_ok(hipStreamSynchronize(s), "bind synchronise");
-  if (st) g->ws = nullptr;
-  return st;
+  return guarded([&]() -> stitch_status {
+    if (!g) return fail(STITCH_E_NULL, "grad is NULL");
+    if (!workspace || ((uintptr_t)workspace & 255) || bytes < g->bytes)
+      return fail(STITCH_E_WORKSPACE, "workspace missing, misaligned or smaller than %zu bytes", g->bytes);
+    const hipStream_t s = (hipStream_t)stream;
+    g->ws = (uint8_t*)workspace;
+    g->frozen = false;
+    g->have_forward = false;
+    stitch_status st = dev_ok(hipMemcpyAsync(g->ws + g->o_mask, g->masks.data(), g->masks.size(), hipMemcpyHostToDevice, s),
+                              "mask upload");
+    if (!st) {
+      launch_pyramids<true>(g->d, pair_work(g), false, true, s);
+      st = dev_ok(hipGetLastError(), "weight pyramid launch");
+    }
+    if (!st) st = dev_ok(hipStreamSynchronize(s), "bind synchronise");
+    if (st) g->ws = nullptr;
+    return st;
+  });
 }
 
 stitch_status stitch_grad_freeze(stitch_grad* g, const double H[18], int64_t* omega_count, void* stream) {
@@ -1550,87 +1552,91 @@ stitch_status stitch_grad_freeze(stitch_grad* g, const double H[18], int64_t* om
 
 stitch_status stitch_grad_forward(stitch_grad* g, const stitch_image* frames, const double H[18], double* loss,
                                   void* stream) {
-  if (!g || !frames || !H || !loss) return fail(STITCH_E_NULL, "grad, frames, H or loss is NULL");
-  if (!g->ws) return fail(STITCH_E_STATE, "no workspace bound");
-  if (!g->frozen) return fail(STITCH_E_STATE, "call stitch_grad_freeze first");
-  for (int c = 0; c < 2; ++c) {
-    stitch_status st = check_image(&frames[c], c ? "frames[1]" : "frames[0]", STITCH_F32, STITCH_CHW, 3);
+  return guarded([&]() -> stitch_status {
+    if (!g || !frames || !H || !loss) return fail(STITCH_E_NULL, "grad, frames, H or loss is NULL");
+    if (!g->ws) return fail(STITCH_E_STATE, "no workspace bound");
+    if (!g->frozen) return fail(STITCH_E_STATE, "call stitch_grad_freeze first");
+    for (int c = 0; c < 2; ++c) {
+      stitch_status st = check_image(&frames[c], c ? "frames[1]" : "frames[0]", STITCH_F32, STITCH_CHW, 3);
+      if (st) return st;
+      if (frames[c].width != g->fw[c] || frames[c].height != g->fh[c])
+        return fail(STITCH_E_SHAPE, "frames[%d] does not match the planned size", c);
+    }
+    Map9 m[2];
+    stitch_status st = maps_from(H, m);
     if (st) return st;
-    if (frames[c].width != g->fw[c] || frames[c].height != g->fh[c])
-      return fail(STITCH_E_SHAPE, "frames[%d] does not match the planned size", c);
-  }
-  Map9 m[2];
-  stitch_status st = maps_from(H, m);
-  if (st) return st;
-  const hipStream_t s = (hipStream_t)stream;
-  const Dims& d = g->d;
-  for (int c = 0; c < 2; ++c) {
-    g->maps[c] = m[c];
-    g->fsrc[c] = (const float*)frames[c].data;
-    g->frow[c] = frames[c].row_pitch / 4;
-    g->fplane[c] = frames[c].plane_pitch / 4;
-  }
-  const std::vector<CamWork> cw = pair_work(g);
-  launch_pyramids<true>(d, cw, true, false, s);
-  for (int k = d.L - 1; k >= 1; --k)
-    launch_blend_level(d, k, cw, nullptr, k + 1 < d.L ? g->dptr(g->o_r[k + 1]) : nullptr, g->dptr(g->o_r[k]), s);
-  LossArgs a;
-  std::memset(&a, 0, sizeof a);
-  for (int c = 0; c < 2; ++c) a.cam[c] = pano_cam(d, cw[c]);
-  a.W = d.W; a.H = d.H;
-  if (d.L > 1) { a.rc = g->dptr(g->o_r[1]); a.cw = d.dw[1]; a.ch = d.dh[1]; }
-  a.omega = g->ws + g->o_om;
-  a.scale = 1.0 / (6.0 * g->omega_n);
-  a.ga = g->dptr(g->o_ga);
-  a.gb = g->dptr(g->o_gb);
-  a.part = g->dptr(g->o_part);
-  hipLaunchKernelGGL(k_gloss, dim3(g->nbx, g->nby), dim3(kT), 0, s, a);
-  hipLaunchKernelGGL(k_gsum, dim3(1), dim3(kT), 0, s, g->dptr(g->o_part), g->nbx * g->nby, g->dptr(g->o_res));
-  st = dev_ok(hipGetLastError(), "forward launch");
-  double sum = 0.0;
-  if (!st) st = dev_ok(hipMemcpyAsync(&sum, g->dptr(g->o_res), 8, hipMemcpyDeviceToHost, s), "loss copy");
-  if (!st) st = dev_ok(hipStreamSynchronize(s), "forward synchronise");
-  if (st) return st;
-  *loss = sum / (6.0 * g->omega_n);
-  g->have_forward = true;
-  return STITCH_OK;
+    const hipStream_t s = (hipStream_t)stream;
+    const Dims& d = g->d;
+    for (int c = 0; c < 2; ++c) {
+      g->maps[c] = m[c];
+      g->fsrc[c] = (const float*)frames[c].data;
+      g->frow[c] = frames[c].row_pitch / 4;
+      g->fplane[c] = frames[c].plane_pitch / 4;
+    }
+    const std::vector<CamWork> cw = pair_work(g);
+    launch_pyramids<true>(d, cw, true, false, s);
+    for (int k = d.L - 1; k >= 1; --k)
+      launch_blend_level(d, k, cw, nullptr, k + 1 < d.L ? g->dptr(g->o_r[k + 1]) : nullptr, g->dptr(g->o_r[k]), s);
+    LossArgs a;
+    std::memset(&a, 0, sizeof a);
+    for (int c = 0; c < 2; ++c) a.cam[c] = pano_cam(d, cw[c]);
+    a.W = d.W; a.H = d.H;
+    if (d.L > 1) { a.rc = g->dptr(g->o_r[1]); a.cw = d.dw[1]; a.ch = d.dh[1]; }
+    a.omega = g->ws + g->o_om;
+    a.scale = 1.0 / (6.0 * g->omega_n);
+    a.ga = g->dptr(g->o_ga);
+    a.gb = g->dptr(g->o_gb);
+    a.part = g->dptr(g->o_part);
+    hipLaunchKernelGGL(k_gloss, dim3(g->nbx, g->nby), dim3(kT), 0, s, a);
+    hipLaunchKernelGGL(k_gsum, dim3(1), dim3(kT), 0, s, g->dptr(g->o_part), g->nbx * g->nby, g->dptr(g->o_res));
+    st = dev_ok(hipGetLastError(), "forward launch");
+    double sum = 0.0;
+    if (!st) st = dev_ok(hipMemcpyAsync(&sum, g->dptr(g->o_res), 8, hipMemcpyDeviceToHost, s), "loss copy");
+    if (!st) st = dev_ok(hipStreamSynchronize(s), "forward synchronise");
+    if (st) return st;
+    *loss = sum / (6.0 * g->omega_n);
+    g->have_forward = true;
+    return STITCH_OK;
+  });
 }
 
 stitch_status stitch_grad_backward(stitch_grad* g, stitch_image* d_frames, double d_map[18], void* stream) {
-  if (!g || !d_frames || !d_map) return fail(STITCH_E_NULL, "grad, d_frames or d_map is NULL");
-  if (!g->have_forward) return fail(STITCH_E_STATE, "call stitch_grad_forward first");
-  for (int c = 0; c < 2; ++c) {
-    stitch_status st = check_image(&d_frames[c], c ? "d_frames[1]" : "d_frames[0]", STITCH_F32, STITCH_CHW, 3);
+  return guarded([&]() -> stitch_status {
+    if (!g || !d_frames || !d_map) return fail(STITCH_E_NULL, "grad, d_frames or d_map is NULL");
+    if (!g->have_forward) return fail(STITCH_E_STATE, "call stitch_grad_forward first");
+    for (int c = 0; c < 2; ++c) {
+      stitch_status st = check_image(&d_frames[c], c ? "d_frames[1]" : "d_frames[0]", STITCH_F32, STITCH_CHW, 3);
+      if (st) return st;
+      if (d_frames[c].width != g->fw[c] || d_frames[c].height != g->fh[c])
+        return fail(STITCH_E_SHAPE, "d_frames[%d] does not match the planned size", c);
+    }
+    const hipStream_t s = (hipStream_t)stream;
+    const Dims& d = g->d;
+    const int64_t np = (int64_t)d.W * d.H;
+    double* dr[kMaxLevels] = {};
+    for (int k = 1; k < d.L; ++k) dr[k] = g->dptr(g->o_dr[k]);
+    const Img3 dr0{g->dptr(g->o_gp), d.W, np, 1};
+    hipLaunchKernelGGL(k_gzero, dim3(1), dim3(1), 0, s, g->dptr(g->o_flag));
+    hipLaunchKernelGGL(k_gpano, dim3(blocks(3 * np)), dim3(kT), 0, s, g->dptr(g->o_ga), g->dptr(g->o_gb), 3 * np,
+                       g->dptr(g->o_gp));
+    launch_dr(d, dr0, dr, s);
+    std::vector<CamWork> cw = pair_work(g);
+    cw[0].direct = Img3{g->dptr(g->o_ga), d.W, np, 1};
+    cw[1].direct = Img3{g->dptr(g->o_gb), d.W, np, 1};
+    launch_adjoint<true>(d, cw, dr0, dr, d_frames, g->dptr(g->o_res), (int*)(g->ws + g->o_flag), s);
+    stitch_status st = dev_ok(hipGetLastError(), "backward launch");
+    double res[19];
+    if (!st) st = dev_ok(hipMemcpyAsync(res, g->dptr(g->o_res), sizeof res, hipMemcpyDeviceToHost, s), "grad copy");
+    if (!st) st = dev_ok(hipStreamSynchronize(s), "backward synchronise");
     if (st) return st;
-    if (d_frames[c].width != g->fw[c] || d_frames[c].height != g->fh[c])
-      return fail(STITCH_E_SHAPE, "d_frames[%d] does not match the planned size", c);
-  }
-  const hipStream_t s = (hipStream_t)stream;
-  const Dims& d = g->d;
-  const int64_t np = (int64_t)d.W * d.H;
-  double* dr[kMaxLevels] = {};
-  for (int k = 1; k < d.L; ++k) dr[k] = g->dptr(g->o_dr[k]);
-  const Img3 dr0{g->dptr(g->o_gp), d.W, np, 1};
-  hipLaunchKernelGGL(k_gzero, dim3(1), dim3(1), 0, s, g->dptr(g->o_flag));
-  hipLaunchKernelGGL(k_gpano, dim3(blocks(3 * np)), dim3(kT), 0, s, g->dptr(g->o_ga), g->dptr(g->o_gb), 3 * np,
-                     g->dptr(g->o_gp));
-  launch_dr(d, dr0, dr, s);
-  std::vector<CamWork> cw = pair_work(g);
-  cw[0].direct = Img3{g->dptr(g->o_ga), d.W, np, 1};
-  cw[1].direct = Img3{g->dptr(g->o_gb), d.W, np, 1};
-  launch_adjoint<true>(d, cw, dr0, dr, d_frames, g->dptr(g->o_res), (int*)(g->ws + g->o_flag), s);
-  stitch_status st = dev_ok(hipGetLastError(), "backward launch");
-  double res[19];
-  if (!st) st = dev_ok(hipMemcpyAsync(res, g->dptr(g->o_res), sizeof res, hipMemcpyDeviceToHost, s), "grad copy");
-  if (!st) st = dev_ok(hipStreamSynchronize(s), "backward synchronise");
-  if (st) return st;
-  int flag = 0;
-  std::memcpy(&flag, &res[18], sizeof flag);
-  if (flag)
-    return fail(STITCH_E_UNSUPPORTED, "a frozen map %s",
-                (flag & 2) ? "reaches its horizon over the frame" : "magnifies a source pixel over about 20 times");
-  for (int i = 0; i < 18; ++i) d_map[i] = res[i];
-  return STITCH_OK;
+    int flag = 0;
+    std::memcpy(&flag, &res[18], sizeof flag);
+    if (flag)
+      return fail(STITCH_E_UNSUPPORTED, "a frozen map %s",
+                  (flag & 2) ? "reaches its horizon over the frame" : "magnifies a source pixel over about 20 times");
+    for (int i = 0; i < 18; ++i) d_map[i] = res[i];
+    return STITCH_OK;
+  });
 }
 
 stitch_status stitch_grad_upstream(stitch_grad* g, stitch_image* d_pano, stitch_image* d_warped, void* stream) {
@@ -1807,110 +1813,114 @@ size_t stitch_frame_backward_workspace_bytes(const stitch_plan* plan) {
 
 stitch_status stitch_frame_forward_f32(stitch_plan* plan, const stitch_image* frames, stitch_image* r0,
                                        void* workspace, size_t bytes, void* stream) {
-  if (!plan || !frames || !r0) return fail(STITCH_E_NULL, "plan, frames or r0 is NULL");
-  VjpLayout v;
-  stitch_status st = vjp_layout(plan, v);
-  if (st) return st;
-  if ((st = vjp_check_ws(v, workspace, bytes))) return st;
-  if ((st = vjp_check_frames(plan, v.n, frames, "frames"))) return st;
-  std::vector<CamWork> cams(v.n);
-  std::vector<PlanCamera> pcs(v.n);
-  for (int i = 0; i < v.n; ++i)
-    if (!vjp_camera(plan, v, i, frames[i], cams[i], pcs[i]))
-      return fail(STITCH_E_HOMOGRAPHY, "camera %d: its map is singular", i);
-  if ((st = check_image(r0, "r0", STITCH_F32, STITCH_CHW, 3))) return st;
-  if (r0->width != v.d.W || r0->height != v.d.H) return fail(STITCH_E_SHAPE, "r0 is not canvas-sized");
-  const hipStream_t s = (hipStream_t)stream;
-  uint8_t* ws = (uint8_t*)workspace;
-  auto D = [&](size_t o) { return (double*)(ws + o); };
-  const int L = v.d.L;
-  std::vector<VjpGroup> groups = vjp_groups(v, ws, v.o_group, false, cams, pcs);
-  if (groups.size() > 1) groups = vjp_groups(v, ws, v.o_group_acc, false, cams, pcs);
-  for (size_t q = 0; q < groups.size() && !st; ++q) {
-    const VjpGroup& g = groups[q];
-    const bool first = q == 0, last = q + 1 == groups.size();
-    if ((st = vjp_upload(g, s))) break;
-    launch_pyramids<false>(v.d, g.cw, true, true, s);
-    // B_k accumulates over the groups in R_k's place; the last one collapses
-    for (int k = L - 1; k >= 1; --k)
-      launch_blend_level(v.d, k, g.cw, first ? nullptr : D(v.o_r[k]), last && k + 1 < L ? D(v.o_r[k + 1]) : nullptr,
-                         D(v.o_r[k]), s);
-    PanoArgs a;
-    std::memset(&a, 0, sizeof a);
-    a.n = (int)g.cw.size();
-    for (int i = 0; i < a.n; ++i) a.cam[i] = pano_cam(v.d, g.cw[i]);
-    a.W = v.d.W; a.H = v.d.H;
-    a.acc = first ? nullptr : D(v.o_acc);
-    if (last && L > 1) { a.rc = D(v.o_r[1]); a.cw = v.d.dw[1]; a.ch = v.d.dh[1]; }
-    if (last) {
-      a.out32 = (float*)r0->data;
-      a.orow = r0->row_pitch / 4;
-      a.oplane = r0->plane_pitch / 4;
-    } else {
-      a.out64 = D(v.o_acc);
+  return guarded([&]() -> stitch_status {
+    if (!plan || !frames || !r0) return fail(STITCH_E_NULL, "plan, frames or r0 is NULL");
+    VjpLayout v;
+    stitch_status st = vjp_layout(plan, v);
+    if (st) return st;
+    if ((st = vjp_check_ws(v, workspace, bytes))) return st;
+    if ((st = vjp_check_frames(plan, v.n, frames, "frames"))) return st;
+    std::vector<CamWork> cams(v.n);
+    std::vector<PlanCamera> pcs(v.n);
+    for (int i = 0; i < v.n; ++i)
+      if (!vjp_camera(plan, v, i, frames[i], cams[i], pcs[i]))
+        return fail(STITCH_E_HOMOGRAPHY, "camera %d: its map is singular", i);
+    if ((st = check_image(r0, "r0", STITCH_F32, STITCH_CHW, 3))) return st;
+    if (r0->width != v.d.W || r0->height != v.d.H) return fail(STITCH_E_SHAPE, "r0 is not canvas-sized");
+    const hipStream_t s = (hipStream_t)stream;
+    uint8_t* ws = (uint8_t*)workspace;
+    auto D = [&](size_t o) { return (double*)(ws + o); };
+    const int L = v.d.L;
+    std::vector<VjpGroup> groups = vjp_groups(v, ws, v.o_group, false, cams, pcs);
+    if (groups.size() > 1) groups = vjp_groups(v, ws, v.o_group_acc, false, cams, pcs);
+    for (size_t q = 0; q < groups.size() && !st; ++q) {
+      const VjpGroup& g = groups[q];
+      const bool first = q == 0, last = q + 1 == groups.size();
+      if ((st = vjp_upload(g, s))) break;
+      launch_pyramids<false>(v.d, g.cw, true, true, s);
+      // B_k accumulates over the groups in R_k's place; the last one collapses
+      for (int k = L - 1; k >= 1; --k)
+        launch_blend_level(v.d, k, g.cw, first ? nullptr : D(v.o_r[k]), last && k + 1 < L ? D(v.o_r[k + 1]) : nullptr,
+                           D(v.o_r[k]), s);
+      PanoArgs a;
+      std::memset(&a, 0, sizeof a);
+      a.n = (int)g.cw.size();
+      for (int i = 0; i < a.n; ++i) a.cam[i] = pano_cam(v.d, g.cw[i]);
+      a.W = v.d.W; a.H = v.d.H;
+      a.acc = first ? nullptr : D(v.o_acc);
+      if (last && L > 1) { a.rc = D(v.o_r[1]); a.cw = v.d.dw[1]; a.ch = v.d.dh[1]; }
+      if (last) {
+        a.out32 = (float*)r0->data;
+        a.orow = r0->row_pitch / 4;
+        a.oplane = r0->plane_pitch / 4;
+      } else {
+        a.out64 = D(v.o_acc);
+      }
+      hipLaunchKernelGGL(k_vpano, dim3(cdiv(a.W, 64), cdiv(a.H, 4)), dim3(kT), 0, s, a);
+      st = dev_ok(hipGetLastError(), "forward launch");
     }
-    hipLaunchKernelGGL(k_vpano, dim3(cdiv(a.W, 64), cdiv(a.H, 4)), dim3(kT), 0, s, a);
-    st = dev_ok(hipGetLastError(), "forward launch");
-  }
-  return st;
+    return st;
+  });
 }
 
 stitch_status stitch_frame_backward(stitch_plan* plan, const stitch_image* frames, const stitch_image* d_pano,
                                     const stitch_image* d_warped, stitch_image* d_frames, double* d_hinv,
                                     void* workspace, size_t bytes, void* stream) {
-  if (!plan || !frames || !d_pano || !d_frames || !d_hinv)
-    return fail(STITCH_E_NULL, "plan, frames, d_pano, d_frames or d_hinv is NULL");
-  VjpLayout v;
-  stitch_status st = vjp_layout(plan, v);
-  if (st) return st;
-  if ((st = vjp_check_ws(v, workspace, bytes))) return st;
-  if ((st = vjp_check_frames(plan, v.n, frames, "frames"))) return st;
-  std::vector<CamWork> cams(v.n);
-  std::vector<PlanCamera> pcs(v.n);
-  for (int i = 0; i < v.n; ++i)
-    if (!vjp_camera(plan, v, i, frames[i], cams[i], pcs[i]))
-      return fail(STITCH_E_HOMOGRAPHY, "camera %d: its map is singular", i);
-  if ((st = vjp_check_frames(plan, v.n, d_frames, "d_frames"))) return st;
-  if ((st = check_image(d_pano, "d_pano", STITCH_F32, STITCH_CHW, 3))) return st;
-  if (d_pano->width != v.d.W || d_pano->height != v.d.H) return fail(STITCH_E_SHAPE, "d_pano is not canvas-sized");
-  for (int i = 0; i < v.n; ++i) {
-    // dG_0 is needed where the weights reach; with a direct term, everywhere
-    cams[i].dom = cams[i].roi[0];
-    if (!d_warped || !d_warped[i].data) continue;
-    char name[40];
-    snprintf(name, sizeof name, "d_warped[%d]", i);
-    if ((st = check_image(&d_warped[i], name, STITCH_F32, STITCH_CHW, 3))) return st;
-    if (d_warped[i].width != v.d.W || d_warped[i].height != v.d.H)
-      return fail(STITCH_E_SHAPE, "%s is not canvas-sized", name);
-    cams[i].direct = Img3{d_warped[i].data, d_warped[i].row_pitch / 4, d_warped[i].plane_pitch / 4, 0};
-    cams[i].dom = Box{0, 0, v.d.W, v.d.H};
-  }
-  const hipStream_t s = (hipStream_t)stream;
-  uint8_t* ws = (uint8_t*)workspace;
-  auto D = [&](size_t o) { return (double*)(ws + o); };
-  double* dr[kMaxLevels] = {};
-  for (int k = 1; k < v.d.L; ++k) dr[k] = D(v.o_r[k]);
-  const Img3 dr0{d_pano->data, d_pano->row_pitch / 4, d_pano->plane_pitch / 4, 0};
-  hipLaunchKernelGGL(k_gzero, dim3(1), dim3(1), 0, s, D(v.o_flag));
-  launch_dr(v.d, dr0, dr, s);
-  st = dev_ok(hipGetLastError(), "backward launch");
-  for (const VjpGroup& g : vjp_groups(v, ws, v.o_group, true, cams, pcs)) {
-    if (st || (st = vjp_upload(g, s))) break;
-    launch_pyramids<false>(v.d, g.cw, false, true, s);
-    launch_adjoint<false>(v.d, g.cw, dr0, dr, d_frames + g.first, D(v.o_res) + 9 * g.first, (int*)(ws + v.o_flag), s);
+  return guarded([&]() -> stitch_status {
+    if (!plan || !frames || !d_pano || !d_frames || !d_hinv)
+      return fail(STITCH_E_NULL, "plan, frames, d_pano, d_frames or d_hinv is NULL");
+    VjpLayout v;
+    stitch_status st = vjp_layout(plan, v);
+    if (st) return st;
+    if ((st = vjp_check_ws(v, workspace, bytes))) return st;
+    if ((st = vjp_check_frames(plan, v.n, frames, "frames"))) return st;
+    std::vector<CamWork> cams(v.n);
+    std::vector<PlanCamera> pcs(v.n);
+    for (int i = 0; i < v.n; ++i)
+      if (!vjp_camera(plan, v, i, frames[i], cams[i], pcs[i]))
+        return fail(STITCH_E_HOMOGRAPHY, "camera %d: its map is singular", i);
+    if ((st = vjp_check_frames(plan, v.n, d_frames, "d_frames"))) return st;
+    if ((st = check_image(d_pano, "d_pano", STITCH_F32, STITCH_CHW, 3))) return st;
+    if (d_pano->width != v.d.W || d_pano->height != v.d.H) return fail(STITCH_E_SHAPE, "d_pano is not canvas-sized");
+    for (int i = 0; i < v.n; ++i) {
+      // dG_0 is needed where the weights reach; with a direct term, everywhere
+      cams[i].dom = cams[i].roi[0];
+      if (!d_warped || !d_warped[i].data) continue;
+      char name[40];
+      snprintf(name, sizeof name, "d_warped[%d]", i);
+      if ((st = check_image(&d_warped[i], name, STITCH_F32, STITCH_CHW, 3))) return st;
+      if (d_warped[i].width != v.d.W || d_warped[i].height != v.d.H)
+        return fail(STITCH_E_SHAPE, "%s is not canvas-sized", name);
+      cams[i].direct = Img3{d_warped[i].data, d_warped[i].row_pitch / 4, d_warped[i].plane_pitch / 4, 0};
+      cams[i].dom = Box{0, 0, v.d.W, v.d.H};
+    }
+    const hipStream_t s = (hipStream_t)stream;
+    uint8_t* ws = (uint8_t*)workspace;
+    auto D = [&](size_t o) { return (double*)(ws + o); };
+    double* dr[kMaxLevels] = {};
+    for (int k = 1; k < v.d.L; ++k) dr[k] = D(v.o_r[k]);
+    const Img3 dr0{d_pano->data, d_pano->row_pitch / 4, d_pano->plane_pitch / 4, 0};
+    hipLaunchKernelGGL(k_gzero, dim3(1), dim3(1), 0, s, D(v.o_flag));
+    launch_dr(v.d, dr0, dr, s);
     st = dev_ok(hipGetLastError(), "backward launch");
-  }
-  std::vector<double> res(9 * (size_t)v.n + 1, 0.0);
-  if (!st) st = dev_ok(hipMemcpyAsync(res.data(), D(v.o_res), res.size() * 8, hipMemcpyDeviceToHost, s), "gradient copy");
-  if (!st) st = dev_ok(hipStreamSynchronize(s), "backward synchronise");
-  if (st) return st;
-  int flag = 0;
-  std::memcpy(&flag, &res[9 * (size_t)v.n], sizeof flag);
-  if (flag)
-    return fail(STITCH_E_UNSUPPORTED, "a map magnifies a source pixel beyond the gather's reach or crosses its "
-                "horizon inside a frame (flags %d); d_frames is incomplete", flag);
-  for (size_t j = 0; j + 1 < res.size(); ++j) d_hinv[j] = res[j];
-  return STITCH_OK;
+    for (const VjpGroup& g : vjp_groups(v, ws, v.o_group, true, cams, pcs)) {
+      if (st || (st = vjp_upload(g, s))) break;
+      launch_pyramids<false>(v.d, g.cw, false, true, s);
+      launch_adjoint<false>(v.d, g.cw, dr0, dr, d_frames + g.first, D(v.o_res) + 9 * g.first, (int*)(ws + v.o_flag), s);
+      st = dev_ok(hipGetLastError(), "backward launch");
+    }
+    std::vector<double> res(9 * (size_t)v.n + 1, 0.0);
+    if (!st) st = dev_ok(hipMemcpyAsync(res.data(), D(v.o_res), res.size() * 8, hipMemcpyDeviceToHost, s), "gradient copy");
+    if (!st) st = dev_ok(hipStreamSynchronize(s), "backward synchronise");
+    if (st) return st;
+    int flag = 0;
+    std::memcpy(&flag, &res[9 * (size_t)v.n], sizeof flag);
+    if (flag)
+      return fail(STITCH_E_UNSUPPORTED, "a map magnifies a source pixel beyond the gather's reach or crosses its "
+                  "horizon inside a frame (flags %d); d_frames is incomplete", flag);
+    for (size_t j = 0; j + 1 < res.size(); ++j) d_hinv[j] = res[j];
+    return STITCH_OK;
+  });
 }
 
 stitch_status stitch_corners_to_h(const double q[8], int32_t w, int32_t h, double H[9]) {

@@ -1267,25 +1267,33 @@ stitch_status stitch_plan_bind(stitch_plan* p, void* workspace, size_t bytes, vo
   if (!workspace) return fail(STITCH_E_WORKSPACE, "workspace is NULL");
   if (((uintptr_t)workspace & 255) != 0) return fail(STITCH_E_WORKSPACE, "workspace is not 256-byte aligned");
   if (bytes < p->ws_bytes) return fail(STITCH_E_WORKSPACE, "workspace has %zu bytes, the plan needs %zu", bytes, p->ws_bytes);
-  p->ws = (uint8_t*)workspace;
-  build_tables(p);
   const hipStream_t s = (hipStream_t)stream;
-  stitch_status st = STITCH_OK;
-  std::vector<std::vector<uint8_t>> masks(p->n);       // alive until the stream has drained
-  for (int i = 0; i < p->n && !st; ++i) {
-    const CamPlan& c = p->cam[i];
-    const Rect r = c.roi[0];
-    if (r.empty()) continue;
-    masks[i].assign((size_t)c.mask_row * r.h, 0);
-    const int x0 = std::max(r.x, c.wsx), x1 = std::min(r.x + r.w, c.wsx + c.wsw);
-    for (int y = std::max(r.y, c.wsy); x0 < x1 && y < std::min(r.y + r.h, c.wsy + c.wsh); ++y) {
-      uint32_t id;
-      std::memcpy(&id, &c.wdict[(size_t)4 * (y - c.wsy)], sizeof id);
-      std::memcpy(&masks[i][(size_t)(y - r.y) * c.mask_row + (x0 - r.x)],
-                  &c.wdict[(size_t)4 * c.wsh + (size_t)id * c.wsw + (x0 - c.wsx)], x1 - x0);
+  p->ws = (uint8_t*)workspace;
+  std::vector<std::vector<uint8_t>> masks;             // alive until the stream has drained
+  stitch_status st = guarded([&] {
+    build_tables(p);
+    masks.resize(p->n);
+    for (int i = 0; i < p->n; ++i) {
+      const CamPlan& c = p->cam[i];
+      const Rect r = c.roi[0];
+      if (r.empty()) continue;
+      masks[i].assign((size_t)c.mask_row * r.h, 0);
+      const int x0 = std::max(r.x, c.wsx), x1 = std::min(r.x + r.w, c.wsx + c.wsw);
+      for (int y = std::max(r.y, c.wsy); x0 < x1 && y < std::min(r.y + r.h, c.wsy + c.wsh); ++y) {
+        uint32_t id;
+        std::memcpy(&id, &c.wdict[(size_t)4 * (y - c.wsy)], sizeof id);
+        std::memcpy(&masks[i][(size_t)(y - r.y) * c.mask_row + (x0 - r.x)],
+                    &c.wdict[(size_t)4 * c.wsh + (size_t)id * c.wsw + (x0 - c.wsx)], x1 - x0);
+      }
     }
-    st = upload(p->ws + c.off_mask0, masks[i].data(), masks[i].size(), s, "seam weight upload");
+    return STITCH_OK;
+  });
+  if (st) {
+    p->ws = nullptr;
+    return st;
   }
+  for (int i = 0; i < p->n && !st; ++i)
+    st = upload(p->ws + p->cam[i].off_mask0, masks[i].data(), masks[i].size(), s, "seam weight upload");
   for (int k = 0; k + 1 < p->L && !st; ++k)
     st = upload(p->ws + p->off_items[k], p->items[k].data(), p->items[k].size() * sizeof(PyrItem), s, "table upload");
   for (int k = 0; k < p->L && !st; ++k)
@@ -1294,10 +1302,8 @@ stitch_status stitch_plan_bind(stitch_plan* p, void* workspace, size_t bytes, vo
   if (!st)
     st = upload(p->ws + p->off_bitems, p->bitems.data(), p->bitems.size() * sizeof(BlendItem), s, "table upload");
   if (!st) st = upload(p->ws + p->off_tail, p->tail.data(), p->tail.size() * sizeof(TailItem), s, "table upload");
-  if (!st) {
-    const hipError_t e = hipStreamSynchronize(s);
-    if (e != hipSuccess) st = hip_fail(e, "bind synchronise");
-  }
+  const hipError_t e = hipStreamSynchronize(s);        // also after a failed upload: the copies before it read masks
+  if (!st && e != hipSuccess) st = hip_fail(e, "bind synchronise");
   if (st) p->ws = nullptr;
   return st;
 }

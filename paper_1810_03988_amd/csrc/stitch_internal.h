@@ -5,6 +5,8 @@
 #include <stdint.h>
 #include <hip/hip_runtime.h>
 
+#include <new>
+
 #include "stitch.h"
 
 namespace stitch {
@@ -173,6 +175,16 @@ void plan_camera(const stitch_plan* p, int i, PlanCamera* out);
 // Host helpers shared by the API files (stitch_api.cpp).
 stitch_status fail(stitch_status s, const char* fmt, ...);
 stitch_status hip_fail(hipError_t e, const char* what);
+// The body of an entry point that takes host memory: running out of it is a status, not an exception
+// that leaves through C.  (A message short enough to need no memory itself.)
+template <typename F>
+stitch_status guarded(F&& body) {
+  try {
+    return body();
+  } catch (const std::bad_alloc&) {
+    return fail(STITCH_E_UNSUPPORTED, "no host memory");
+  }
+}
 stitch_status check_image(const stitch_image* im, const char* name, int dtype, int layout, int channels);
 bool hinv_spec(const double* H, float out[9], double* sign_out, const char** why);
 // Bounding box {x, y, w, h} of the non-zero bytes of a w x h map; false when there is none.
