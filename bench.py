@@ -90,6 +90,18 @@ KERNEL_KINDS = {
     "k_blend_tail<_Float16, false, true>": "blend_middle/top (f16), small levels",
     "k_blend_tail<float, true, true>": "blend of every level (f32)",
     "k_blend_tail<_Float16, true, true>": "blend of every level (f16)",
+    "k_level0<float, false>": "level 0 copied", "k_level0<_Float16, false>": "level 0 copied",
+    "k_level0<float, true>": "level 0 from bytes (f32)", "k_level0<_Float16, true>": "level 0 from bytes (f16)",
+    "k_tail<float, true>": "stage or frame: small levels (f32)", "k_tail<_Float16, true>": "stage or frame: small levels (f16)",
+    "k_warp<float>": "stage: warp (f32)", "k_warp<_Float16>": "stage: warp (f16)",
+    "k_expand_sub<float>": "stage: band (f32)", "k_expand_sub<_Float16>": "stage: band (f16)",
+    "k_vreduce0<false, true>": "gradient: G_1, Gm_1", "k_vreduce0<false, false>": "gradient: Gm_1",
+    "k_vreduce0<true, true>": "pair loss: G_1, Gm_1", "k_vreduce0<true, false>": "pair loss: Gm_1",
+    "k_vreduce": "gradient: G_k, Gm_k", "k_vblend": "gradient: R_k", "k_vpano": "gradient: R_0",
+    "k_vtileT": "gradient: dR_1, dG_1", "k_vexpandT": "gradient: dR_k", "k_vdg": "gradient: dG_k",
+    "k_vdg0<false>": "gradient: dG_0, map sums", "k_vdg0<true>": "pair loss: dG_0, map sums",
+    "k_vsrcT<false>": "gradient: frames", "k_vsrcT<true>": "pair loss: frames", "k_vsum9": "gradient: map sums' total",
+    "k_gloss": "pair loss: terms", "k_gcells": "pair loss: cells", "k_gpano": "pair loss: dP",
     "k_lorb_clear": "L-ORB clear", "k_lorb_detect": "L-ORB detect (FAST, R, suppression)",
     "k_lorb_select": "L-ORB select (histogram threshold)", "k_lorb_rank": "L-ORB rank",
     "k_lorb_brief": "L-ORB BRIEF",
@@ -105,17 +117,20 @@ COPY_KERNEL_HINT = "neg"
 def _short_kernel(name: str) -> str:
     import re
     name = name.replace("(anonymous namespace)::", "")
-    m = re.search(r"(k_[a-z_]+)<([^()]*)>", name)
+    m = re.search(r"(k_[a-z0-9_]+)<([^()]*)>", name)
     if m:
         return m.group(1) + "<" + m.group(2) + ">"
-    # mangled names (as some rocprofv3 builds report them): this library's kernels
-    m = re.search(r"\d+(k_[a-z_]+?)I(DF16_|f)((?:Lb[01]E)*)E", name)
+    # mangled names (as some rocprofv3 builds report them): this library's kernels, a name's length
+    # before it, then its template arguments (a storage type, flags)
+    m = re.search(r"_GLOBAL__N_1(\d+)(k_\w+)", name)
     if m:
-        flags = ["true" if v == "1" else "false" for v in re.findall(r"Lb([01])E", m.group(3))]
-        return f"{m.group(1)}<{', '.join(['_Float16' if m.group(2) == 'DF16_' else 'float'] + flags)}>"
-    m = re.search(r"_GLOBAL__N_1\d+(k_[a-z0-9_]+?)E", name)
-    if m:
-        return m.group(1)
+        n = int(m.group(1))
+        kernel, rest = m.group(2)[:n], m.group(2)[n:]
+        m = re.match(r"I((?:DF16_|f|Lb[01]E)+)E", rest)
+        if not m:
+            return kernel
+        args = {"DF16_": "_Float16", "f": "float", "Lb1E": "true", "Lb0E": "false"}
+        return f"{kernel}<{', '.join(args[t] for t in re.findall(r'DF16_|f|Lb[01]E', m.group(1)))}>"
     return name.split("(")[0][-90:]
 
 
