@@ -117,7 +117,7 @@ COPY_KERNEL_HINT = "neg"
 def _short_kernel(name: str) -> str:
     import re
     name = name.replace("(anonymous namespace)::", "")
-    m = re.search(r"(k_[a-z0-9_]+)<([^()]*)>", name)
+    m = re.search(r"(k_\w+)<([^()]*)>", name)
     if m:
         return m.group(1) + "<" + m.group(2) + ">"
     # mangled names (as some rocprofv3 builds report them): this library's kernels, a name's length

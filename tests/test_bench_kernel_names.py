@@ -18,6 +18,7 @@ spec.loader.exec_module(bench)
     ("_ZN12_GLOBAL__N_17k_vsrcTILb0EEEvNS_7SrcArgsEPi", "k_vsrcT<false>"),
     ("_ZN12_GLOBAL__N_17k_vpanoENS_8PanoArgsE", "k_vpano"),
     ("void stitch::(anonymous namespace)::k_level0<_Float16, true>(void const*, long)", "k_level0<_Float16, true>"),
+    ("void (anonymous namespace)::k_vsrcT<false>((anonymous namespace)::SrcArgs, int*)", "k_vsrcT<false>"),
 ])
 def test_short_names(name, want):
     assert bench._short_kernel(name) == want
