@@ -429,12 +429,12 @@ def phase_bytes(plan, rig, s, keep_r0=False):
     return out
 
 
-def plain_kinds(L, per_step):
-    """Launch kinds of the plain form's event timing -> the phases each covers in a step
-    (per_step: launches of each kind): the small levels' single launches, which are timed as a
+def plain_kinds(L, per_frame):
+    """Launch kinds of the plain form's event timing -> the phases each covers in a frame
+    (per_frame: launches of each kind): the small levels' single launches, which are timed as a
     level pass and as the top blend (or level 0's), cover every level the others leave."""
-    m = per_step.get("blend_middle", 0)
-    own0 = "blend_top" in per_step
+    m = per_frame.get("blend_middle", 0)
+    own0 = "blend_top" in per_frame
     return {"warp_level0_pass": ["pyr0"], "level_pass": [f"pyr{k}" for k in range(1, L - 1)],
             "blend_level0": [f"blend{k}" for k in range(1 if own0 else L)],
             "blend_middle": [f"blend{k}" for k in range(1, m + 1)],
@@ -1149,25 +1149,30 @@ def kernel_table(plan, rig, timing, steps, s):
     frame, over its launches)."""
     ph = phase_bytes(plan, rig, s)
     table = {}
-    per_step = {kind: launches // steps for kind, (_, launches) in timing.items()}
-    kinds = plain_kinds(rig.levels, per_step)
+    frames = timing["warp_level0_pass"][1]           # one such launch a frame
+    per_frame = {kind: launches // frames for kind, (_, launches) in timing.items()}
+    kinds = plain_kinds(rig.levels, per_frame)
     for kind, (tot_ms, launches) in timing.items():
         keys = kinds.get(kind, [])
-        if not keys or not per_step[kind]:
+        if not keys or not per_frame[kind]:
             continue
-        table[kind] = _row(tot_ms, launches, steps, sum(ph[k] for k in keys) / per_step[kind])
+        table[kind] = _row(tot_ms, launches, steps, sum(ph[k] for k in keys) / per_frame[kind])
     return table
 
 
 def batch_kernel_table(plan, rig, timing, steps, s, njobs):
-    """Batched form: one launch per phase per step covering all njobs frames."""
+    """Batched form: one launch per phase per step covering all njobs frames; small levels that share
+    a launch are timed as the finest of them, which then covers every level up to the next one timed."""
     ph = phase_bytes(plan, rig, s)
     table = {}
     for key, (tot_ms, launches) in sorted(timing.items()):
-        name = phase_name(key)
-        pk = f"{key[0]}{key[1]}"
-        if pk in ph:
-            table[name] = _row(tot_ms, launches, steps, njobs * ph[pk])
+        if f"{key[0]}{key[1]}" not in ph:
+            continue
+        k = key[1] + 1
+        while f"{key[0]}{k}" in ph and (key[0], k) not in timing:
+            k += 1
+        table[phase_name(key)] = _row(tot_ms, launches, steps,
+                                      njobs * sum(ph[f"{key[0]}{i}"] for i in range(key[1], k)))
     return table
 
 
