@@ -453,7 +453,8 @@ __global__ void __launch_bounds__(kThreads, 4) k_pyr(const PyrItem* __restrict__
         // own; the remaining 7 columns of every row are one last round.  (One numbering of
         // all samples cost divisions and per-lane row addresses: the pass of 8 jobs at 640 to 3840
         // columns, FP16, took 174 million instructions and 409 us; with B's shorter rows 144
-        // million and 385 us.)  Above it, samples are numbered through.
+        // million and 385 us; 379 since no sample asks whether its source is there.)  Above
+        // it, samples are numbered through.
         constexpr int NE = NR * EW;
         constexpr int NM = (NR + 3) / 4;
         constexpr int NQ = WARP ? NM + 1 : (NE + kThreads - 1) / kThreads;
